@@ -301,23 +301,23 @@ g4d_status g4d_get_stats(g4d_ctx* ctx, g4d_stats* out, int64_t* active_per_view)
  *                          taking the next tile (in the tile order) from a
  *                          device counter until none is left; N > 0: N such
  *                          workgroups. Results are identical.
- *   G4D_TUNE_LDS_BATCH     list entries the forward rasteriser stages in
- *                          LDS at a time: 64, 128 or 256 (default). Results
- *                          are identical.
+ *   G4D_TUNE_LDS_BATCH     64, 128 or 256 (default): accepted and returned,
+ *                          without effect. The forward rasteriser's waves
+ *                          stage 64 list entries at a time, each its own.
  *   G4D_TUNE_AUTOTUNE      1: the next render that is not being captured
  *                          first times its batch (once, then twice with HIP
  *                          events per candidate) under, in turn,
- *                          G4D_TUNE_SORT_BLOCKS in {512, 1024, 1280, 2048},
- *                          G4D_TUNE_TILE_ORDER x G4D_TUNE_PERSISTENT_BLOCKS
- *                          in {0, 1} x {0, -1}, and G4D_TUNE_LDS_BATCH in
- *                          {64, 128, 256}, keeping the fastest of each group
- *                          before the next, then renders normally. One-shot.
+ *                          G4D_TUNE_SORT_BLOCKS in {512, 1024, 1280, 2048}
+ *                          and G4D_TUNE_TILE_ORDER x
+ *                          G4D_TUNE_PERSISTENT_BLOCKS in {0, 1} x {0, -1},
+ *                          keeping the fastest of each group before the next,
+ *                          then renders normally. One-shot.
  *
  * The rasteriser knobs of a (lds_batch, split_threshold, persistent_blocks)
- * tuning call map to these keys: lds_batch -> G4D_TUNE_LDS_BATCH (the
- * forward's batch; the backward stages 12 entries at a time, fixed by its
- * LDS budget of five workgroups per CU and its 12-primitive x 16-column
- * second phase); persistent_blocks -> G4D_TUNE_PERSISTENT_BLOCKS;
+ * tuning call map to these keys: lds_batch -> G4D_TUNE_LDS_BATCH (without
+ * effect: the forward stages 64 entries per wave, the backward 12 entries at a
+ * time, fixed by its LDS budget of five workgroups per CU and its 12-primitive
+ * x 16-column second phase); persistent_blocks -> G4D_TUNE_PERSISTENT_BLOCKS;
  * split_threshold has no key: heavy tiles are not split. A wave owns an 8x8
  * quarter of its tile, so a split would not shorten its longest walk, and
  * with the tiles taken heaviest first the launch does not end on one heavy

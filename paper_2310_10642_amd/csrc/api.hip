@@ -66,7 +66,7 @@ struct g4d_ctx {
   bool totals_on_device = false;   // the last render was sync-free: its totals are device counters
   bool heavy_first = true;         // rasterise tiles by decreasing list length
   int persistent_blocks = 0;       // rasteriser workgroups taking tiles from a queue (0: one per tile)
-  int lds_batch = 256;             // forward rasteriser: list entries staged in LDS at a time
+  int lds_batch = 256;             // G4D_TUNE_LDS_BATCH as set (no effect)
   bool ellipse_cull = true;        // bin and walk by the alpha-floor ellipse, not its rectangle
   bool autotune_pending = false;   // the next uncaptured render tunes the knobs first
   bool flow_mode = false;          // the render in progress blends flow (Sec. 4.4), not colour
@@ -552,7 +552,7 @@ g4d_status rasterise_round(g4d_ctx* c, const g4d_ctx::Round& r, float* out_rgb, 
   static const float kZero3[3] = {0.f, 0.f, 0.f};
   launch_raster_forward(r.tiles, c->heavy_first ? P<uint32_t>(c->oval) : nullptr,
                         c->persistent_blocks ? P<uint32_t>(c->counters) + kCntQueue : nullptr, c->persistent_blocks,
-                        c->lds_batch, r.v1 - r.v0,
+                        r.v1 - r.v0,
                         P<ViewDev>(c->views_d), P<uint2>(c->ranges), P<uint32_t>(c->ival), P<Record>(c->rec_sorted),
                         c->flow_mode ? kZero3 : c->opts.bg, c->flow_mode ? 2 : 3, c->ellipse_cull, out_rgb,
                         out_depth, out_alpha,
@@ -586,9 +586,8 @@ void render_bufs(g4d_ctx* c, DevBuf** b) {
 // Times the render of this batch under the knobs that do not change results
 // and keeps the fastest, one knob group at a time with the others at their
 // best so far: radix-sort workgroups; tile order x persistent rasteriser
-// (queue of resident workgroups or one workgroup per tile); the forward
-// rasteriser's LDS batch. Each candidate renders once to size its scratch,
-// then twice timed.
+// (queue of resident workgroups or one workgroup per tile). Each candidate
+// renders once to size its scratch, then twice timed.
 g4d_status autotune(g4d_ctx* c, int32_t n_views, const g4d_camera* cams, const float* times, float* rgb, float* dep,
                     float* alp) {
   const bool timing = c->timing;
@@ -629,14 +628,12 @@ g4d_status autotune(g4d_ctx* c, int32_t n_views, const g4d_camera* cams, const f
     return G4D_OK;
   };
   const int blocks[] = {512, 1024, 1280, 2048};
-  const int batches[] = {64, 128, 256};
   if (!st) st = pick(4, [&](int i) { c->sort_blocks = blocks[i]; });
   if (!st)
     st = pick(4, [&](int i) {
       c->heavy_first = (i & 1) != 0;
       c->persistent_blocks = (i & 2) ? -1 : 0;
     });
-  if (!st) st = pick(3, [&](int i) { c->lds_batch = batches[i]; });
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   c->timing = timing;

@@ -165,12 +165,12 @@ void launch_ranges(const uint32_t* n_dev, uint32_t n_max, const uint16_t* ikey, 
 // heaviest lists first. queue (nullable): a device counter; then `blocks`
 // workgroups (-1: as many as stay resident) take tiles from it in that order
 // until they run out (zeroed before the launch); otherwise one workgroup per
-// tile. batch (forward): list entries staged in LDS at a time, 64, 128 or 256.
+// tile.
 // channels: 3 (rgb planes) or 2 (the first two record colour values, e.g. flow).
 // cull: waves walk only the entries whose alpha-floor ellipse meets their
 // quadrant (false: every entry; same results).
-void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* queue, int blocks, int batch,
-                           int n_views, const ViewDev* views, const uint2* ranges, const uint32_t* ival,
+void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* queue, int blocks, int n_views,
+                           const ViewDev* views, const uint2* ranges, const uint32_t* ival,
                            const Record* rec_sorted, const float* bg, int channels, bool cull, float* out_rgb,
                            float* out_depth, float* out_alpha, float* pix_t, uint32_t* pix_last, hipStream_t s);
 // The image loss folded into the backward rasteriser: with kind (1 = L1,

@@ -1,16 +1,24 @@
 // Tile rasteriser: front-to-back alpha blending of Eq. (6) with p_i(t) folded
 // into each primitive's opacity (Sec. 3.2), and its backward pass.
 //
-// One workgroup per 16x16 tile; each of its 4 waves owns an 8x8 quadrant, one
-// pixel per lane. The tile's primitive list is staged through LDS in batches.
-// While staging, each entry's alpha-floor ellipse (the pixels where
-// opacity * exp(power) can reach 1/255) is bounded by a box and tested against
-// the four quadrants; every wave then walks only the entries that can touch
-// its quadrant, 16 at a time under a wave-uniform bit mask with the entry
-// index a constant in each unrolled step (LDS reads at immediate offsets).
-// A skipped entry would have failed the 1/255 test at every pixel of the
-// quadrant, so the blend is unchanged. The per-fragment body is branch-free:
-// skipped and post-stop fragments get alpha 0.
+// A tile is 16x16 pixels, four 8x8 quadrants, one pixel of a quadrant per lane
+// of a wave. The tile's primitive list is staged through LDS in batches. While
+// staging, each entry's alpha-floor ellipse (the pixels where
+// opacity * exp(power) can reach 1/255) is tested against the quadrants; only
+// the entries that can touch a quadrant are walked there. A skipped entry would
+// have failed the 1/255 test at every pixel of the quadrant, so the blend is
+// unchanged.
+//
+// The forward pass gives a wave one, two or all four quadrants of its tile. It
+// is bound by instruction issue and by LDS reads: an entry's nine values come
+// to every lane, 18 LDS cycles per wave and entry at 128 B per cycle, so one
+// quadrant per wave (four waves per tile) keeps a CU's LDS as busy as its four
+// SIMDs' vector ALUs. With four pixels per lane an entry is read once per tile
+// and its offsets and half of its quadratic form are shared by two quadrants.
+// Waves share nothing and meet at no barrier, and a quadrant whose pixels have
+// all stopped is left out at once. 300k primitives, 8 views 1352x1014 (43.5k
+// tiles): 444 -> 351 us against four waves per tile over lists staged by the
+// workgroup.
 //
 // The forward pass keeps only the final transmittance and the number of list
 // entries up to the last contributor per pixel. The backward pass walks the
@@ -201,21 +209,101 @@ __device__ __forceinline__ bool next_item(const uint32_t* __restrict__ order, ui
   return true;
 }
 
+// Index of the lowest set bit (unspecified, but a lane, when there is none).
+__device__ __forceinline__ int lowest(uint64_t m) {
+  int j;
+  asm("s_ff1_i32_b64 %0, %1" : "=s"(j) : "s"(m));
+  return j;
+}
+
+// The front-to-back blend of one pixel per lane. A pixel that is done (or
+// outside the image) has an infinite floor, so no fragment counts any more.
+struct Blend {
+  float T, C0, C1, C2, D, floor;
+  uint32_t last;  // 1 + list position of the last contributor
+};
+
+// A staged list entry.
+struct Entry {
+  float u, v, A, B, C, l2o, z, r, g, b;
+};
+template <bool DEPTH>
+__device__ __forceinline__ Entry staged_entry(const Record& s) {
+  const float4 a = s.a;
+  const float2 b = make_float2(s.b.x, s.b.y);
+  return Entry{a.x, a.y, a.z, a.w, b.x, b.y, DEPTH ? s.b.z : 0.f, s.c.x, s.c.y, s.c.z};
+}
+
+// One entry over one quadrant: p2 = log2 alpha, pos its list position + 1. done
+// is called when the quadrant's last pixel stops.
+template <bool DEPTH, typename Done>
+__device__ __forceinline__ void blend(Blend& s, float p2, const Entry& e, uint32_t pos, const Done& done) {
+  uint64_t go = __ballot(p2 >= s.floor);  // the lanes it counts for
+  if (!go) return;
+  const float a = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(p2), 0.f, kAlphaMax);
+  const float Tn = fmaf(-a, s.T, s.T);
+  const uint64_t stopped = go & __ballot(Tn < kTStop);
+  if (__builtin_expect(stopped != 0ull, 0)) {
+    asm volatile("");  // kept a branch: seldom taken
+    s.floor = p2 >= s.floor && Tn < kTStop ? __builtin_inff() : s.floor;
+    go &= ~stopped;
+    if (!__any(s.floor < 0.f)) done();
+  }
+  // the valid lanes' updates, under their execution mask (in one piece: left
+  // to itself the compiler tests the mask and branches around them)
+  float w;
+  uint64_t exec;
+  if (DEPTH)
+    asm("s_and_saveexec_b64 %[x0], %[m]\n\t"
+        "v_mul_f32_e32 %[w], %[a], %[T]\n\t"
+        "v_fmac_f32_e32 %[c0], %[w], %[x]\n\t"
+        "v_fmac_f32_e32 %[c1], %[w], %[y]\n\t"
+        "v_fmac_f32_e32 %[c2], %[w], %[zc]\n\t"
+        "v_fmac_f32_e32 %[d], %[w], %[z]\n\t"
+        "v_mov_b32_e32 %[T], %[n]\n\t"
+        "v_mov_b32_e32 %[l], %[p]\n\t"
+        "s_mov_b64 exec, %[x0]"
+        : [x0] "=&s"(exec), [w] "=&v"(w), [T] "+v"(s.T), [c0] "+v"(s.C0), [c1] "+v"(s.C1), [c2] "+v"(s.C2),
+          [d] "+v"(s.D), [l] "+v"(s.last)
+        : [m] "s"(go), [a] "v"(a), [n] "v"(Tn), [x] "v"(e.r), [y] "v"(e.g), [zc] "v"(e.b), [z] "v"(e.z),
+          [p] "v"(pos)
+        : "scc");
+  else
+    asm("s_and_saveexec_b64 %[x0], %[m]\n\t"
+        "v_mul_f32_e32 %[w], %[a], %[T]\n\t"
+        "v_fmac_f32_e32 %[c0], %[w], %[x]\n\t"
+        "v_fmac_f32_e32 %[c1], %[w], %[y]\n\t"
+        "v_fmac_f32_e32 %[c2], %[w], %[zc]\n\t"
+        "v_mov_b32_e32 %[T], %[n]\n\t"
+        "v_mov_b32_e32 %[l], %[p]\n\t"
+        "s_mov_b64 exec, %[x0]"
+        : [x0] "=&s"(exec), [w] "=&v"(w), [T] "+v"(s.T), [c0] "+v"(s.C0), [c1] "+v"(s.C1), [c2] "+v"(s.C2),
+          [l] "+v"(s.last)
+        : [m] "s"(go), [a] "v"(a), [n] "v"(Tn), [x] "v"(e.r), [y] "v"(e.g), [zc] "v"(e.b), [p] "v"(pos)
+        : "scc");
+}
+
 // DEPTH: whether the depth plane is written (otherwise its sum is compiled
-// out). BATCH: list entries staged in LDS at a time (64, 128 or 256).
-template <bool DEPTH, int BATCH>
-__global__ void __launch_bounds__(256) k_raster_forward(const uint32_t* __restrict__ order, uint32_t n_items,
-                                                         uint32_t* queue, int n_views,
-                                                         const ViewDev* __restrict__ views,
-                                                         const uint2* __restrict__ ranges,
-                                                         const uint32_t* __restrict__ ival,
-                                                         const Record* __restrict__ recs, float bg0, float bg1,
-                                                         float bg2, int channels, bool cull,
-                                                         float* __restrict__ out_rgb,
-                                                         float* __restrict__ out_depth, float* __restrict__ out_alpha,
-                                                         float* __restrict__ pix_t, uint32_t* __restrict__ pix_last) {
-  __shared__ float4 s_a[BATCH], s_b[BATCH], s_c[BATCH];
-  __shared__ __align__(16) uint8_t s_mask[BATCH];
+// out). NQ: quadrants per wave: 4 (one wave per tile, four pixels per lane), 2
+// (two waves, one over the tile's upper and one over its lower half) or 1.
+// A wave stages 64 list entries at a time in LDS of its own, a lane each, and
+// tests them against its quadrants; then it walks those that can touch any,
+// reading each one's values once for all its quadrants.
+template <bool DEPTH, int NQ>
+__global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __restrict__ order, uint32_t n_items,
+                                                              uint32_t* queue, int n_views,
+                                                              const ViewDev* __restrict__ views,
+                                                              const uint2* __restrict__ ranges,
+                                                              const uint32_t* __restrict__ ival,
+                                                              const Record* __restrict__ recs, float bg0, float bg1,
+                                                              float bg2, int channels, bool cull,
+                                                              float* __restrict__ out_rgb,
+                                                              float* __restrict__ out_depth,
+                                                              float* __restrict__ out_alpha,
+                                                              float* __restrict__ pix_t,
+                                                              uint32_t* __restrict__ pix_last) {
+  constexpr int kWaves = 4 / NQ;
+  __shared__ Record s_rec[kWaves][64];  // staged: (u, v, A, B) (C, log2 opacity, z, -) (r, g, b, -)
   __shared__ uint32_t s_item;
   int tile;
   for (bool first = true; next_item(order, n_items, queue, &s_item, first, tile); first = false) {
@@ -223,91 +311,108 @@ __global__ void __launch_bounds__(256) k_raster_forward(const uint32_t* __restri
   const ViewDev& vw = views[vi];
   const int lt = tile - vw.tile_base;
   const int tx = lt % vw.tiles_x, ty = lt / vw.tiles_x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int px = tx * kTile + (wave & 1) * 8 + (lane & 7);
-  const int py = ty * kTile + (wave >> 1) * 8 + (lane >> 3);
-  const bool inside = px < vw.width && py < vw.height;
-  const float fx = px + 0.5f, fy = py + 0.5f;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int q0 = wave * NQ;  // the wave's first quadrant
+  const int px = tx * kTile + 8 * (q0 & 1) + (lane & 7), py = ty * kTile + 8 * (q0 >> 1) + (lane >> 3);
   const float tile_x0 = (float)(tx * kTile), tile_y0 = (float)(ty * kTile);
+  const float fx[2] = {px + 0.5f, px + 8 + 0.5f};
+  const float fy[2] = {py + 0.5f, py + 8 + 0.5f};
   const uint2 rg = ranges[tile];
-  const int count = (int)(rg.y - rg.x);
+  const uint32_t count = rg.y - rg.x;
+  const uint32_t* list = ival + rg.x;
 
-  float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, D = 0.f;
-  uint32_t last = 0;
-  bool done = !inside;
-  for (int b0 = 0; b0 < count; b0 += BATCH) {
-    if (__syncthreads_count(done) == 256) break;
-    const int e = b0 + threadIdx.x;
-    uint32_t mask = 0u;
-    if (threadIdx.x < BATCH && e < count) {
-      const Record r = recs[ival[rg.x + e]];
-      float4 sa, sb, sc;
-      stage_record(r, sa, sb, sc);
-      s_a[threadIdx.x] = sa;
-      s_b[threadIdx.x] = sb;
-      s_c[threadIdx.x] = sc;
-      if (cull) {
+  Blend s[NQ];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) mask |= quadrant_hit(sa, sb, tile_x0, tile_y0, q) ? (1u << q) : 0u;
-      } else {
-        mask = 0xFu;
-      }
-    }
-    if (threadIdx.x < BATCH) s_mask[threadIdx.x] = (uint8_t)mask;
-    __syncthreads();
-    if (__all(done)) continue;
-    // chunks of 16 entries: a wave-uniform mask of those that can touch this
-    // wave's quadrant, walked with constant LDS offsets
-    const int nb = min(BATCH, count - b0);
-    for (int c0 = 0; c0 < nb; c0 += 16) {
-      const uint32_t m = lane < 16 ? (uint32_t)s_mask[c0 + lane] : 0u;
-      const uint32_t todo = (uint32_t)__ballot((m >> wave) & 1u);
-      // the chunk's first entry as a vector register, so each entry's LDS
-      // reads are immediate offsets from it
-      int cv;
-      asm volatile("v_mov_b32 %0, %1" : "=v"(cv) : "s"(c0));
-      const float4* ca = s_a + cv;
-      const float4* cb = s_b + cv;
-      const float4* cc = s_c + cv;
-      uint32_t last_j = 0u;  // 1 + the chunk's last contributing entry (inline constants)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        if (!((todo >> j) & 1u)) continue;
-        const float4 sa = ca[j];
-        const float4 sb = cb[j];
-        const float p2 = frag_log2(fx - sa.x, fy - sa.y, sa, sb);
-        float a = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(p2), 0.f, kAlphaMax);
-        const bool valid = p2 >= kLog2AlphaMin && !done;  // then a >= 1/255 > 0
-        a = valid ? a : 0.f;
-        const float Tn = fmaf(-a, T, T);
-        const bool stop = Tn < kTStop;  // T >= kTStop always, so stop implies a > 0
-        done = done || stop;
-        a = stop ? 0.f : a;
-        const float4 sc = cc[j];
-        const float w = a * T;
-        C0 = fmaf(w, sc.x, C0);
-        C1 = fmaf(w, sc.y, C1);
-        C2 = fmaf(w, sc.z, C2);
-        if (DEPTH) D = fmaf(w, sb.z, D);
-        T = stop ? T : Tn;
-        last_j = (valid && !stop) ? (uint32_t)(j + 1) : last_j;  // a > 0, as masks
-      }
-      last = last_j ? (uint32_t)(b0 + c0) + last_j : last;
-      if (__all(done)) break;
-    }
+  for (int q = 0; q < NQ; ++q) {
+    const bool inside = px + 8 * (q & 1) < vw.width && py + 8 * (q >> 1) < vw.height;
+    s[q] = Blend{1.f, 0.f, 0.f, 0.f, 0.f, inside ? kLog2AlphaMin : __builtin_inff(), 0u};
   }
-  if (inside) {
-    const long long hw = (long long)vw.width * vw.height;
-    const long long pl = (long long)py * vw.width + px;
+  uint32_t d = (uint32_t)lane < count ? list[lane] : 0u;
+  for (uint32_t b0 = 0; b0 < count; b0 += 64) {
+    uint32_t hits = 0u;  // per lane: the quadrants its entry can touch
+    if (b0 + lane < count) {
+      Record& r = s_rec[wave][lane];
+      float4 sa, sb, sc;
+      stage_record(recs[d], sa, sb, sc);
+      r.a = sa;
+      r.b = sb;
+      r.c = sc;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) hits |= !cull || quadrant_hit(sa, sb, tile_x0, tile_y0, q0 + q) ? 1u << q : 0u;
+    }
+    d = b0 + 64 + lane < count ? list[b0 + 64 + lane] : 0u;  // the next entries' records
+    uint32_t live = 0u;  // the quadrants with a pixel still going
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) live |= __any(s[q].floor < 0.f) ? 1u << q : 0u;
+    if (!live) break;
+    uint64_t any = __ballot(hits & live);
+    __builtin_amdgcn_wave_barrier();  // (compiler only: the wave's LDS accesses are in order)
+    const auto walk = [&](const Entry& e, int j) {
+      const uint32_t touch = __builtin_amdgcn_readlane(hits, j) & live;
+      uint32_t pos = b0 + j + 1;
+      asm("" : "+v"(pos));  // a vector register from here on
+      const float dx[2] = {fx[0] - e.u, fx[1] - e.u};
+      float row1[2], row2[2];
+#pragma unroll
+      for (int h = 0; h < (NQ + 1) / 2; ++h) {
+        const float dy = fy[h] - e.v;
+        row1[h] = e.B * dy;
+        row2[h] = fmaf(e.C * dy, dy, e.l2o);
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        if (NQ > 1 && !__builtin_expect((touch >> q) & 1u, 1)) continue;
+        const float dq = dx[q & 1];
+        const float p2 = fmaf(dq, fmaf(e.A, dq, row1[q >> 1]), row2[q >> 1]);
+        blend<DEPTH>(s[q], p2, e, pos, [&] {
+          live &= ~(1u << q);
+          any &= __ballot(hits & live);
+        });
+      }
+    };
+    const Record* stage = s_rec[wave];
+    if constexpr (NQ == 1) {
+      // few waves: the next entry's LDS reads are in flight while one is blended
+      if (any) {
+        int j0 = lowest(any), j1;
+        Entry e0 = staged_entry<DEPTH>(stage[j0]), e1;
+        for (;;) {
+          any &= ~(1ull << j0);
+          j1 = lowest(any) & 63;
+          e1 = staged_entry<DEPTH>(stage[j1]);
+          walk(e0, j0);
+          if (!any) break;
+          any &= ~(1ull << j1);
+          j0 = lowest(any) & 63;
+          e0 = staged_entry<DEPTH>(stage[j0]);
+          walk(e1, j1);
+          if (!any) break;
+        }
+      }
+    } else {
+      while (any) {
+        const int j = lowest(any);
+        any &= ~(1ull << j);
+        walk(staged_entry<DEPTH>(stage[j]), j);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  const long long hw = (long long)vw.width * vw.height;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int x = px + 8 * (q & 1), y = py + 8 * (q >> 1);
+    if (x >= vw.width || y >= vw.height) continue;
+    const long long pl = (long long)y * vw.width + x;
     const long long pix = vw.pix_base + pl;
     float* rgb = out_rgb + channels * vw.pix_base + pl;
-    rgb[0] = fmaf(T, bg0, C0);
-    rgb[hw] = fmaf(T, bg1, C1);
-    if (channels == 3) rgb[2 * hw] = fmaf(T, bg2, C2);
-    if (DEPTH) out_depth[pix] = D;
-    if (out_alpha) out_alpha[pix] = 1.f - T;
-    pix_t[pix] = T;
-    pix_last[pix] = last;
+    rgb[0] = fmaf(s[q].T, bg0, s[q].C0);
+    rgb[hw] = fmaf(s[q].T, bg1, s[q].C1);
+    if (channels == 3) rgb[2 * hw] = fmaf(s[q].T, bg2, s[q].C2);
+    if (DEPTH) out_depth[pix] = s[q].D;
+    if (out_alpha) out_alpha[pix] = 1.f - s[q].T;
+    pix_t[pix] = s[q].T;
+    pix_last[pix] = s[q].last;
   }
   }  // items
 }
@@ -631,14 +736,14 @@ __global__ void __launch_bounds__(256, 5) k_raster_backward(
 // Workgroups of `kernel` that stay resident on the current device (looked
 // up once per kernel and device).
 template <typename K>
-unsigned resident_grid(K kernel) {
+unsigned resident_grid(K kernel, int threads) {
   constexpr int kDevs = 64;
   static unsigned cached[kDevs] = {};
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 1024;
   if (dev >= 0 && dev < kDevs && cached[dev]) return cached[dev];
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu < 1 || cus < 1)
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1 || cus < 1)
     return 1024;
   const unsigned g = (unsigned)(per_cu * cus);
   if (dev >= 0 && dev < kDevs) cached[dev] = g;
@@ -648,44 +753,50 @@ unsigned resident_grid(K kernel) {
 // Grid of a launch over total_tiles items: one workgroup per item, or with
 // a queue, `blocks` workgroups (-1: as many as stay resident).
 template <typename K>
-unsigned item_grid(K kernel, int total_tiles, uint32_t* queue, int blocks, hipStream_t s) {
+unsigned item_grid(K kernel, int threads, int total_tiles, uint32_t* queue, int blocks, hipStream_t s) {
   unsigned grid = (unsigned)total_tiles;
   if (queue) {
-    const unsigned want = blocks > 0 ? (unsigned)blocks : resident_grid(kernel);
+    const unsigned want = blocks > 0 ? (unsigned)blocks : resident_grid(kernel, threads);
     grid = std::min(grid, want);
     launch_fill_u32(queue, 1, 0u, s);
   }
   return grid;
 }
 
-template <bool DEPTH, int BATCH>
+template <bool DEPTH, int NQ>
 void launch_fwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blocks, int n_views,
                 const ViewDev* views, const uint2* ranges, const uint32_t* ival, const Record* rec_sorted,
                 const float* bg, int channels, bool cull, float* out_rgb, float* out_depth, float* out_alpha,
                 float* pix_t, uint32_t* pix_last, hipStream_t s) {
-  const unsigned grid = item_grid(k_raster_forward<DEPTH, BATCH>, total_tiles, queue, blocks, s);
-  hipLaunchKernelGGL((k_raster_forward<DEPTH, BATCH>), dim3(grid), dim3(256), 0, s, order, (uint32_t)total_tiles,
+  const unsigned grid = item_grid(k_raster_forward<DEPTH, NQ>, 256 / NQ, total_tiles, queue, blocks, s);
+  hipLaunchKernelGGL((k_raster_forward<DEPTH, NQ>), dim3(grid), dim3(256 / NQ), 0, s, order, (uint32_t)total_tiles,
                      queue, n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], channels, cull, out_rgb,
                      out_depth, out_alpha, pix_t, pix_last);
 }
 
 }  // namespace
 
-void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* queue, int blocks, int batch,
-                           int n_views, const ViewDev* views, const uint2* ranges, const uint32_t* ival,
+void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* queue, int blocks, int n_views,
+                           const ViewDev* views, const uint2* ranges, const uint32_t* ival,
                            const Record* rec_sorted, const float* bg, int channels, bool cull, float* out_rgb,
                            float* out_depth, float* out_alpha, float* pix_t, uint32_t* pix_last, hipStream_t s) {
   if (total_tiles == 0) return;
-#define G4D_FWD(D, B)                                                                                            \
-  launch_fwd<D, B>(total_tiles, order, queue, blocks, n_views, views, ranges, ival, rec_sorted, bg, channels, cull, \
-                   out_rgb, out_depth, out_alpha, pix_t, pix_last, s)
+  // Quadrants per wave, by the waves that the launch would have (8192 stay
+  // resident): wider waves share more work per entry, but leave a small launch
+  // too few waves and a long tail. Measured (us, one / two / four quadrants per
+  // wave; 300k primitives at 1352x1014): 5.4k tiles 97 / 114 / 173, 10.9k 152 /
+  // 147 / 196, 21.8k 281 / 224 / 256, 32.6k 420 / 325 / 338 (with depth), 43.5k
+  // 446 / 376 / 351.
+#define G4D_FWD(D, NQ)                                                                                            \
+  launch_fwd<D, NQ>(total_tiles, order, queue, blocks, n_views, views, ranges, ival, rec_sorted, bg, channels, cull, \
+                    out_rgb, out_depth, out_alpha, pix_t, pix_last, s)
   const bool d = out_depth != nullptr;
-  if (batch == 64) {
-    if (d) G4D_FWD(true, 64); else G4D_FWD(false, 64);
-  } else if (batch == 128) {
-    if (d) G4D_FWD(true, 128); else G4D_FWD(false, 128);
+  if (total_tiles < 8192) {
+    if (d) G4D_FWD(true, 1); else G4D_FWD(false, 1);
+  } else if (total_tiles < 5 * 8192) {
+    if (d) G4D_FWD(true, 2); else G4D_FWD(false, 2);
   } else {
-    if (d) G4D_FWD(true, 256); else G4D_FWD(false, 256);
+    if (d) G4D_FWD(true, 4); else G4D_FWD(false, 4);
   }
 #undef G4D_FWD
 }
@@ -697,7 +808,7 @@ void launch_bwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blo
                 const float* bg, const float* dl_rgb, const float* dl_depth, const float* dl_alpha,
                 const float* pix_t, const uint32_t* pix_last, double* grad2d, bool mark_blended, bool cull,
                 const LossArgs& loss, hipStream_t s) {
-  const unsigned grid = item_grid(k_raster_backward<HD, HA>, total_tiles, queue, blocks, s);
+  const unsigned grid = item_grid(k_raster_backward<HD, HA>, 256, total_tiles, queue, blocks, s);
   hipLaunchKernelGGL((k_raster_backward<HD, HA>), dim3(grid), dim3(256), 0, s, order, (uint32_t)total_tiles, queue,
                      n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], dl_rgb, dl_depth, dl_alpha, pix_t,
                      pix_last, grad2d, mark_blended, cull, loss);

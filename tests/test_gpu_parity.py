@@ -1395,3 +1395,27 @@ def test_nonfinite_parameters_are_culled_and_counted():
         assert (a[pick] == 0).all(), name
         nb = np.linalg.norm(b)
         assert np.linalg.norm(a[keep] - b) <= 1e-5 * nb, name
+
+
+@pytest.mark.parametrize("views", [683, 3414])
+def test_forward_quadrants_per_wave(views):
+    """The forward rasteriser gives a wave one, two or four quadrants by the
+    launch's tile count (12 tiles a view here, ragged at both edges: 8196 and
+    40968 tiles, just past its two lines). Every view equals its own small
+    render bit for bit, with and without the depth plane, all in one launch
+    and taken from the tile queue."""
+    from paper_2310_10642_amd import g4d
+    r, _ = PT.gpu_setup(_big_splat_scene(61, 400, grow=0.6, sh=1, to=1))
+    cams = [scenegen.ring_camera(0.01 * v, 61, 45) for v in range(views)]
+    times = [(v % 97) / 97.0 for v in range(views)]
+    hw = 61 * 45
+    for queue in (0, -1):
+        r.set_tuning(g4d.G4D_TUNE_PERSISTENT_BLOCKS, queue)
+        rgb, dep, alp = r.render(cams, times)
+        flat = r.render(cams, times, depth=False, alpha=False)[0]
+        assert torch.equal(flat, rgb)
+        r.set_tuning(g4d.G4D_TUNE_PERSISTENT_BLOCKS, 0)
+        for v in (0, 1, views // 2, views - 1):
+            one = r.render([cams[v]], [times[v]])
+            for got, want, k in zip((rgb, dep, alp), one, (3, 1, 1)):
+                assert torch.equal(got[k * hw * v:k * hw * (v + 1)], want), (queue, v, k)
