@@ -37,7 +37,7 @@ struct ViewDev {
 
 // Doubles per active record in the screen-space gradient buffer: one 128-byte
 // line holding dL/du, dL/dv, dL/dconic (3), dL/d(opacity p), dL/drgb (3),
-// dL/dz, padding and (last) the blended flag. The tiles' shares are added in
+// dL/dz, padding and (last) the count of tiles it blended in. The tiles' shares are added in
 // FP64: a long footprint adds terms of both signs from many tiles, whose
 // float32 sum would lose the small total.
 constexpr int kGrad2dStride = 16;

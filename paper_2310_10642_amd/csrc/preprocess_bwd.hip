@@ -54,8 +54,8 @@ __global__ void __launch_bounds__(256) k_bwd_pairs(RenderParams p, const uint32_
   const double2 q2 = *reinterpret_cast<const double2*>(ln + 4), q3 = *reinterpret_cast<const double2*>(ln + 6);
   const double2 q4 = *reinterpret_cast<const double2*>(ln + 8);
   const double gu = q0.x, gv = q0.y, gC0 = q1.x, gC1 = q1.y, gC2 = q2.x, go = q2.y, gdepth = q4.y;
-  // last value of the line: 1 when the record blended some pixel (set by the
-  // rasteriser's backward when statistics are on)
+  // last value of the line: the tiles in which the record blended some pixel
+  // (counted by the rasteriser's backward when statistics are on)
   const bool blended = ln[15] > 0.5;
   // colour = max(0, raw + 0.5): the clamp passes the gradient where the blended colour is positive
   const float4 rc = recs[d].c;
