@@ -18,6 +18,9 @@ constexpr float kTStop = 1e-4f;           // transmittance stop threshold
 constexpr float kColorOffset = 0.5f;
 // log2(1/255): fragments with log2(opacity * exp(power)) below this are skipped
 constexpr float kLog2AlphaMin = -7.994353436858858f;
+// log2(0.99) less a margin over the rounding of log2 and exp2: a fragment of a
+// record whose log2 opacity is below this never reaches the alpha clamp
+constexpr float kLog2AlphaMax = -0.0146f;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // One view of a batch, device side.

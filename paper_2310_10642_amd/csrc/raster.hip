@@ -23,15 +23,14 @@
 // The forward pass keeps only the final transmittance and the number of list
 // entries up to the last contributor per pixel. The backward pass walks the
 // list back to front from there, recovering T_i = T_{i+1} / (1 - a_i), and
-// works in two phases per batch of 12 primitives: (1) each lane (pixel)
-// writes dL/dpower and a_i T_i for the batch into LDS; (2) waves 1-3 regroup
-// as 12 primitives x 16 pixel columns and accumulate the per-primitive sums
-// over the tile's pixels (only over quadrants where the primitive blended),
-// while wave 0 stages the next batch.
-// A 16-lane DPP reduce-scatter per batch combines the columns, leaving each
-// of ten lanes of a primitive's row with one value of its gradient line, and
-// those lanes add the tile's share with one FP64 atomic instruction into one
-// 128-byte line.
+// works in two phases per group of primitives: (1) each pixel's dL/dpower and
+// a_i T_i for the group go into LDS; (2) the lanes regroup as primitives x 16
+// pixel columns and accumulate the per-primitive sums over the tile's pixels.
+// A reduce-scatter per group combines the columns, leaving each of ten lanes
+// of a primitive with one value of its gradient line, and those lanes add the
+// tile's share with one FP64 atomic instruction into one 128-byte line. There
+// are two kernels: one wave per tile (large launches), and four waves per tile
+// in step at barriers, batches of 12 primitives (small ones).
 #include <algorithm>
 #include <type_traits>
 
@@ -45,8 +44,8 @@ using shade::sc_fma;
 // The gradient line's place for the number of tiles in which the record
 // blended (with densification statistics on). An add in the same atomic
 // instruction as the line's values: a plain store of a flag took the lines
-// from the atomics in flight (backward of 500k primitives, 8 views: 1330 us
-// without statistics, 1568 with the store, 1345 with the count).
+// from the atomics in flight (four-wave backward of 500k primitives, 8 views:
+// 1330 us without statistics, 1568 with the store, 1345 with the count).
 constexpr int kBlendedSlot = 15;
 
 // List entries per backward batch. 12 rather than 16: the per-(primitive,
@@ -434,6 +433,33 @@ __device__ __forceinline__ bool ill_conditioned(const Record& r) {
   return det < 0.01f * tr * tr;
 }
 
+// The ten values of a gradient line (dL/du, dL/dv, dL/dconic (3), dL/d(opacity
+// p), dL/drgb (3), dL/dz) from one column's sums. Row moments are about the
+// tile's middle row (offset m = k - 7.5) and moved to the primitive's centre:
+// with dy = dc + m, sum g dy = dc Sg + Sgm and sum g dy^2 = dc^2 Sg + 2 dc Sgm
+// + Sgmm. The 2D-mean, conic and opacity values are linear in the moments, so
+// they are formed before the sum over the columns.
+template <typename G, bool HAS_D>
+__device__ __forceinline__ void form_line(G (&q)[10], bool live, const float4& pa, const float4& pb, G dx, G dc, G Sg,
+                                          G Sgm, G Sgmm, float Sr, float Sgc, float Sb, float Sd) {
+  const G Sgy = sc_fma(dc, Sg, Sgm);
+  const G Sgyy = sc_fma(dc, sc_fma(dc, Sg, (G)2 * Sgm), Sgmm);
+  const G k0 = live ? (G)pa.z * (G)(-2.f / kLog2e) : (G)0, k1 = live ? (G)pa.w * (G)(-1.f / kLog2e) : (G)0;
+  const G k2 = live ? (G)pb.x * (G)(-2.f / kLog2e) : (G)0;
+  const G iop = live ? (G)__builtin_amdgcn_exp2f(-pb.y) : (G)0;
+  const G Sgx = dx * Sg, Sgxy = dx * Sgy;
+  q[0] = sc_fma(k0, Sgx, k1 * Sgy);
+  q[1] = sc_fma(k1, Sgx, k2 * Sgy);
+  q[2] = (G)-0.5 * dx * Sgx;
+  q[3] = -Sgxy;
+  q[4] = (G)-0.5 * Sgyy;
+  q[5] = Sg * iop;
+  q[6] = Sr;
+  q[7] = Sgc;
+  q[8] = Sb;
+  q[9] = HAS_D ? (G)Sd : (G)0;
+}
+
 // Phase 2 of the backward for primitive j2 of the staged batch and pixel
 // column c2: its share of the tile sums over the rows of the quadrants where
 // it blended, formed into the ten values of its gradient line (before the row
@@ -476,28 +502,7 @@ __device__ __forceinline__ void phase2_line(G (&q)[10], bool live, int j2, int c
       }
     }
   }
-  const G Sgy = sc_fma(dc, Sg, Sgm);
-  const G Sgyy = sc_fma(dc, sc_fma(dc, Sg, (G)2 * Sgm), Sgmm);
-  // v: Sg, Sgx, Sgy, Sgxx, Sgxy, Sgyy, w*dL/dr, w*dL/dg, w*dL/db, w*dL/dD
-  // This column's share of the primitive's gradient line (the 2D-mean,
-  // conic and opacity entries are linear in the moments, so they are formed
-  // before the row sum): dL/du, dL/dv, dL/dconic (3), dL/d(opacity p),
-  // dL/drgb (3), dL/dz.
-  const float4 pa = s_a[j2], pb = s_b[j2];
-  const G k0 = live ? (G)pa.z * (G)(-2.f / kLog2e) : (G)0, k1 = live ? (G)pa.w * (G)(-1.f / kLog2e) : (G)0;
-  const G k2 = live ? (G)pb.x * (G)(-2.f / kLog2e) : (G)0;
-  const G iop = live ? (G)__builtin_amdgcn_exp2f(-pb.y) : (G)0;
-  const G Sgx = dx * Sg, Sgxy = dx * Sgy;
-  q[0] = sc_fma(k0, Sgx, k1 * Sgy);
-  q[1] = sc_fma(k1, Sgx, k2 * Sgy);
-  q[2] = (G)-0.5 * dx * Sgx;
-  q[3] = -Sgxy;
-  q[4] = (G)-0.5 * Sgyy;
-  q[5] = Sg * iop;
-  q[6] = Sr;
-  q[7] = Sgc;
-  q[8] = Sb;
-  q[9] = HAS_D ? (G)Sd : (G)0;
+  form_line<G, HAS_D>(q, live, s_a[j2], s_b[j2], dx, dc, Sg, Sgm, Sgmm, Sr, Sgc, Sb, Sd);
 }
 
 // HAS_D / HAS_A: whether dL/d(depth) and dL/d(alpha) are given (otherwise
@@ -742,6 +747,381 @@ __global__ void __launch_bounds__(256, 5) k_raster_backward(
   }  // items
 }
 
+// ---- the backward with one wave per tile ----
+// Four pixels per lane, one of each quadrant, as in the forward with four
+// quadrants per wave: an entry's values are read from LDS once per tile
+// instead of once per quadrant, and the quadrants share its offsets. Groups of
+// four entries alternate between phase 1 and phase 2 (lane 4 c + e sums entry
+// e of the group over pixel column c) within the wave: no barrier, no idle
+// wave. What bounds it is vector instruction issue (SQ counters: 0.93 of the
+// launch); the kernel of four waves per tile moves 1.7 times the LDS
+// instructions and keeps LDS and vector ALUs about equally busy. 10 KB of LDS
+// and 128 registers let four waves share a SIMD. 300k primitives, 8 views
+// 1352x1014: 1100 -> 862 us (with three waves per SIMD 1005, and 1045 with the
+// LDS reads of phase 2 not all ahead of its sums).
+constexpr int kWaveBatch = 4;
+// LDS slots of the group's per-pixel values: the tile's left and right 8
+// columns in planes of their own, in each an entry's 16 rows x 8 columns. A
+// quadrant's write is 64 consecutive words (lane = pixel); a read of one row
+// takes four entries x 16 columns at strides of 8 and 32 words mod 64, so all
+// lanes hit distinct banks.
+constexpr int kWavePrim = 128 + 8;
+constexpr int kWavePlane = kWaveBatch * kWavePrim;
+static_assert(kWavePrim % 64 == 8 && kWavePlane % 64 == 32, "bank-conflict-free strides");
+
+using f32x4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
+
+// Sum of ten values over the 16 columns c of lanes 4 c + e: two reduce-scatter
+// steps over lane bits 5 and 4, each a register swap between wave halves (then
+// rows) and an add, and an all-reduce of the three values left over the row's
+// four columns. Lane 4 c + e ends with value line_slot(lane) of entry e
+// (unspecified where that is -1).
+__device__ __forceinline__ int line_slot(int lane) {
+  const int b4 = (lane >> 4) & 1, i = (lane >> 2) & 3;
+  return i < 3 - b4 ? 5 * (lane >> 5) + 3 * b4 + i : -1;
+}
+__device__ __forceinline__ float swap_add32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_add16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float columns_reduce_scatter10(const float (&q)[10], int lane) {
+  float r[5], s[3];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) r[i] = swap_add32(q[i], q[i + 5]);
+  s[0] = swap_add16(r[0], r[3]);
+  s[1] = swap_add16(r[1], r[4]);
+  s[2] = swap_add16(r[2], r[2]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    s[i] += dpp<0x128>(s[i]);  // row rotations by 8 and 4 lanes: the row's other three columns
+    s[i] += dpp<0x124>(s[i]);
+  }
+  const int i = (lane >> 2) & 3;
+  return i == 0 ? s[0] : (i == 1 ? s[1] : s[2]);
+}
+// The same for the FP64 lines of ill-conditioned footprints (seldom taken).
+__device__ __forceinline__ double columns_reduce_scatter10(const double (&q)[10], int lane) {
+  const int slot = line_slot(lane);
+  double out = 0.0;
+#pragma unroll
+  for (int i = 0; i < 10; ++i) {
+    double v = q[i];
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+    out = slot == i ? v : out;
+  }
+  return out;
+}
+
+// v in the lanes of mask, else 0.
+__device__ __forceinline__ float masked(float v, uint64_t mask) {
+  float r;
+  asm("v_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(v), "s"(mask));
+  return r;
+}
+
+// One pixel's state back to front.
+template <bool HAS_D, bool HAS_A>
+struct BackPixel {
+  float T, beta, g0, g1, g2, gD, gA;
+  uint32_t last;
+};
+
+template <bool HAS_D, bool HAS_A>
+__global__ void __launch_bounds__(64, 4) k_raster_backward_wave(
+    const uint32_t* __restrict__ order, uint32_t n_items, uint32_t* queue, int n_views,
+    const ViewDev* __restrict__ views, const uint2* __restrict__ ranges, const uint32_t* __restrict__ ival,
+    const Record* __restrict__ recs, float bg0, float bg1, float bg2, const float* __restrict__ dl_rgb,
+    const float* __restrict__ dl_depth, const float* __restrict__ dl_alpha, const float* __restrict__ pix_t,
+    const uint32_t* __restrict__ pix_last, double* __restrict__ grad2d, bool mark_blended, bool cull, LossArgs loss) {
+  // per (entry, pixel): dL/dpower, then a_i T_i
+  __shared__ float s_gw[4 * kWavePlane];
+  constexpr int kW = 2 * kWavePlane;
+  __shared__ Record s_rec[32];           // staged: (u, v, A, B) (C, log2 opacity, z, record) (r, g, b, -)
+  static_assert(4 * 256 <= 4 * kWavePlane, "the output gradients pass through s_gw");
+  static_assert(sizeof(s_gw) + sizeof(s_rec) <= 10240, "16 workgroups per CU");
+
+  int tile;
+  uint32_t* s_item = reinterpret_cast<uint32_t*>(s_gw);  // between tiles
+  for (bool first = true; next_item(order, n_items, queue, s_item, first, tile); first = false) {
+  const int vi = find_view(views, n_views, tile);
+  const ViewDev& vw = views[vi];
+  const int lt = tile - vw.tile_base;
+  const int tx = lt % vw.tiles_x, ty = lt / vw.tiles_x;
+  const int lane = threadIdx.x;
+  const int px = tx * kTile + (lane & 7), py = ty * kTile + (lane >> 3);
+  const float tile_x0 = (float)(tx * kTile), tile_y0 = (float)(ty * kTile);
+  const float fx[2] = {px + 0.5f, px + 8 + 0.5f};
+  const float fy[2] = {py + 0.5f, py + 8 + 0.5f};
+  const uint2 rg = ranges[tile];
+  const uint32_t* list = ival + rg.x;
+
+  BackPixel<HAS_D, HAS_A> s[4];
+  uint32_t most[4], least[4];  // per quadrant: largest and smallest last contributor
+  float lsum = 0.f;
+  bool nf = false;
+  // every load first, from the pixel or (outside the image) its nearest one
+  const long long hw = (long long)vw.width * vw.height;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const long long pl = (long long)min(py + 8 * (q >> 1), vw.height - 1) * vw.width + min(px + 8 * (q & 1), vw.width - 1);
+    const long long pix = vw.pix_base + pl;
+    const float* g = dl_rgb + 3 * vw.pix_base + pl;
+    s[q].g0 = g[0];
+    s[q].g1 = g[hw];
+    s[q].g2 = g[2 * hw];
+    s[q].gD = HAS_D ? dl_depth[pix] : 0.f;
+    s[q].gA = HAS_A ? dl_alpha[pix] : 0.f;
+    s[q].T = pix_t[pix];
+    s[q].last = pix_last[pix];
+  }
+  if (loss.kind) {
+    // with a folded loss the rgb input is the rendered image: the loss term
+    // and dL/dC of each channel against the target, formed as the image-loss
+    // kernel forms them
+    float tg[4][3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const long long pl = (long long)min(py + 8 * (q >> 1), vw.height - 1) * vw.width + min(px + 8 * (q & 1), vw.width - 1);
+      const float* t = loss.target + 3 * vw.pix_base + pl;
+      tg[q][0] = t[0];
+      tg[q][1] = t[hw];
+      tg[q][2] = t[2 * hw];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float l = shade::loss_term(loss.kind, s[q].g0 - tg[q][0], loss.scale, s[q].g0) +
+                      shade::loss_term(loss.kind, s[q].g1 - tg[q][1], loss.scale, s[q].g1) +
+                      shade::loss_term(loss.kind, s[q].g2 - tg[q][2], loss.scale, s[q].g2);
+      lsum += px + 8 * (q & 1) < vw.width && py + 8 * (q >> 1) < vw.height ? l : 0.f;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (px + 8 * (q & 1) >= vw.width || py + 8 * (q >> 1) >= vw.height)
+      s[q] = BackPixel<HAS_D, HAS_A>{1.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0u};
+    // only the dot product of the pixel's output gradient with the colour,
+    // depth and alpha of everything behind the current primitive (normalised
+    // by the transmittance after it) enters dL/da; it starts at the background
+    s[q].beta = fmaf(s[q].g0, bg0, fmaf(s[q].g1, bg1, s[q].g2 * bg2));
+    nf = nf || !isfinite(s[q].g0) || !isfinite(s[q].g1) || !isfinite(s[q].g2) || (HAS_D && !isfinite(s[q].gD));
+    most[q] = __builtin_amdgcn_readfirstlane(wave_max_u32(s[q].last));
+    least[q] = __builtin_amdgcn_readfirstlane(wave_min_u32(s[q].last));
+  }
+  const bool tile_nf = __any(nf);
+  if (loss.kind) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
+    if (lane == 0) loss.part[tile] = lsum;  // the tile's loss, summed over its pixels
+  }
+  // phase 2's left operand of row k: value lane & 3 (r, g, b, depth) of pixel
+  // (k, lane >> 2)'s output gradient, turned through LDS
+  float grad[16];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    reinterpret_cast<float4*>(s_gw)[((lane >> 3) + 8 * (q >> 1)) * 16 + (lane & 7) + 8 * (q & 1)] =
+        make_float4(s[q].g0, s[q].g1, s[q].g2, s[q].gD);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) grad[k] = s_gw[64 * k + lane];
+  __builtin_amdgcn_wave_barrier();
+
+  const int total = (int)max(max(most[0], most[1]), max(most[2], most[3]));
+  // the list from its last contributor to its front, 32 entries at a time:
+  // lane i tests entry i against the upper two quadrants, lane 32 + i against
+  // the lower two
+  const int se = lane & 31, sq = (lane >> 5) * 2;
+  const uint32_t most0 = sq ? most[2] : most[0], most1 = sq ? most[3] : most[1];
+  int b0 = ((total + 31) / 32 - 1) * 32;
+  uint32_t d = b0 >= 0 && b0 + se < total ? list[b0 + se] : 0u;
+  for (; b0 >= 0; b0 -= 32) {
+    uint32_t hits = 0u;  // per lane: which of its two quadrants the entry can touch, before their last contributors
+    bool ill = false, clamp = false;
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t p = (uint32_t)(b0 + se);
+    if (p < (uint32_t)total) {
+      const Record r = recs[d];
+      float4 sa, sb, sc;
+      stage_record(r, sa, sb, sc);
+      sb.w = __uint_as_float(d);
+      s_rec[se].a = sa;  // (both lanes of an entry write the same)
+      s_rec[se].b = sb;
+      s_rec[se].c = sc;
+      hits = (p < most0 && (!cull || quadrant_hit(sa, sb, tile_x0, tile_y0, sq)) ? 1u : 0u) |
+             (p < most1 && (!cull || quadrant_hit(sa, sb, tile_x0, tile_y0, sq + 1)) ? 2u : 0u);
+      ill = ill_conditioned(r);
+      clamp = sb.y >= kLog2AlphaMax;
+    }
+    if (b0 >= 32) d = list[b0 - 32 + se];  // the next entries' records
+    const uint64_t touched = __ballot(hits != 0u);
+    uint32_t any = (uint32_t)touched | (uint32_t)(touched >> 32);
+    const uint32_t ills = (uint32_t)__ballot(ill), clamps = (uint32_t)__ballot(clamp);
+    __builtin_amdgcn_wave_barrier();
+    while (any) {
+      // ---- phase 1: up to four entries, back to front ----
+      uint32_t js = 0u, acts = 0u;  // per entry of the group, 8 bits each: its staged index; the quadrants it blended in
+      int n = 0;
+      uint32_t group = 0u;
+      do {
+        const int j = 31 - __builtin_clz(any);
+        any &= ~(1u << j);
+        group |= 1u << j;
+        const uint32_t touch = __builtin_amdgcn_readlane(hits, j) | __builtin_amdgcn_readlane(hits, j + 32) << 2;
+        const uint32_t pos = b0 + j;
+        const float4 sa = s_rec[j].a;
+        const float2 sb = make_float2(s_rec[j].b.x, s_rec[j].b.y);
+        const float z = HAS_D ? s_rec[j].b.z : 0.f;
+        const float4 sc = s_rec[j].c;
+        const float dx[2] = {fx[0] - sa.x, fx[1] - sa.x};
+        float row1[2], row2[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float dy = fy[h] - sa.y;
+          row1[h] = sa.w * dy;
+          row2[h] = fmaf(sb.x * dy, dy, sb.y);
+        }
+        float* gp = s_gw + n * kWavePrim + lane;
+        uint32_t act = 0u;
+        uint32_t clamped = (clamps >> j) & 1u;  // whether its alpha can reach the clamp
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int at = (q & 1) * kWavePlane + (q >> 1) * 64;
+          uint64_t valid = 0ull;
+          float p2 = 0.f;
+          if (__builtin_expect((touch >> q) & 1u, 1)) {
+            const float dq = dx[q & 1];
+            p2 = fmaf(dq, fmaf(sa.z, dq, row1[q >> 1]), row2[q >> 1]);
+            valid = __ballot(p2 >= kLog2AlphaMin);
+            if (pos >= least[q]) {  // (entries before every lane's last contributor need no test)
+              asm volatile("");
+              valid &= __ballot(pos < s[q].last);
+            }
+          }
+          if (__builtin_expect(valid == 0ull, 0)) {
+            gp[at] = 0.f;
+            gp[at + kW] = 0.f;
+            continue;
+          }
+          const float G = __builtin_amdgcn_exp2f(p2);
+          float a = masked(G, valid);
+          asm("" : "+s"(clamped));  // tested anew each time: kept as a flag it would cost vector instructions
+          if (__builtin_expect(clamped != 0u, 0)) {
+            asm volatile("");
+            a = fminf(a, kAlphaMax);
+          }
+          s[q].T = s[q].T * __builtin_amdgcn_rcpf(1.f - a);
+          float dot = fmaf(s[q].g0, sc.x, fmaf(s[q].g1, sc.y, s[q].g2 * sc.z));
+          if (HAS_D) dot = fmaf(s[q].gD, z, dot);
+          if (HAS_A) dot += s[q].gA;
+          const float t = dot - s[q].beta;
+          s[q].beta = fmaf(a, t, s[q].beta);
+          // dL/dpower = dL/da * a for an unclamped alpha (a = G), zero where
+          // the clamp holds; a skipped fragment has a = 0
+          const float w = a * s[q].T;
+          float g = w * t;
+          asm("" : "+s"(clamped));
+          if (__builtin_expect(clamped != 0u, 0)) {
+            asm volatile("");
+            g = G < kAlphaMax ? g : 0.f;
+          }
+          gp[at] = g;
+          gp[at + kW] = w;
+          act |= 1u << q;
+        }
+        js |= (uint32_t)j << (8 * n);
+        acts |= act << (8 * n);
+        ++n;
+      } while (n < kWaveBatch && any);
+      __builtin_amdgcn_wave_barrier();
+      // ---- phase 2: lane 4 c + e, entry e over pixel column c ----
+      const int c = lane >> 2, e = lane & 3;
+      const int je = (js >> (8 * e)) & 31;
+      const uint32_t act = (acts >> (8 * e)) & 0xFu;
+      const float4 pa = s_rec[je].a, pb = s_rec[je].b;
+      const int at = (c >> 3) * kWavePlane + e * kWavePrim + (c & 7);
+      const float* gp = s_gw + at;
+      float gk[16], wk[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) wk[k] = gp[kW + 8 * k];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) gk[k] = gp[8 * k];
+      __builtin_amdgcn_sched_barrier(0);  // all reads in flight before the first sum
+      // the colour and depth sums as 4x4x1 products of 16 blocks (block =
+      // column): the pixel's output gradient times the four entries' a_i T_i,
+      // one FMA each in the order of the rows, the tile's halves apart
+      f32x4 sw[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        sw[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(grad[k], wk[k], sw[0], 0, 0, 0);
+        sw[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(grad[8 + k], wk[8 + k], sw[1], 0, 0, 0);
+      }
+      // the row moments, rows k and 15 - k (at -m and m) together
+      float Sg = 0.f, Sgm = 0.f, Sgmm = 0.f;
+#pragma unroll
+      for (int k = 8; k < 16; ++k) {
+        const float m = (float)k - 7.5f, both = gk[k] + gk[15 - k];
+        Sg += both;
+        Sgm = fmaf(gk[k] - gk[15 - k], m, Sgm);
+        Sgmm = fmaf(both, m * m, Sgmm);
+      }
+      if (tile_nf) {
+        // a non-finite output gradient stays out of the sums of the entries
+        // that did not blend in its quadrant (0 times it is NaN)
+        if (!((act >> (c >> 3)) & 1u)) sw[0] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (!((act >> (2 + (c >> 3))) & 1u)) sw[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      const f32x4 S = sw[0] + sw[1];
+      // (the slots past the group's end hold what an earlier group left there;
+      // their lanes' sums stay in their lanes and are not added)
+      int slot = e < n ? line_slot(lane) : -1;
+      bool add;
+      double val;
+      if (__builtin_expect((ills & group) != 0u, 0)) {
+        // FP64 moments where the four include an ill-conditioned footprint
+        double dg = 0.0, dgm = 0.0, dgmm = 0.0;
+#pragma unroll 1
+        for (int k = 0; k < 16; ++k) {
+          const double g = gp[8 * k], m = (double)k - 7.5;
+          dg += g;
+          dgm = fma(g, m, dgm);
+          dgmm = fma(g, m * m, dgmm);
+        }
+        double q[10];
+        const double dx = (double)(tx * kTile + c) + 0.5 - (double)pa.x;
+        const double dc = (double)(ty * kTile) + 8.0 - (double)pa.y;
+        form_line<double, HAS_D>(q, true, pa, pb, dx, dc, dg, dgm, dgmm, S[0], S[1], S[2], S[3]);
+        val = columns_reduce_scatter10(q, lane);
+        add = val != 0.0;
+      } else {
+        float q[10];
+        const float dx = (float)(tx * kTile + c) + 0.5f - pa.x;
+        const float dc = (float)(ty * kTile) + 8.f - pa.y;
+        form_line<float, HAS_D>(q, true, pa, pb, dx, dc, Sg, Sgm, Sgmm, S[0], S[1], S[2], S[3]);
+        const float v = columns_reduce_scatter10(q, lane);
+        add = v != 0.f;
+        val = (double)v;
+      }
+      const uint32_t rec = __float_as_uint(pb.w);
+      // the record blended in this tile: one more lane counts it in the
+      // gradient line's last value
+      if (mark_blended && c == 15 && e < n && act) {
+        slot = kBlendedSlot;
+        val = 1.0;
+        add = true;
+      }
+      // ten lanes of an entry each add one value of its gradient line, so a
+      // wave's atomics for an entry share one 128-byte line
+      if (slot >= 0 && add) unsafeAtomicAdd(grad2d + (size_t)rec * kGrad2dStride + slot, val);
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  }  // items
+}
+
 // Workgroups of `kernel` that stay resident on the current device (looked
 // up once per kernel and device).
 template <typename K>
@@ -817,6 +1197,18 @@ void launch_bwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blo
                 const float* bg, const float* dl_rgb, const float* dl_depth, const float* dl_alpha,
                 const float* pix_t, const uint32_t* pix_last, double* grad2d, bool mark_blended, bool cull,
                 const LossArgs& loss, hipStream_t s) {
+  // One wave per tile once the launch has five times the 4096 such waves that
+  // stay resident: fewer waves leave a tail of long tiles, each walked by one
+  // wave. Measured (us, four waves per tile / one; 300k primitives at
+  // 1352x1014): 5.4k tiles 200 / 320, 10.9k 290 / 365, 16.3k 421 / 458, 21.8k
+  // 562 / 516, 32.6k 844 / 693, 43.5k 1100 / 862.
+  if (total_tiles >= 5 * 4096) {
+    const unsigned grid = item_grid(k_raster_backward_wave<HD, HA>, 64, total_tiles, queue, blocks, s);
+    hipLaunchKernelGGL((k_raster_backward_wave<HD, HA>), dim3(grid), dim3(64), 0, s, order, (uint32_t)total_tiles,
+                       queue, n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], dl_rgb, dl_depth, dl_alpha,
+                       pix_t, pix_last, grad2d, mark_blended, cull, loss);
+    return;
+  }
   const unsigned grid = item_grid(k_raster_backward<HD, HA>, 256, total_tiles, queue, blocks, s);
   hipLaunchKernelGGL((k_raster_backward<HD, HA>), dim3(grid), dim3(256), 0, s, order, (uint32_t)total_tiles, queue,
                      n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], dl_rgb, dl_depth, dl_alpha, pix_t,

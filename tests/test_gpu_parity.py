@@ -1419,3 +1419,49 @@ def test_forward_quadrants_per_wave(views):
             one = r.render([cams[v]], [times[v]])
             for got, want, k in zip((rgb, dep, alp), one, (3, 1, 1)):
                 assert torch.equal(got[k * hw * v:k * hw * (v + 1)], want), (queue, v, k)
+
+
+@pytest.mark.parametrize("planes", ["rgb", "depth", "alpha", "both", "loss", "nan"])
+def test_backward_one_wave_per_tile(planes):
+    """A launch of 20480 or more tiles takes the one-wave-per-tile backward;
+    the same views in two halves take the four-wave one. Needle footprints
+    (the FP64 moments) and opaque ones (the alpha clamp), ragged 61x45 images
+    (12 tiles a view), odd counts of list entries.
+
+    Both add the same terms: a tile's sums have 256 float32 terms, some 25
+    roundings deep (1.5e-6 of the sum of their magnitudes), in another order,
+    and their totals are added in FP64; 20 times that allows for the
+    cancellation between terms of both signs. A non-finite output gradient
+    makes the same values non-finite."""
+    from paper_2310_10642_amd import g4d
+    views = 1710
+    sc = _needle_scene(62, 151, 1.2, 0.8)
+    sc.opacity_logit[::3] += np.float32(8.0)
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.ring_camera(0.01 * v, 61, 45) for v in range(views)]
+    times = [(v % 97) / 97.0 for v in range(views)]
+    hw, rng = 61 * 45, np.random.default_rng(63)
+    dl = [torch.from_numpy(rng.uniform(-1, 1, k * hw * views).astype(np.float32)).cuda() for k in (3, 1, 1)]
+    if planes == "nan":
+        dl[0][5 * 3 * hw + hw + 777] = float("nan")
+        dl[0][900 * 3 * hw + 1234] = float("inf")
+    use = (planes in ("depth", "both"), planes in ("alpha", "both"))
+
+    def run(v0, v1, grads, accumulate):
+        rgb = r.render(cams[v0:v1], times[v0:v1])[0]
+        a = [x[k * hw * v0:k * hw * v1].contiguous() for x, k in zip(dl, (3, 1, 1))]
+        if planes == "loss":
+            return r.backward_loss(g4d.G4D_LOSS_L2, rgb, a[0], 0.5, loss, out=grads, accumulate=accumulate)
+        return r.backward(a[0], a[1] if use[0] else None, a[2] if use[1] else None, out=grads, accumulate=accumulate)
+
+    loss = torch.zeros(1, device="cuda")
+    g = [x.double().cpu() for x in run(0, views, None, False)]
+    loss_one, loss = float(loss), torch.zeros(1, device="cuda")
+    parts = run(0, views // 2, None, False)
+    ref = [x.double().cpu() for x in run(views // 2, views, parts, True)]
+    for a, b in zip(g, ref):
+        fine = torch.isfinite(b)
+        assert torch.equal(fine, torch.isfinite(a)) and (planes == "nan") == (not bool(fine.all()))
+        a, b = torch.where(fine, a, 0.0), torch.where(fine, b, 0.0)
+        assert float((a - b).norm()) <= 3e-5 * float(b.norm())
+    assert planes != "loss" or abs(loss_one - float(loss)) <= 1e-5 * float(loss)
