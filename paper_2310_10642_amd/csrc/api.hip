@@ -74,7 +74,7 @@ struct g4d_ctx {
   bool no_alloc = false;           // a render_noalloc is in progress: scratch never grows
   void* fixed_scratch = nullptr;   // this device's no-allocation scratch (see g4d_render_noalloc)
 
-  DevBuf views_d, act, pos, dkey, rec, slot, ckey, cval, ckey2, cval2, rec_sorted, tcount, toff;
+  DevBuf views_d, pactive, plisted, pfirst, gcount, dkey, rec, slot, ckey, cval, ckey2, cval2, rec_sorted, toff;
   DevBuf ikey, ival, ikey2, ival2, ranges, pix_t, pix_last, grad2d, scan_scratch, radix_scratch, counters;
   DevBuf bwd_scratch, okey, oval, okey2, oval2, cdir, pany, plist, loss_part;
   uint32_t* counters_h = nullptr;  // pinned
@@ -102,7 +102,7 @@ constexpr int kCntInst64 = 2;     // 64-bit instance total (words 2, 3)
 constexpr int kCntFrag = 4;       // 64-bit fragment sum (words 4, 5)
 constexpr int kCntMaxList = 6;    // longest tile list over the rounds of a render
 constexpr int kCntOverflow = 7;   // sticky: a sync-free render exceeded the instance arena
-constexpr int kCntViews = 8;      // per-view active counts follow
+constexpr int kCntViews = 8;      // per view the active records up to its end (within its round) follow
 constexpr int kMaxViews = 4096;
 // after the views: a sync-free render's totals over its rounds, active
 // records (u32) and instances (64-bit, words +2, +3)
@@ -127,6 +127,8 @@ constexpr size_t kNAInstances = size_t(1) << 22;
 constexpr size_t kNAPixels = size_t(1) << 21;
 constexpr size_t kNATiles = size_t(1) << 16;
 constexpr int kNASortBlocks = 2048;
+// activity groups of a round: its pairs by 256, rounded up per view
+constexpr size_t kNAGroups = kNAPairs / 256 + kMaxViews;
 
 size_t na_align(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -136,8 +138,9 @@ void na_sizes(size_t* out) {
   const size_t P = kNAPairs, I = kNAInstances, X = kNAPixels, T = kNATiles;
   const size_t sizes[] = {
       sizeof(ViewDev) * kMaxViews,                                    // views_d
-      4 * P, 4 * P, 4 * P, 4 * P, 4 * P, 4 * P, 4 * P, 4 * P,         // act pos dkey slot ckey cval ckey2 cval2
-      4 * P, 4 * P,                                                   // tcount toff
+      32 * kNAGroups, 32 * kNAGroups, 16 * kNAGroups, 4 * kNAGroups,  // pactive plisted pfirst gcount
+      4 * P, 4 * P, 4 * P, 4 * P, 4 * P, 4 * P,                       // dkey slot ckey cval ckey2 cval2
+      4 * P,                                                          // toff
       sizeof(Record) * P, sizeof(Record) * P, sizeof(float4) * P,     // rec rec_sorted cdir
       P, 4 * P,                                                       // pany plist (primitives <= P)
       4 * scan_scratch_words(P), 4 * radix_scratch_words(kNASortBlocks),
@@ -147,12 +150,12 @@ void na_sizes(size_t* out) {
       sizeof(uint32_t) * kCntWords};                                  // counters
   for (size_t i = 0; i < sizeof(sizes) / sizeof(sizes[0]); ++i) out[i] = sizes[i];
 }
-constexpr int kNABufs = 30;
+constexpr int kNABufs = 31;
 
 constexpr size_t na_total_bytes() {
   // an upper bound of the carved total (each buffer 256-byte aligned)
-  return (sizeof(ViewDev) * kMaxViews + 256) + 12 * (4 * kNAPairs + 256) + 2 * (48 * kNAPairs + 256) +
-         (16 * kNAPairs + 256) + (5 * kNAPairs + 512) + (4 * (kNAPairs / 4096 + 2) + 256) + (4 * (256 * kNASortBlocks + 256) + 256) +
+  return (sizeof(ViewDev) * kMaxViews + 256) + (84 * kNAGroups + 1024) + 7 * (4 * kNAPairs + 256) +
+         2 * (48 * kNAPairs + 256) + (16 * kNAPairs + 256) + (5 * kNAPairs + 512) + (4 * (kNAPairs / 256 + 4) + 256) + (4 * (256 * kNASortBlocks + 256) + 256) +
          4 * (4 * kNAInstances + 256) + (8 * kNATiles + 256) + 4 * (4 * kNATiles + 256) + 2 * (4 * kNAPixels + 256) +
          (4 * kCntWords + 256);
 }
@@ -337,6 +340,10 @@ RenderParams make_params(g4d_ctx* c, int n_views) {
   return p;
 }
 
+PairBits pair_bits(g4d_ctx* c) {
+  return PairBits{(int)c->n, 4 * pair_groups((int)c->n), P<uint32_t>(c->pactive), P<uint64_t>(c->plisted), P<uint32_t>(c->pfirst)};
+}
+
 // The main stream waits for a colour pass still running on the side stream.
 g4d_status join_side(g4d_ctx* c) {
   if (!c->side_pending) return G4D_OK;
@@ -352,7 +359,7 @@ g4d_status fork_colour(g4d_ctx* c, const RenderParams& p) {
   HIPCHK(c, hipEventRecord(c->ev_fork, c->stream));
   HIPCHK(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
   side_stage_begin(c);
-  launch_colour(p, P<uint32_t>(c->act), P<float4>(c->cdir), P<Record>(c->rec), c->side);
+  launch_colour(p, pair_bits(c), P<float4>(c->cdir), P<Record>(c->rec), c->side);
   side_stage_end(c, G4D_STAGE_COLOUR);
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipEventRecord(c->ev_join, c->side));
@@ -385,18 +392,21 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
   }
   const uint64_t vn = (uint64_t)c->n * nv;
   if ((st = ensure(c, c->views_d, sizeof(ViewDev) * nv))) return st;
-  if ((st = ensure(c, c->act, 4 * vn))) return st;
-  if ((st = ensure(c, c->pos, 4 * vn))) return st;
-  if ((st = ensure(c, c->dkey, 4 * vn))) return st;
+  const size_t vgroups = pair_groups((int)c->n), groups = vgroups * nv;
+  if ((st = ensure(c, c->pactive, 32 * groups))) return st;
+  if ((st = ensure(c, c->plisted, 32 * groups))) return st;
+  if ((st = ensure(c, c->pfirst, 16 * groups))) return st;
+  if ((st = ensure(c, c->gcount, 4 * groups))) return st;
+  const size_t places = 64 * (((size_t)c->n + 63) / 64) * nv;  // a place per pair of every unit
+  if ((st = ensure(c, c->dkey, 4 * places))) return st;
   if ((st = ensure(c, c->slot, 4 * vn))) return st;
-  if ((st = ensure(c, c->rec, sizeof(Record) * vn))) return st;
-  if ((st = ensure(c, c->cdir, sizeof(float4) * vn))) return st;
+  if ((st = ensure(c, c->rec, sizeof(Record) * places))) return st;
+  if ((st = ensure(c, c->cdir, sizeof(float4) * places))) return st;
   if ((st = ensure(c, c->ckey, 4 * vn))) return st;
   if ((st = ensure(c, c->cval, 4 * vn))) return st;
   if ((st = ensure(c, c->ckey2, 4 * vn))) return st;
   if ((st = ensure(c, c->cval2, 4 * vn))) return st;
   if ((st = ensure(c, c->rec_sorted, sizeof(Record) * vn))) return st;
-  if ((st = ensure(c, c->tcount, 4 * vn))) return st;
   if ((st = ensure(c, c->toff, 4 * vn))) return st;
   if ((st = ensure(c, c->pany, (size_t)c->n))) return st;
   if ((st = ensure(c, c->plist, 4 * (size_t)c->n))) return st;
@@ -407,26 +417,23 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
   if (count) p.nonfinite = cnt + kCntNF + v0;
 
   launch_set_views(vr.data(), nv, P<ViewDev>(c->views_d), s);
-  launch_fill_u32(cnt, 4, 0u, s);
-  launch_fill_u32(cnt + kCntPList, 1, 0u, s);
   if (count) launch_fill_u32(cnt + kCntNF + v0, (uint64_t)nv, 0u, s);
   // 1. per (view, primitive): cull, slice, project (the colour follows the
   //    gather, on the second stream)
   stage_begin(c);
-  launch_preprocess(p, P<uint32_t>(c->act), P<uint32_t>(c->dkey), P<Record>(c->rec), P<int32_t>(c->slot),
-                    P<float4>(c->cdir), s);
+  launch_preprocess(p, pair_bits(c), P<uint32_t>(c->gcount), P<uint32_t>(c->dkey),
+                    P<Record>(c->rec), P<float4>(c->cdir), s);
   stage_end(c, G4D_STAGE_PREPROCESS);
   // the records' colours on the second stream, beside the scans and the
   // depth sort (joined before the gather copies the records)
   if ((st = fork_colour(c, p))) return st;
   // 2. compaction of active records
   stage_begin(c);
-  launch_scan(P<uint32_t>(c->act), P<uint32_t>(c->pos), nullptr, (uint32_t)vn, (uint32_t)vn, cnt + kCntA,
-              P<uint32_t>(c->scan_scratch), s, P<uint32_t>(c->dkey), P<uint32_t>(c->ckey), P<uint32_t>(c->cval));
   // per-view counts: at the round's place for a sync-free render, which
   // reads them only after its last round
-  launch_view_counts(P<uint32_t>(c->pos), nv, (uint32_t)c->n, cnt + kCntA,
-                     cnt + kCntViews + (c->totals_on_device ? v0 : 0), s);
+  launch_compact(pair_bits(c), P<uint32_t>(c->gcount), nv, P<uint32_t>(c->dkey), P<uint32_t>(c->ckey),
+                 P<uint32_t>(c->cval), cnt + kCntA,
+                 cnt + kCntViews + (c->totals_on_device ? v0 : 0), P<uint32_t>(c->scan_scratch), s);
   // 3. stable sort by depth; its grid is sized from the active records seen
   // so far (any grid gives the same order: blocks take ranges of the count
   // the device holds)
@@ -436,10 +443,9 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
              (uint32_t)vn, 0, 32, g_depth, P<uint32_t>(c->radix_scratch), s);
   // 4. depth-ordered records, slot map, tiles per record; 5. instance offsets
   if ((st = join_side(c))) return st;
-  launch_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->cval), P<Record>(c->rec), P<Record>(c->rec_sorted),
-                P<int32_t>(c->slot), P<uint32_t>(c->tcount), c->ellipse_cull, cnt + kCntInst64, s);
-  launch_scan(P<uint32_t>(c->tcount), P<uint32_t>(c->toff), cnt + kCntA, 0, (uint32_t)vn, cnt + kCntI,
-              P<uint32_t>(c->scan_scratch), s);
+  launch_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->cval), pair_bits(c), P<Record>(c->rec),
+                P<Record>(c->rec_sorted), P<int32_t>(c->slot), P<uint32_t>(c->toff), c->ellipse_cull,
+                P<uint32_t>(c->scan_scratch), cnt + kCntI, cnt + kCntInst64, s);
   stage_end(c, G4D_STAGE_BINNING);
   HIPCHK(c, hipGetLastError());
   return G4D_OK;
@@ -454,8 +460,11 @@ g4d_status read_pairs(g4d_ctx* c, int v0, int nv, uint32_t& A, uint64_t& inst64)
   HIPCHK(c, hipStreamSynchronize(c->stream));
   A = c->counters_h[kCntA];
   std::memcpy(&inst64, c->counters_h + kCntInst64, sizeof(inst64));
-  std::copy(c->counters_h + vb, c->counters_h + vb + nv, c->view_active.begin() + v0);
-  for (int v = 0; v < nv; ++v) c->active_hint = std::max(c->active_hint, c->counters_h[vb + v]);
+  for (int v = 0; v < nv; ++v) {
+    const uint32_t k = c->counters_h[vb + v] - (v ? c->counters_h[vb + v - 1] : 0u);
+    c->view_active[v0 + v] = k;
+    c->active_hint = std::max(c->active_hint, k);
+  }
   return G4D_OK;
 }
 
@@ -515,13 +524,13 @@ g4d_status bin_tiles(g4d_ctx* c, int tiles, uint32_t a_max, uint32_t cap) {
   // 16-bit keys take a quarter off the sort's bytes per instance
   if (tile_bits <= 16) {
     uint16_t *k16 = static_cast<uint16_t*>(ek), *a16 = static_cast<uint16_t*>(ak);
-    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), cnt + kCntI, cap, rs, ids, (int)c->n, vd,
+    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), P<uint32_t>(c->scan_scratch), cnt + kCntI, cap, rs, ids, (int)c->n, vd,
                 c->ellipse_cull, k16, ev, rg_init, (uint32_t)tiles, s);
     if (passes) radix_sort16(k16, ev, a16, av, cnt + kCntI, cap, 0, tile_bits, g_tile, rsc, s, rg, (uint32_t)tiles);
     else launch_ranges(cnt + kCntI, cap, k16, rg, s);
   } else {
     uint32_t *k32 = static_cast<uint32_t*>(ek), *a32 = static_cast<uint32_t*>(ak);
-    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), cnt + kCntI, cap, rs, ids, (int)c->n, vd,
+    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), P<uint32_t>(c->scan_scratch), cnt + kCntI, cap, rs, ids, (int)c->n, vd,
                 c->ellipse_cull, k32, ev, rg_init, (uint32_t)tiles, s);
     radix_sort(k32, ev, a32, av, cnt + kCntI, cap, 0, tile_bits, g_tile, rsc, s, /*copy_back=*/false, rg,
                (uint32_t)tiles);
@@ -576,8 +585,8 @@ g4d_status resolve_round(g4d_ctx* c, g4d_ctx::Round& r) {
 
 // The render's scratch buffers in the carving order of na_sizes.
 void render_bufs(g4d_ctx* c, DevBuf** b) {
-  DevBuf* l[kNABufs] = {&c->views_d, &c->act,  &c->pos,   &c->dkey,  &c->slot,   &c->ckey,         &c->cval,
-                        &c->ckey2,   &c->cval2, &c->tcount, &c->toff, &c->rec,    &c->rec_sorted,   &c->cdir,
+  DevBuf* l[kNABufs] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey,  &c->slot,   &c->ckey,         &c->cval,
+                        &c->ckey2,   &c->cval2, &c->toff, &c->rec,    &c->rec_sorted,   &c->cdir,
                         &c->pany,    &c->plist, &c->scan_scratch, &c->radix_scratch, &c->ikey, &c->ival, &c->ikey2, &c->ival2, &c->ranges,
                         &c->okey,    &c->oval,  &c->okey2, &c->oval2, &c->pix_t,  &c->pix_last,     &c->counters};
   for (int i = 0; i < kNABufs; ++i) b[i] = l[i];
@@ -697,8 +706,8 @@ g4d_status g4d_destroy(g4d_ctx* c) {
   if (!c) return G4D_EINVAL;
   (void)hipStreamSynchronize(c->stream);
   (void)hipStreamSynchronize(c->side);
-  DevBuf* bufs[] = {&c->views_d, &c->act, &c->pos, &c->dkey, &c->rec, &c->slot, &c->ckey, &c->cval, &c->ckey2,
-                    &c->cval2, &c->rec_sorted, &c->tcount, &c->toff, &c->ikey, &c->ival, &c->ikey2, &c->ival2,
+  DevBuf* bufs[] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey, &c->rec, &c->slot, &c->ckey, &c->cval, &c->ckey2,
+                    &c->cval2, &c->rec_sorted, &c->toff, &c->ikey, &c->ival, &c->ikey2, &c->ival2,
                     &c->ranges, &c->pix_t, &c->pix_last, &c->grad2d, &c->scan_scratch, &c->radix_scratch,
                     &c->counters, &c->bwd_scratch, &c->okey, &c->oval, &c->okey2, &c->oval2, &c->cdir,
                     &c->pany, &c->plist, &c->loss_part};
@@ -828,7 +837,9 @@ g4d_status g4d_render_noalloc(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
   const int64_t round_pairs = c->round_pairs, round_instances = c->round_instances;
   const int sort_blocks = c->sort_blocks;
   const bool timing = c->timing;
-  c->round_pairs = std::min<int64_t>(round_pairs, (int64_t)kNAPairs);
+  // (the pairs' places are padded to whole units of 64 primitives)
+  const int64_t padded = std::max<int64_t>(1, (c->n + 63) / 64 * 64);
+  c->round_pairs = std::min<int64_t>(round_pairs, (int64_t)kNAPairs / padded * std::max<int64_t>(c->n, 1));
   c->round_instances = std::min<int64_t>(round_instances, (int64_t)kNAInstances);
   c->sort_blocks = std::min(sort_blocks, kNASortBlocks);
   c->timing = false;  // stage timing would create events
@@ -1054,7 +1065,7 @@ g4d_status backward_impl(g4d_ctx* c, const LossSpec& ls, const float* rgb_in, co
     }
     RenderParams p = make_params(c, nv);
     stage_begin(c);
-    launch_preprocess_backward(p, P<int32_t>(c->slot), P<double>(c->grad2d), cnt + kCntA, a_max, P<uint32_t>(c->cval),
+    launch_preprocess_backward(p, pair_bits(c), P<int32_t>(c->slot), P<double>(c->grad2d), cnt + kCntA, a_max, P<uint32_t>(c->cval),
                                P<Record>(c->rec_sorted), P<float>(c->bwd_scratch), g_means4, g_log_scales4, g_q_left,
                                g_q_right, g_opacity_logit, g_coeffs, accumulate, c->densify, s);
     stage_end(c, G4D_STAGE_PREPROCESS_BWD);
@@ -1184,7 +1195,9 @@ g4d_status g4d_get_stats(g4d_ctx* c, g4d_stats* out, int64_t* active_per_view) {
     HIPCHK(c, hipMemcpyAsync(c->counters_h + kCntViews, cnt + kCntViews, sizeof(uint32_t) * (kCntWords - kCntViews),
                              hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    std::copy(c->counters_h + kCntViews, c->counters_h + kCntViews + c->n_views, c->view_active.begin());
+    for (const g4d_ctx::Round& r : c->rounds)
+      for (int v = r.v0; v < r.v1; ++v)
+        c->view_active[v] = c->counters_h[kCntViews + v] - (v > r.v0 ? c->counters_h[kCntViews + v - 1] : 0u);
     c->A_total = c->counters_h[kCntTot];
     std::memcpy(&c->I_total, c->counters_h + kCntTot + 2, sizeof(uint64_t));
   }

@@ -77,8 +77,8 @@ struct RenderParams {
   // parameter, indexed by the view within the call (null: not counted)
   uint32_t* nonfinite;
   // written by the preprocess: per primitive, 1 when it is active in some
-  // view of the call; the list of those primitives (in no particular order)
-  // and its length
+  // view of the call; by the colour pass: the list of those primitives (in no
+  // particular order) and its length (zero before)
   uint8_t* pany;
   uint32_t* plist;
   uint32_t* plist_n;
@@ -91,21 +91,42 @@ struct DensifyStats {
   int32_t* blend_count;
 };
 
+// The (view, primitive) pairs of a call. A unit is 64 consecutive primitives,
+// a group four units; there are whole groups. Per view and unit: a bit per
+// active pair, a bit per listed pair (one that a bound of the temporal filter
+// let through; the active ones among them), and the place of its first listed
+// pair. The pairs of a unit take consecutive places in (view, primitive) order
+// from 64 n_views unit on: dkey, rec and cdir are indexed by place.
+struct PairBits {
+  int n;
+  uint32_t units;    // per view
+  uint32_t* active;  // [n_views][units][2]
+  uint64_t* listed;  // [n_views][units]
+  uint32_t* first;   // [n_views][units]
+};
+inline uint32_t pair_groups(int n) { return (uint32_t)(((int64_t)n + 255) / 256); }
+#ifdef __HIPCC__
+// The place of an active pair.
+__device__ __forceinline__ uint32_t pair_place(const PairBits& pb, uint32_t view, uint32_t gidx) {
+  const size_t u = (size_t)view * pb.units + (gidx >> 6);
+  return pb.first[u] + (uint32_t)__popcll(pb.listed[u] & ((1ull << (gidx & 63)) - 1ull));
+}
+#endif
+
 // ---- launchers (preprocess.hip) ----
-// cdir: per (view, primitive) scratch [n_views * n] of (view direction, t - mu_t).
-void launch_preprocess(const RenderParams& p, uint32_t* act, uint32_t* dkey, Record* rec, int32_t* slot,
-                       float4* cdir, hipStream_t s);
-// 4DSH colour of every active pair (act[pair] set by the preprocess) into
-// rec[pair].c.xyz, pair = view * n + primitive, before the gather orders the
-// records by depth; nothing in flow mode.
-void launch_colour(const RenderParams& p, const uint32_t* act, const float4* cdir, Record* rec, hipStream_t s);
+// group_count: the active pairs of each view's groups; cdir: view direction,
+// t - mu_t. dkey, rec and cdir are written for the active pairs.
+void launch_preprocess(const RenderParams& p, const PairBits& pb, uint32_t* group_count, uint32_t* dkey,
+                       Record* rec, float4* cdir, hipStream_t s);
+// Lists the primitives active in some view (p.plist), then the 4DSH colour of
+// every active pair into its record, before the gather orders the records by
+// depth; nothing in flow mode.
+void launch_colour(const RenderParams& p, const PairBits& pb, const float4* cdir, Record* rec, hipStream_t s);
 // ---- launchers (preprocess_bwd.hip) ----
 size_t preprocess_backward_scratch_floats(size_t n_records);
-// Lanes per primitive in k_preprocess for a call of n_views views.
-int preprocess_lanes(int n_views);
 // Workgroups of the kernels that walk the active-primitive list of n primitives.
 unsigned list_grid(int n);
-void launch_preprocess_backward(const RenderParams& p, const int32_t* slot, const double* grad2d,
+void launch_preprocess_backward(const RenderParams& p, const PairBits& pb, const int32_t* slot, const double* grad2d,
                                 const uint32_t* n_records_dev, uint32_t n_records_max, const uint32_t* ids,
                                 const Record* recs, float* scratch, float* g_means4, float* g_log_scales4,
                                 float* g_q_left, float* g_q_right, float* g_opacity_logit, float* g_coeffs,
@@ -116,13 +137,13 @@ void launch_image_loss(int kind, uint64_t n, const float* img, const float* tgt,
                        float* grad, hipStream_t s);
 
 // ---- launchers (sort.hip) ----
-// Exclusive scan of n u32 (n read from n_dev when non-null, else n_host); writes total to *total.
-// With ckey: the input is a 0/1 flag per element, and every flagged element i
-// is also compacted: ckey[out[i]] = dkey[i], cval[out[i]] = i.
+// Scratch words of the compaction and the gather for n_max pairs.
 size_t scan_scratch_words(size_t n_max);
-void launch_scan(const uint32_t* in, uint32_t* out, const uint32_t* n_dev, uint32_t n_host, uint32_t n_max,
-                 uint32_t* total, uint32_t* scratch, hipStream_t s, const uint32_t* dkey = nullptr,
-                 uint32_t* ckey = nullptr, uint32_t* cval = nullptr);
+// The active pairs in (view, primitive) order: ckey[i] = dkey[place], cval[i] =
+// view * n + primitive; their number in *total, and after each view's last in view_end[view].
+// scratch: scan scratch words.
+void launch_compact(const PairBits& pb, const uint32_t* count, int n_views, const uint32_t* dkey, uint32_t* ckey,
+                    uint32_t* cval, uint32_t* total, uint32_t* view_end, uint32_t* scratch, hipStream_t s);
 // LSD radix sort of (key, value) pairs on bits [bit0, bit1) in 8-bit passes
 // that ping-pong via alt; the result ends in keys/vals, copied back after an
 // odd number of passes unless copy_back is false (then it is in the alt pair).
@@ -143,22 +164,23 @@ void radix_sort16(uint16_t* keys, uint32_t* vals, uint16_t* keys_alt, uint32_t* 
                   uint2* last_ranges = nullptr, uint32_t n_ranges = 0);
 void launch_ranges_init(uint2* ranges, uint32_t tiles, hipStream_t s);
 void launch_ranges_fix(uint2* ranges, uint32_t tiles, hipStream_t s);
-// Depth-ordered records, slot map (view*n + index -> depth position), tiles per record,
-// and the 64-bit instance total (to detect 32-bit overflow) in inst64[0..1].
+// Depth-ordered records, slot map (view*n + index -> depth position; of active pairs), and
+// the place of each record's first instance: toff[d] from its 256-record
+// block's start boff[d / 256]. The instance total in *total, and as 64 bits (to
+// detect 32-bit overflow) in total64[0..1]. boff: scan scratch words.
 // exact: count only the rectangle's tiles the record's alpha-floor ellipse reaches.
-void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const Record* rec, Record* rec_sorted,
-                   int32_t* slot, uint32_t* tcount, bool exact, uint32_t* inst64, hipStream_t s);
-void launch_view_counts(const uint32_t* pos, int n_views, uint32_t n, const uint32_t* total, uint32_t* out,
-                        hipStream_t s);
+void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
+                   const Record* rec, Record* rec_sorted, int32_t* slot, uint32_t* toff, bool exact, uint32_t* boff,
+                   uint32_t* total, uint32_t* total64, hipStream_t s);
 // Instances beyond min(*total, cap) are not written; exact as for launch_gather.
 // Keys are 16-bit when the round's tile ids are below 2^16, else 32-bit. With
 // ranges_init, the launch also sets ranges_init[0..tiles) to (~0u, 0), the
 // start state of the ranges the sort's last pass fills.
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* total, uint32_t cap,
-                 const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total,
+                 uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
                  uint32_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s);
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* total, uint32_t cap,
-                 const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total,
+                 uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
                  uint16_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s);
 void launch_ranges(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ikey, uint2* ranges, hipStream_t s);
 void launch_ranges(const uint32_t* n_dev, uint32_t n_max, const uint16_t* ikey, uint2* ranges, hipStream_t s);

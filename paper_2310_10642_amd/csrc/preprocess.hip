@@ -1,6 +1,5 @@
-// Per-primitive stages of the 4D Gaussian render. k_preprocess (one thread
-// per primitive, looping over the views of a batch so the parameters are
-// read once): 4D covariance Sigma = R S S^T R^T with R = L(q_l) R(q_r)
+// Per-primitive stages of the 4D Gaussian render. k_preprocess (all views of a
+// batch at once): 4D covariance Sigma = R S S^T R^T with R = L(q_l) R(q_r)
 // (Sec. 3.2, "Representation of 4D Gaussian"), temporal marginal and filter
 // (Sec. 3.2 and Sec. 4.2), conditional 3D Gaussian at t (Sec. 3.2), EWA
 // projection (Eqs. 3-4), footprint and tile rectangle -- and, for a flow
@@ -13,6 +12,8 @@
 // pairs, written into their depth-ordered records once the gather has placed
 // them; it reads the coefficients of the primitives active in some view only.
 // The backward is in preprocess_bwd.hip.
+#include <cmath>
+
 #include "shade.h"
 
 namespace g4d {
@@ -24,46 +25,147 @@ __device__ __forceinline__ bool finite4(float4 a) {
   return isfinite(a.x) && isfinite(a.y) && isfinite(a.z) && isfinite(a.w);
 }
 
-// One thread per primitive, looping over the views of the call (the FP64
-// shape is built once); `lanes` adjacent threads may share a primitive's
-// views (1 here: the FP64 shape would be built once per lane). The lanes of a
-// primitive then agree whether it is active in some view; the first appends
-// it to the list that the colour passes walk.
-__global__ void __launch_bounds__(256) k_preprocess(RenderParams p, int lanes, uint32_t* __restrict__ act,
-                                                    uint32_t* __restrict__ dkey, Record* __restrict__ rec,
-                                                    int32_t* __restrict__ slot, float4* __restrict__ cdir) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int gidx = t / lanes, sub = t - gidx * lanes;
-  const bool live = gidx < p.n;
-  const int gi = live ? gidx : 0;
-  const int vpl = (p.n_views + lanes - 1) / lanes;
-  const int v0 = min(sub * vpl, p.n_views), v1 = min(v0 + vpl, p.n_views);
-  const float4 mu = p.means4[gi];
-  const float4 ls = p.log_scales4[gi];
-  const float4 qlf = p.q_left[gi];
-  const float4 qrf = p.q_right[gi];
-  const float logit = p.opacity_logit[gi];
-  // a primitive with a non-finite parameter is culled in every view (and counted)
-  const bool bad = live && !(finite4(mu) && finite4(ls) && finite4(qlf) && finite4(qrf) && isfinite(logit));
-  bool any = false;
-  if (bad) {
-    for (int vi = v0; vi < v1; ++vi) {
-      const size_t idx = (size_t)vi * p.n + gidx;
-      act[idx] = 0u;
-      slot[idx] = -1;
-      if (p.nonfinite) atomicAdd(p.nonfinite + vi, 1u);
+// A FP32 bound on Sigma_44 from above: Sigma_44 = sum_k (R_3k s_k)^2, every
+// rounding of R_3k (sums of four products of unit-quaternion components, below
+// 1e-6) taken against it, and a relative 1e-4 for the exponentials and the sum.
+__device__ __forceinline__ float sigma44_bound(float4 ql, float4 qr, float4 ls) {
+  const float nl = ql.x * ql.x + ql.y * ql.y + ql.z * ql.z + ql.w * ql.w;
+  const float nr = qr.x * qr.x + qr.y * qr.y + qr.z * qr.z + qr.w * qr.w;
+  // (squares that overflow or lose bits to underflow bound nothing)
+  if (!(fminf(nl, nr) > 1e-30f && fmaxf(nl, nr) < 1e30f)) return INFINITY;
+  const float il = rsqrtf(nl), ir = rsqrtf(nr);
+  float L[4][4], Rr[4][4];
+  isoclinic_left(make_float4(ql.x * il, ql.y * il, ql.z * il, ql.w * il), L);
+  isoclinic_right(make_float4(qr.x * ir, qr.y * ir, qr.z * ir, qr.w * ir), Rr);
+  const float e[4] = {ls.x, ls.y, ls.z, ls.w};
+  float sum = 1e-30f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    float r = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r = fmaf(L[3][i], Rr[i][k], r);
+    const float m = (fabsf(r) + 2e-6f) * expf(e[k]);
+    sum = fmaf(m, m, sum);
+  }
+  return sum * 1.0001f;
+}
+
+// A wave per unit of 64 consecutive primitives, kPreViews views at a time,
+// without barriers between the steps:
+//   1. a lane per primitive: the views in which it can pass the temporal
+//      filter, by a FP32 bound that never drops one (cull2 = -2 log t_cull,
+//      enlarged), and the FP64 shape if there is any, kept in LDS;
+//   2. a lane per such (view, primitive) pair: the exact filter, slice,
+//      projection, footprint, record.
+// The pairs come from ballots, so the lanes of the second step are full: with
+// a thread per primitive and a loop over the views, a wave ran a view's ~300
+// FP64 instructions whenever any of its 64 lanes was active. A pair's outputs
+// do not depend on the lane that computes them.
+// What a pair writes goes to its place in the unit's slab (64 n_views places),
+// the unit's pairs one after the other in (view, primitive) order, so that a
+// wave's 68 bytes per pair fill whole cache lines. Laid out by (view,
+// primitive), with gaps at the culled pairs, it was bound by partial lines.
+// 62 -> 16 us for one view of 300k primitives, 78 -> 31 for 8 of them, 375 ->
+// 132 for 16 views of 1M, 605 -> 218 for 8 of 3M;
+// the same kernel with gaps took 17, 48, 348 and 504;
+// the colour kernels that read the pairs back, 92 -> 86, 560 -> 447, 917 -> 714.
+constexpr int kPreViews = 16;
+struct PreWave {
+  double S[10][64];  // per primitive: Sigma (00 01 02 03 11 12 13 22 23 33)
+  double opa[64];
+  float4 mu[64];
+  uint16_t pair[64 * kPreViews];  // view << 8 | primitive
+  uint32_t act[kPreViews][2];     // the active pairs
+};
+__global__ void __launch_bounds__(256, 3) k_preprocess(RenderParams p, float cull2, PairBits pb,
+                                                       uint32_t* __restrict__ group_count,
+                                                       uint32_t* __restrict__ dkey,
+                                                       Record* __restrict__ rec, float4* __restrict__ cdir) {
+  __shared__ PreWave s_waves[4];
+  __shared__ ViewDev s_view[kPreViews];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  PreWave& w = s_waves[wave];
+  const uint32_t unit = blockIdx.x * 4 + wave;  // (there are whole groups of four units)
+  const int gidx = (int)(unit * 64) + lane;
+  const double t_cull = p.t_cull, near = p.near_plane;
+  const uint64_t lower = (1ull << lane) - 1ull;
+  if (blockIdx.x == 0 && tid == 0) *p.plist_n = 0u;  // for the listing of the active primitives
+  float s44 = 0.f, mu_t = 0.f;
+  bool usable = false, any = false;
+  float4 ls = make_float4(0.f, 0.f, 0.f, 0.f), qlf = ls, qrf = ls;
+  if (gidx < p.n) {
+    const float4 mu = p.means4[gidx];
+    ls = p.log_scales4[gidx];
+    qlf = p.q_left[gidx];
+    qrf = p.q_right[gidx];
+    const float logit = p.opacity_logit[gidx];
+    // a primitive with a non-finite parameter is culled in every view (and counted)
+    usable = finite4(mu) && finite4(ls) && finite4(qlf) && finite4(qrf) && isfinite(logit);
+    if (usable) {
+      s44 = sigma44_bound(qlf, qrf, ls);
+      mu_t = mu.w;
+      w.mu[lane] = mu;
+      w.opa[lane] = (double)logit;  // (its sigmoid with the shape)
+    } else if (p.nonfinite) {
+      for (int vi = 0; vi < p.n_views; ++vi) atomicAdd(p.nonfinite + vi, 1u);
     }
-  } else if (live) {
-    Shape4T<double> sh;
-    build_shape<double>(qlf, qrf, ls, sh);
-    const double opa = 1.0 / (1.0 + exp(-(double)logit));
-    const double t_cull = p.t_cull, near = p.near_plane;
-    for (int vi = v0; vi < v1; ++vi) {
-      const size_t idx = (size_t)vi * p.n + gidx;
-      const ViewDev& vw = p.views[vi];
+  }
+  bool have_shape = false;
+  uint32_t place = unit * 64u * (uint32_t)p.n_views;  // the next pair's
+  for (int vc = 0; vc < p.n_views; vc += kPreViews) {
+    const int nv = min(kPreViews, p.n_views - vc);
+    __syncthreads();  // the previous views are read
+    for (int i = tid; i < nv * (int)(sizeof(ViewDev) / 4); i += 256)
+      reinterpret_cast<uint32_t*>(s_view)[i] = reinterpret_cast<const uint32_t*>(p.views + vc)[i];
+    if (lane < 2 * kPreViews) w.act[lane >> 1][lane & 1] = 0u;
+    __syncthreads();
+    // ---- 1. which pairs can pass the temporal filter ----
+    uint32_t m = 0u;
+    int pairs = 0;
+    for (int v = 0; v < nv; ++v) {
+      const float dt = s_view[v].t - mu_t, dt2 = dt * dt;
+      // (a square out of float's range, or a NaN, is left to the exact test)
+      const bool out = dt2 > cull2 * s44 && dt2 < 3e38f;
+      const bool in = usable && !out;
+      const uint64_t b = __ballot(in);
+      if (in) w.pair[pairs + __popcll(b & lower)] = (uint16_t)(v << 8 | lane);
+      if (lane == 0) {
+        pb.listed[(size_t)(vc + v) * pb.units + unit] = b;
+        pb.first[(size_t)(vc + v) * pb.units + unit] = place + (uint32_t)pairs;
+      }
+      pairs += (int)__popcll(b);
+      m |= in ? 1u : 0u;
+    }
+    if (m && !have_shape) {
+      Shape4T<double> sh;
+      build_shape<double>(qlf, qrf, ls, sh);
+      int k = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = i; j < 4; ++j) w.S[k++][lane] = sh.S[i][j];
+      w.opa[lane] = 1.0 / (1.0 + exp(-w.opa[lane]));
+      have_shape = true;
+    }
+    __builtin_amdgcn_wave_barrier();  // (the wave's LDS accesses are in order)
+    // ---- 2. pairs ----
+    for (int i = lane; i < pairs; i += 64) {
+      const int v = w.pair[i] >> 8, c = w.pair[i] & 255;
+      const ViewDev& vw = s_view[v];
+      Shape4T<double> sh;
+      int k = 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = r; j < 4; ++j) {
+          sh.S[r][j] = w.S[k++][c];
+          sh.S[j][r] = sh.S[r][j];
+        }
+      sh.inv44 = 1.0 / sh.S[3][3];
+      const double opa = w.opa[c];
       // temporal marginal and filter, slice, camera, EWA projection
       ViewGeomT<double> g;
-      bool ok = view_geometry<double>(mu, sh, vw, t_cull, near, g);
+      bool ok = view_geometry<double>(w.mu[c], sh, vw, t_cull, near, g);
       int x0 = 0, x1 = 0, y0 = 0, y1 = 0;
       if (ok) {
         // ---- footprint: integer 3-sigma radius, half-open tile rectangle ----
@@ -100,12 +202,8 @@ __global__ void __launch_bounds__(256) k_preprocess(RenderParams p, int lanes, u
         }
         ok = ok && (x1 > x0) && (y1 > y0);
       }
-      if (!ok) {
-        act[idx] = 0u;
-        slot[idx] = -1;
-        continue;
-      }
-      any = true;
+      if (!ok) continue;
+      const uint32_t at = place + (uint32_t)i;
       const double z = g.pc[2];
       const float zf = (float)z;
       Record r;
@@ -119,41 +217,75 @@ __global__ void __launch_bounds__(256) k_preprocess(RenderParams p, int lanes, u
         const double sc = (double)p.flow_dt * sh.inv44;
         double dp[3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-          dp[i] = sc * ((double)vw.rot[3 * i] * g.v3[0] + (double)vw.rot[3 * i + 1] * g.v3[1] +
-                        (double)vw.rot[3 * i + 2] * g.v3[2]);
+        for (int a = 0; a < 3; ++a)
+          dp[a] = sc * ((double)vw.rot[3 * a] * g.v3[0] + (double)vw.rot[3 * a + 1] * g.v3[1] +
+                        (double)vw.rot[3 * a + 2] * g.v3[2]);
         const double z1 = z + dp[2];
         const bool front = z1 > near;
         const double q = front ? 1.0 / (z * z1) : 0.0;
         r.c = make_float4((float)(vw.fx * (dp[0] * z - g.pc[0] * dp[2]) * q),
                           (float)(vw.fy * (dp[1] * z - g.pc[1] * dp[2]) * q), 0.f, yr);
       } else {
-        // colour: k_colour fills c.xyz of the record's depth-ordered copy from
-        // the view direction and t - mu_t
+        // colour: k_colour fills c.xyz from the view direction and t - mu_t
         r.c = make_float4(0.f, 0.f, 0.f, yr);
-        cdir[idx] = make_float4((float)g.dir[0], (float)g.dir[1], (float)g.dir[2], (float)g.dt);
+        cdir[at] = make_float4((float)g.dir[0], (float)g.dir[1], (float)g.dir[2], (float)g.dt);
       }
-      rec[idx] = r;
-      act[idx] = 1u;
-      dkey[idx] = __float_as_uint(zf);  // z > near > 0: bit order = numeric order
-      slot[idx] = -1;
+      rec[at] = r;
+      dkey[at] = __float_as_uint(zf);  // z > near > 0: bit order = numeric order
+      atomicOr(&w.act[v][c >> 5], 1u << (c & 31));
     }
+    place += (uint32_t)pairs;
+    __syncthreads();
+    // the units' bits and the group's counts
+    if (tid < nv * 8) {
+      const int v = tid >> 3, k = tid & 7;
+      const uint32_t word = s_waves[k >> 1].act[v][k & 1];
+      pb.active[((size_t)(vc + v) * pb.units + 4 * blockIdx.x) * 2 + k] = word;
+      uint32_t c = (uint32_t)__popc(word);  // a group's eight words are in eight adjacent lanes
+      c += __shfl_xor(c, 1, 64);
+      c += __shfl_xor(c, 2, 64);
+      c += __shfl_xor(c, 4, 64);
+      if (k == 0) group_count[(size_t)(vc + v) * gridDim.x + blockIdx.x] = c;
+    }
+    for (int v = 0; v < nv; ++v) any = any || ((w.act[v][lane >> 5] >> (lane & 31)) & 1u);
   }
-  // the primitive's lanes agree on "active in some view"; the first records
-  // it and appends it to the list (one atomic per wave)
-  const int lane = threadIdx.x & 63;
-  const int lead = lane - sub;  // lanes of a primitive never straddle a wave (lanes divides 64)
-  const uint64_t m = __ballot(any);
-  const bool gany = ((m >> lead) & ((lanes >= 64 ? ~0ull : (1ull << lanes) - 1ull))) != 0ull;
-  const bool append = live && sub == 0 && gany;
-  if (live && sub == 0) p.pany[gidx] = gany ? 1 : 0;
-  const uint64_t am = __ballot(append);
-  if (am) {
-    uint32_t base = 0;
-    if (lane == __ffsll((long long)am) - 1) base = atomicAdd(p.plist_n, (uint32_t)__popcll(am));
-    base = __shfl(base, __ffsll((long long)am) - 1, 64);
-    const uint64_t below = lane ? (am & (~0ull >> (64 - lane))) : 0ull;
-    if (append) p.plist[base + (uint32_t)__popcll(below)] = (uint32_t)gidx;
+  if (gidx < p.n) p.pany[gidx] = any ? 1 : 0;
+}
+
+// The primitives active in some view (in no particular order) and their
+// number: 4096 per workgroup, one atomic each (at ~12.5 ns per atomic on one
+// counter, one per wave of the preprocess took 50 us on 300k primitives).
+__global__ void __launch_bounds__(256) k_list_active(const uint8_t* __restrict__ pany, int n,
+                                                     uint32_t* __restrict__ list, uint32_t* __restrict__ list_n) {
+  __shared__ uint32_t s_wave[4], s_base;
+  const int i0 = (int)(blockIdx.x * 4096 + threadIdx.x * 16);
+  uint32_t m = 0u;
+  if (i0 + 16 <= n) {
+    const uint4 q = *reinterpret_cast<const uint4*>(pany + i0);
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int j = 0; j < 16; ++j) m |= ((w[j >> 2] >> (8 * (j & 3))) & 1u) << j;
+  } else {
+    for (int j = 0; j < 16 && i0 + j < n; ++j) m |= (uint32_t)(pany[i0 + j] & 1) << j;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t c = (uint32_t)__popc(m);
+  uint32_t x = c;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(x, off, 64);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) s_wave[wave] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) s_base = atomicAdd(list_n, s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3]);
+  __syncthreads();
+  uint32_t at = s_base + x - c;
+  for (int w = 0; w < wave; ++w) at += s_wave[w];
+  while (m) {
+    const int j = __ffs(m) - 1;
+    m &= m - 1u;
+    list[at++] = (uint32_t)(i0 + j);
   }
 }
 
@@ -173,7 +305,7 @@ constexpr int kColourViews = 8;  // views whose activity flags k_colour loads to
 // c = max(0, 0.5 + sum). A primitive with a non-finite coefficient gets a
 // NaN colour, which the rasterisers read as fully transparent (and the pair
 // is counted as culled).
-__global__ void __launch_bounds__(256) k_colour(RenderParams p, const uint32_t* __restrict__ act,
+__global__ void __launch_bounds__(256) k_colour(RenderParams p, PairBits pb,
                                                 const float4* __restrict__ cdir, Record* __restrict__ rec) {
   const int nb = (p.sh_degree + 1) * (p.sh_degree + 1);
   const int nt = p.t_order + 1;
@@ -203,24 +335,34 @@ __global__ void __launch_bounds__(256) k_colour(RenderParams p, const uint32_t* 
       uint32_t m = 0u;
 #pragma unroll
       for (int w = 0; w < kColourViews; ++w) {
-        ds[w] = (live && v0 + w < p.n_views && act[(size_t)(v0 + w) * p.n + gidx]) ? 1 : -1;
+        ds[w] = -1;
+        if (live && v0 + w < p.n_views) {
+          const int at = (int)pair_place(pb, v0 + w, gidx);
+          ds[w] = pair_active(pb, v0 + w, gidx) ? at : -1;
+        }
         m |= (ds[w] >= 0 ? 1u : 0u) << w;
       }
       uint32_t rounds = (uint32_t)__popc(m);
 #pragma unroll
       for (int off = 4; off < 64; off <<= 1) rounds = max(rounds, (uint32_t)__shfl_xor((int)rounds, off, 64));
-      // the quad's next active view, its record slot and its direction (in flight)
-      int w = m ? __ffs(m) - 1 : -1;
-      m = m ? m & (m - 1u) : 0u;
-      float4 cd = w >= 0 ? cdir[(size_t)(v0 + w) * p.n + gidx] : make_float4(0.f, 0.f, 1.f, 0.f);
-      for (uint32_t r = 0; r < rounds; ++r) {
-        const int wc = w;
-        const float4 cdc = cd;
+      // the quad's next active view, its pair's place and direction (in flight)
+      int w, d;
+      const auto next = [&] {
         w = m ? __ffs(m) - 1 : -1;
         m = m ? m & (m - 1u) : 0u;
-        if (w >= 0) cd = cdir[(size_t)(v0 + w) * p.n + gidx];
+        d = -1;
+#pragma unroll
+        for (int ww = 0; ww < kColourViews; ++ww) d = (ww == w) ? ds[ww] : d;
+      };
+      next();
+      float4 cd = w >= 0 ? cdir[d] : make_float4(0.f, 0.f, 1.f, 0.f);
+      for (uint32_t r = 0; r < rounds; ++r) {
+        const int wc = w, dc = d;
+        const float4 cdc = cd;
+        next();
+        if (w >= 0) cd = cdir[d];
         if (wc < 0) continue;  // uniform per quad
-        float* o = reinterpret_cast<float*>(&rec[(size_t)(v0 + wc) * p.n + gidx].c);
+        float* o = reinterpret_cast<float*>(&rec[dc].c);
         if (bad) {
           if (sub == 0) {
             const float nan = __int_as_float(0x7FC00000);
@@ -259,15 +401,14 @@ __global__ void __launch_bounds__(256) k_colour(RenderParams p, const uint32_t* 
 
 }  // namespace
 
-int preprocess_lanes(int) { return 1; }
-
-void launch_preprocess(const RenderParams& p, uint32_t* act, uint32_t* dkey, Record* rec, int32_t* slot,
-                       float4* cdir, hipStream_t s) {
+void launch_preprocess(const RenderParams& p, const PairBits& pb, uint32_t* group_count, uint32_t* dkey,
+                       Record* rec, float4* cdir, hipStream_t s) {
   if (p.n == 0) return;
-  const int lanes = preprocess_lanes(p.n_views);
-  const uint64_t threads = (uint64_t)p.n * lanes;
-  hipLaunchKernelGGL(k_preprocess, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p, lanes, act, dkey, rec,
-                     slot, cdir);
+  // -2 log t_cull, enlarged past every rounding of the FP32 test (infinite, so
+  // that every pair is listed, for t_cull = 0)
+  const float cull2 = (float)(-2.0 * std::log((double)p.t_cull) * 1.001 + 1e-5);
+  hipLaunchKernelGGL(k_preprocess, dim3(pair_groups(p.n)), dim3(256), 0, s, p, cull2, pb, group_count, dkey, rec,
+                     cdir);
 }
 
 // Workgroups of the kernels that walk the active-primitive list (64 listed
@@ -278,9 +419,11 @@ unsigned list_grid(int n) {
   return need < 1 ? 1 : (need < 16384 ? need : 16384);
 }
 
-void launch_colour(const RenderParams& p, const uint32_t* act, const float4* cdir, Record* rec, hipStream_t s) {
+void launch_colour(const RenderParams& p, const PairBits& pb, const float4* cdir, Record* rec, hipStream_t s) {
   if (p.n == 0 || p.flow) return;
-  hipLaunchKernelGGL(k_colour, dim3(list_grid(p.n)), dim3(256), 0, s, p, act, cdir, rec);
+  hipLaunchKernelGGL(k_list_active, dim3((unsigned)((p.n + 4095) / 4096)), dim3(256), 0, s, p.pany, p.n, p.plist,
+                     p.plist_n);
+  hipLaunchKernelGGL(k_colour, dim3(list_grid(p.n)), dim3(256), 0, s, p, pb, cdir, rec);
 }
 
 }  // namespace g4d

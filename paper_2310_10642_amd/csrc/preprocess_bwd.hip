@@ -164,7 +164,8 @@ constexpr int kBwdColourViews = 8;  // views whose slots k_bwd_colour loads toge
 // Three waves per SIMD (at most 168 VGPRs, a few spilled values) rather than
 // the two its 178 registers allow: it streams every listed primitive's
 // coefficients in and their gradients out.
-__global__ void __launch_bounds__(256, 3) k_bwd_colour(RenderParams p, const int32_t* __restrict__ slot,
+__global__ void __launch_bounds__(256, 3) k_bwd_colour(RenderParams p, PairBits pb,
+                                                     const int32_t* __restrict__ slot,
                                                      const float4* __restrict__ colbuf, float4* __restrict__ cgbuf,
                                                      float* __restrict__ g_coeffs, bool accumulate) {
   const int nb = (p.sh_degree + 1) * (p.sh_degree + 1);
@@ -196,7 +197,11 @@ __global__ void __launch_bounds__(256, 3) k_bwd_colour(RenderParams p, const int
       uint32_t m = 0u;
 #pragma unroll
       for (int w = 0; w < kBwdColourViews; ++w) {
-        ds[w] = (live && v0 + w < p.n_views) ? slot[(size_t)(v0 + w) * p.n + gidx] : -1;
+        ds[w] = -1;
+        if (live && v0 + w < p.n_views) {
+          const int d = slot[(size_t)(v0 + w) * p.n + gidx];  // in flight with the word of bits
+          ds[w] = pair_active(pb, v0 + w, gidx) ? d : -1;
+        }
         m |= (ds[w] >= 0 ? 1u : 0u) << w;
       }
       // rounds: the most active views of a primitive in this wave
@@ -287,7 +292,8 @@ __global__ void __launch_bounds__(256) k_zero_inactive_coeffs(RenderParams p, fl
 // Three waves per SIMD (at most 168 VGPRs, a few spilled values) rather than
 // the two its 174 registers allow: it streams every primitive's parameters in
 // and their gradients out.
-__global__ void __launch_bounds__(128, 3) k_bwd_prims(RenderParams p, const int32_t* __restrict__ slot,
+__global__ void __launch_bounds__(128, 3) k_bwd_prims(RenderParams p, PairBits pb,
+                                                   const int32_t* __restrict__ slot,
                                                    const float4* __restrict__ geo, const float4* __restrict__ cgbuf,
                                                    float4* __restrict__ g_means4, float4* __restrict__ g_log_scales4,
                                                    float4* __restrict__ g_q_left, float4* __restrict__ g_q_right,
@@ -321,8 +327,8 @@ __global__ void __launch_bounds__(128, 3) k_bwd_prims(RenderParams p, const int3
   float st_uv = 0.f, st_t = 0.f;
   int st_n = 0;
   for (int vi = 0; vi < p.n_views; ++vi) {
-    const int d = slot[(size_t)vi * p.n + gidx];
-    if (d < 0) continue;
+    const int d = slot[(size_t)vi * p.n + gidx];  // in flight with the word of bits
+    if (!pair_active(pb, vi, gidx)) continue;
     const float4 a = geo[4 * (size_t)d], b = geo[4 * (size_t)d + 1], c = geo[4 * (size_t)d + 2];
     const float4 e = geo[4 * (size_t)d + 3];
     G4[0][0] += a.x; G4[0][1] += a.y; G4[0][2] += a.z; G4[0][3] += a.w;
@@ -427,7 +433,7 @@ size_t preprocess_backward_scratch_floats(size_t n_records) {
   return n_records * (kGeoFloats + kColFloats + kCgFloats);
 }
 
-void launch_preprocess_backward(const RenderParams& p, const int32_t* slot, const double* grad2d,
+void launch_preprocess_backward(const RenderParams& p, const PairBits& pb, const int32_t* slot, const double* grad2d,
                                 const uint32_t* n_records_dev, uint32_t n_records_max, const uint32_t* ids,
                                 const Record* recs, float* scratch, float* g_means4, float* g_log_scales4,
                                 float* g_q_left, float* g_q_right, float* g_opacity_logit, float* g_coeffs,
@@ -444,8 +450,8 @@ void launch_preprocess_backward(const RenderParams& p, const int32_t* slot, cons
     const uint64_t g = (total + 255) / 256;
     hipLaunchKernelGGL(k_zero_inactive_coeffs, dim3((unsigned)(g < 8192 ? g : 8192)), dim3(256), 0, s, p, g_coeffs);
   }
-  hipLaunchKernelGGL(k_bwd_colour, dim3(list_grid(p.n)), dim3(256), 0, s, p, slot, col, cg, g_coeffs, accumulate);
-  hipLaunchKernelGGL(k_bwd_prims, dim3((p.n + 127) / 128), dim3(128), 0, s, p, slot, geo, cg,
+  hipLaunchKernelGGL(k_bwd_colour, dim3(list_grid(p.n)), dim3(256), 0, s, p, pb, slot, col, cg, g_coeffs, accumulate);
+  hipLaunchKernelGGL(k_bwd_prims, dim3((p.n + 127) / 128), dim3(128), 0, s, p, pb, slot, geo, cg,
                      reinterpret_cast<float4*>(g_means4), reinterpret_cast<float4*>(g_log_scales4),
                      reinterpret_cast<float4*>(g_q_left), reinterpret_cast<float4*>(g_q_right), g_opacity_logit,
                      accumulate, stats);

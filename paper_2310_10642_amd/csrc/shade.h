@@ -296,6 +296,11 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v;
 }
 
+// Whether a pair is active.
+__device__ __forceinline__ bool pair_active(const PairBits& pb, int view, int gidx) {
+  return (pb.active[2 * ((size_t)view * pb.units + (gidx >> 6)) + ((gidx >> 5) & 1)] >> (gidx & 31)) & 1u;
+}
+
 // The colour kernels give each primitive one quad: lane `sub` owns the basis
 // functions lm = 4 sub + i, i < kBasisPerLane, and their coefficients.
 constexpr int kBasisPerLane = 4;

@@ -166,79 +166,73 @@ __global__ void __launch_bounds__(kThreads) k_scan_reduce(const uint32_t* __rest
   if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-// Exclusive scan of the tile: each block's offset is the sum of the block
-// sums before it, added up by the block's own threads (no separate pass over
-// the block sums), and the last block writes the total. With ckey, the input
-// is a 0/1 flag per element and every flagged element i also lands in the
-// compacted arrays: ckey[out[i]] = dkey[i], cval[out[i]] = i (the flagged
-// lanes of one store instruction write a short increasing run of positions).
-__global__ void __launch_bounds__(kThreads) k_scan_apply(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
-                                                          const uint32_t* n_dev, uint32_t n_max,
-                                                          const uint32_t* __restrict__ bsum,
-                                                          uint32_t* __restrict__ total,
-                                                          const uint32_t* __restrict__ dkey,
-                                                          uint32_t* __restrict__ ckey, uint32_t* __restrict__ cval) {
+// ---------------------------------------------------------- compaction ----
+// The active pairs in (view, primitive) order: ckey = depth key, cval = pair
+// id. The bits and a count per 256-pair group come from the preprocess; a
+// workgroup takes 16 groups, four to a wave, which loads its 16 units' words
+// at once and then writes each unit's keys as one run. Its first position is
+// the sum of the groups before it: of whole 4096-group sums (coarse, when
+// there are that many groups) and of the counts after them. view_end[v] gets
+// the position after view v's last pair.
+constexpr int kCompactGroups = 16;
+constexpr int kCoarseGroups = kTileElems;  // groups per coarse sum
+__global__ void __launch_bounds__(kThreads) k_compact(PairBits pb, const uint32_t* __restrict__ count,
+                                                       const uint32_t* __restrict__ coarse, uint32_t groups,
+                                                       const uint32_t* __restrict__ dkey, uint32_t* __restrict__ ckey,
+                                                       uint32_t* __restrict__ cval, uint32_t* __restrict__ total,
+                                                       uint32_t* __restrict__ view_end) {
   __shared__ uint32_t s_wave[4];
-  const uint32_t n = dev_n(n_dev, n_max);
-  const uint32_t nb = (n + kTileElems - 1) / kTileElems;
-  if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) *total = 0u;
-  if (blockIdx.x >= nb) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t g0 = blockIdx.x * kCompactGroups;
+  const uint32_t u0 = (g0 + 4 * wave) * 4, u_end = groups * 4;
+  // lane j < 16: the wave's unit j
+  uint2 act = make_uint2(0u, 0u), lst = make_uint2(0u, 0u);
+  uint32_t first = 0u;
+  if (lane < 16 && u0 + lane < u_end) {
+    act = reinterpret_cast<const uint2*>(pb.active)[u0 + lane];
+    lst = reinterpret_cast<const uint2*>(pb.listed)[u0 + lane];
+    first = pb.first[u0 + lane];
+  }
+  const uint32_t before = (lane < 4 * wave && g0 + lane < groups) ? count[g0 + lane] : 0u;
+  const uint32_t c0 = coarse ? g0 / kCoarseGroups * kCoarseGroups : 0u;
   uint32_t part = 0;
-  for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kThreads) part += bsum[b];
-  uint32_t prefix;
-  block_exclusive_scan(part, s_wave, prefix);  // contains barriers; prefix = the block sums before this block
-  const size_t base = (size_t)blockIdx.x * kTileElems;
-  const bool full = base + kTileElems <= n;
-  uint4 g[4];
-  uint32_t gx[4];  // each group's exclusive offset within the wave
-  uint32_t wsum = 0;
+  if (coarse)
+    for (uint32_t i = threadIdx.x; i < c0 / kCoarseGroups; i += kThreads) part += coarse[i];
+  for (uint32_t i = c0 + threadIdx.x; i < g0; i += kThreads) part += count[i];
+  uint32_t run;
+  block_exclusive_scan(part, s_wave, run);  // contains barriers; run = the pairs before the block
+  uint32_t b16 = before;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    g[j] = load_group(in, base + scan_group(j), n, full);
-    const uint32_t s = g[j].x + g[j].y + g[j].z + g[j].w;
-    const uint32_t inc = wave_inclusive_scan(s);
-    gx[j] = wsum + inc - s;
-    wsum += __shfl(inc, 63, 64);
-  }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) s_wave[wave] = wsum;
-  __syncthreads();
-  uint32_t wbase = prefix, tot = 0;
+  for (int m = 8; m; m >>= 1) b16 += __shfl_xor(b16, m);
+  run += (uint32_t)__builtin_amdgcn_readfirstlane((int)b16);
+  const uint32_t vg = pb.units / 4;
+  uint32_t v = (g0 + 4 * wave) / vg, g = (g0 + 4 * wave) - v * vg;
 #pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
-    const uint32_t c = s_wave[w];
-    wbase += (w < wave) ? c : 0u;
-    tot += c;
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const size_t e = base + scan_group(j);
-    const uint32_t v[4] = {g[j].x, g[j].y, g[j].z, g[j].w};
-    uint32_t o[4];
-    uint32_t run = wbase + gx[j];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      o[i] = run;
-      run += v[i];
-    }
-    if (full) {
-      *reinterpret_cast<uint4*>(out + e) = make_uint4(o[0], o[1], o[2], o[3]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (e + i < n) out[e + i] = o[i];
-    }
-    if (ckey) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (v[i]) {  // a flagged element lies below n
-          ckey[o[i]] = dkey[e + i];
-          cval[o[i]] = (uint32_t)(e + i);
-        }
+  for (int j = 0; j < 16; ++j) {
+    if (u0 + j >= u_end) break;
+    if (j % 4 == 0) {
+      if (j) {
+        if (++g == vg) ++v, g = 0;
       }
+      if (g == 0 && v > 0 && lane == 0) view_end[v - 1] = run;
     }
+    const uint32_t bx = (uint32_t)__builtin_amdgcn_readlane((int)act.x, j);
+    const uint32_t by = (uint32_t)__builtin_amdgcn_readlane((int)act.y, j);
+    if (((lane < 32 ? bx : by) >> (lane & 31)) & 1u) {
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(by, __builtin_amdgcn_mbcnt_lo(bx, 0u));
+      const uint32_t lx = (uint32_t)__builtin_amdgcn_readlane((int)lst.x, j);
+      const uint32_t ly = (uint32_t)__builtin_amdgcn_readlane((int)lst.y, j);
+      const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)first, j) +
+                          __builtin_amdgcn_mbcnt_hi(ly, __builtin_amdgcn_mbcnt_lo(lx, 0u));
+      ckey[run + below] = dkey[at];
+      cval[run + below] = v * (uint32_t)pb.n + g * 256u + 64u * (j % 4) + lane;
+    }
+    run += (uint32_t)(__popc(bx) + __popc(by));
   }
-  if (blockIdx.x + 1 == nb && threadIdx.x == 0) *total = prefix + tot;
+  if (u0 < u_end && u0 + 16 >= u_end && lane == 0) {
+    *total = run;
+    view_end[v] = run;
+  }
 }
 
 // ---------------------------------------------------------- radix sort ----
@@ -523,18 +517,19 @@ __global__ void __launch_bounds__(kThreads) k_rs_downsweep(const K* __restrict__
 
 // ------------------------------------------------------------- gather ----
 __global__ void __launch_bounds__(kThreads) k_gather(const uint32_t* n_dev, uint32_t n_max,
-                                                      const uint32_t* __restrict__ ids, const Record* __restrict__ rec,
+                                                      const uint32_t* __restrict__ ids, PairBits pb,
+                                                      const Record* __restrict__ rec,
                                                       Record* __restrict__ rec_sorted, int32_t* __restrict__ slot,
-                                                      uint32_t* __restrict__ tcount, bool exact,
-                                                      unsigned long long* __restrict__ inst64) {
+                                                      uint32_t* __restrict__ toff, bool exact,
+                                                      uint32_t* __restrict__ bsum) {
   __shared__ uint32_t s_wave[4];
   const uint32_t n = dev_n(n_dev, n_max);
   const uint32_t d = blockIdx.x * blockDim.x + threadIdx.x;
   if (blockIdx.x * blockDim.x >= n) return;
   uint32_t cnt = 0;
   if (d < n) {
-    const uint32_t id = ids[d];
-    const Record r = rec[id];
+    const uint32_t id = ids[d], v = id / (uint32_t)pb.n;
+    const Record r = rec[pair_place(pb, v, id - v * (uint32_t)pb.n)];
     rec_sorted[d] = r;
     slot[id] = (int32_t)d;
     const Footprint f = footprint(r);
@@ -543,26 +538,76 @@ __global__ void __launch_bounds__(kThreads) k_gather(const uint32_t* n_dev, uint
       row_span(f, ty, exact, xa, xb);
       cnt += xb - xa;
     }
-    tcount[d] = cnt;
   }
   uint32_t total;
-  block_exclusive_scan(cnt, s_wave, total);
-  if (threadIdx.x == 0) atomicAdd(inst64, (unsigned long long)total);
+  const uint32_t ex = block_exclusive_scan(cnt, s_wave, total);  // <= 256 * 2^20 tiles
+  if (d < n) toff[d] = ex;
+  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-// Active records per view from the compaction scan: pos[(v+1) n] - pos[v n].
-__global__ void k_view_counts(const uint32_t* __restrict__ pos, int n_views, uint32_t n, const uint32_t* total,
-                              uint32_t* __restrict__ out) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n_views) return;
-  if (n == 0) {
-    out[v] = 0u;
-    return;
+// The gather's block sums to block offsets, in place, by one workgroup, 16
+// sums per thread at a step (4M records); the total, also as 64 bits. The
+// gather's blocks added it to one counter before, some 12 ns each, one after
+// the other, and two passes over the records' counts made the offsets: 57 us
+// with the gather for 0.7M records, 42 now (5 of them here; 10 for 6M records).
+constexpr int kOffsetThreads = 1024;
+__global__ void __launch_bounds__(kOffsetThreads) k_block_offsets(const uint32_t* n_dev, uint32_t n_max,
+                                                                   uint32_t* __restrict__ bsum,
+                                                                   uint32_t* __restrict__ total,
+                                                                   unsigned long long* __restrict__ total64) {
+  __shared__ uint64_t s_wave[2][kOffsetThreads / 64];
+  const uint32_t nb = (dev_n(n_dev, n_max) + kThreads - 1) / kThreads;
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint64_t carry = 0;
+  int side = 0;
+  for (uint32_t b0 = 0; b0 < nb; b0 += 16 * kOffsetThreads, side ^= 1) {
+    const uint32_t e = b0 + 1024u * wave + 4u * lane;
+    uint4 g[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[j] = load_group(bsum, (size_t)e + 256 * j, nb, e + 256 * j + 4 <= nb);
+    uint64_t wsum = 0;
+    uint32_t gx[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint64_t q = (uint64_t)g[j].x + g[j].y + g[j].z + g[j].w;
+      uint64_t inc = q;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint64_t y = __shfl_up(inc, off, 64);
+        if (lane >= (uint32_t)off) inc += y;
+      }
+      gx[j] = (uint32_t)(wsum + inc - q);
+      wsum += __shfl(inc, 63, 64);
+    }
+    if (lane == 0) s_wave[side][wave] = wsum;
+    __syncthreads();
+    uint64_t before = carry;
+#pragma unroll
+    for (uint32_t w = 0; w < kOffsetThreads / 64; ++w) {
+      before += w < wave ? s_wave[side][w] : 0ull;
+      carry += s_wave[side][w];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t i = e + 256 * j;
+      uint4 o;
+      o.x = (uint32_t)before + gx[j];
+      o.y = o.x + g[j].x;
+      o.z = o.y + g[j].y;
+      o.w = o.z + g[j].z;
+      if (i + 4 <= nb) {
+        *reinterpret_cast<uint4*>(bsum + i) = o;
+      } else {
+        if (i < nb) bsum[i] = o.x;
+        if (i + 1 < nb) bsum[i + 1] = o.y;
+        if (i + 2 < nb) bsum[i + 2] = o.z;
+      }
+    }
   }
-  const size_t b = (size_t)v * n;
-  const uint32_t start = pos[b];
-  const uint32_t end = (v + 1 < n_views) ? pos[b + n] : *total;
-  out[v] = end - start;
+  if (threadIdx.x == 0) {
+    *total = (uint32_t)carry;
+    *total64 = carry;
+  }
 }
 
 // ---------------------------------------------------------------- emit ----
@@ -578,7 +623,8 @@ constexpr int kEmitInst = 4096;
 // K: the key type, uint16_t when the round's tile ids are below 2^16.
 template <typename K>
 __global__ void __launch_bounds__(kThreads) k_emit(const uint32_t* n_dev, uint32_t n_max,
-                                                    const uint32_t* __restrict__ toff, const uint32_t* total,
+                                                    const uint32_t* __restrict__ toff,
+                                                    const uint32_t* __restrict__ boff, const uint32_t* total,
                                                     uint32_t cap, const Record* __restrict__ rec_sorted,
                                                     const uint32_t* __restrict__ ids, uint32_t n_prims,
                                                     const ViewDev* __restrict__ views, bool exact,
@@ -606,8 +652,11 @@ __global__ void __launch_bounds__(kThreads) k_emit(const uint32_t* n_dev, uint32
   uint32_t h = 0;
   if (threadIdx.x < kEmitRecs) {
     const uint32_t d = d0 + threadIdx.x;
-    offs[threadIdx.x] = d < n ? toff[d] : tot;
-    if (threadIdx.x == 0) offs[kEmitRecs] = (d0 + kEmitRecs < n) ? toff[d0 + kEmitRecs] : tot;
+    offs[threadIdx.x] = d < n ? boff[d / kThreads] + toff[d] : tot;
+    if (threadIdx.x == 0) {
+      const uint32_t e = d0 + kEmitRecs;
+      offs[kEmitRecs] = e < n ? boff[e / kThreads] + toff[e] : tot;
+    }
     if (d < n) {
       const Footprint f = footprint(rec_sorted[d]);
       s_fp[threadIdx.x] = f;
@@ -795,20 +844,26 @@ inline unsigned grid_for(uint64_t n, unsigned bs) { return (unsigned)((n + bs - 
 
 }  // namespace
 
-size_t scan_scratch_words(size_t n_max) { return (n_max + kTileElems - 1) / kTileElems + 1; }
+size_t scan_scratch_words(size_t n_max) { return (n_max + kThreads - 1) / kThreads + 4; }
 
-void launch_scan(const uint32_t* in, uint32_t* out, const uint32_t* n_dev, uint32_t n_host, uint32_t n_max,
-                 uint32_t* total, uint32_t* scratch, hipStream_t s, const uint32_t* dkey, uint32_t* ckey,
-                 uint32_t* cval) {
-  const uint32_t cap = n_dev ? n_max : n_host;
-  const unsigned nb = grid_for(cap, kTileElems);
-  if (nb == 0) {
+void launch_compact(const PairBits& pb, const uint32_t* count, int n_views, const uint32_t* dkey, uint32_t* ckey,
+                    uint32_t* cval, uint32_t* total, uint32_t* view_end, uint32_t* scratch, hipStream_t s) {
+  const uint32_t view_groups = pb.units / 4;
+  if (view_groups == 0 || n_views == 0) {
     launch_fill_u32(total, 1, 0u, s);
+    launch_fill_u32(view_end, (uint64_t)n_views, 0u, s);
     return;
   }
-  hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kThreads), 0, s, in, n_dev, cap, scratch);
-  hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(kThreads), 0, s, in, out, n_dev, cap, scratch, total, dkey, ckey,
-                     cval);
+  const uint32_t groups = view_groups * (uint32_t)n_views;
+  // up to 16384 groups (4M pairs) a workgroup adds the counts before it itself
+  // (at most 64 loads per thread); beyond, a pass over the counts sums them by
+  // the 4096 first
+  const bool coarse = groups > 4 * (uint32_t)kCoarseGroups;
+  if (coarse)
+    hipLaunchKernelGGL(k_scan_reduce, dim3(grid_for(groups, kTileElems)), dim3(kThreads), 0, s, count, nullptr, groups,
+                       scratch);
+  hipLaunchKernelGGL(k_compact, dim3(grid_for(groups, kCompactGroups)), dim3(kThreads), 0, s, pb, count,
+                     coarse ? scratch : nullptr, groups, dkey, ckey, cval, total, view_end);
 }
 
 size_t radix_scratch_words(int grid) { return (size_t)256 * grid + 256; }
@@ -859,41 +914,43 @@ void radix_sort16(uint16_t* keys, uint32_t* vals, uint16_t* keys_alt, uint32_t* 
                    n_ranges);
 }
 
-void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const Record* rec, Record* rec_sorted,
-                   int32_t* slot, uint32_t* tcount, bool exact, uint32_t* inst64, hipStream_t s) {
-  if (n_max == 0) return;
-  hipLaunchKernelGGL(k_gather, dim3(grid_for(n_max, kThreads)), dim3(kThreads), 0, s, n_dev, n_max, ids, rec,
-                     rec_sorted, slot, tcount, exact, reinterpret_cast<unsigned long long*>(inst64));
-}
-
-void launch_view_counts(const uint32_t* pos, int n_views, uint32_t n, const uint32_t* total, uint32_t* out,
-                        hipStream_t s) {
-  hipLaunchKernelGGL(k_view_counts, dim3(grid_for(n_views, 64)), dim3(64), 0, s, pos, n_views, n, total, out);
+void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
+                   const Record* rec, Record* rec_sorted, int32_t* slot, uint32_t* toff, bool exact, uint32_t* boff,
+                   uint32_t* total, uint32_t* total64, hipStream_t s) {
+  if (n_max == 0) {
+    launch_fill_u32(total, 1, 0u, s);
+    launch_fill_u32(total64, 2, 0u, s);
+    return;
+  }
+  hipLaunchKernelGGL(k_gather, dim3(grid_for(n_max, kThreads)), dim3(kThreads), 0, s, n_dev, n_max, ids, pb,
+                     rec, rec_sorted, slot, toff, exact, boff);
+  hipLaunchKernelGGL(k_block_offsets, dim3(1), dim3(kOffsetThreads), 0, s, n_dev, n_max, boff, total,
+                     reinterpret_cast<unsigned long long*>(total64));
 }
 
 template <typename K>
-void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* total, uint32_t cap,
+void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total, uint32_t cap,
                const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact, K* ikey,
                uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
   if (n_max == 0) {
     if (ranges_init) launch_ranges_init(ranges_init, tiles, s);
     return;
   }
-  hipLaunchKernelGGL(k_emit<K>, dim3(grid_for(n_max, kEmitRecs)), dim3(kThreads), 0, s, n_dev, n_max, toff, total,
+  hipLaunchKernelGGL(k_emit<K>, dim3(grid_for(n_max, kEmitRecs)), dim3(kThreads), 0, s, n_dev, n_max, toff, boff, total,
                      cap, rec_sorted, ids, (uint32_t)n_prims, views, exact, ikey, ival, ranges_init, tiles);
 }
 
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* total, uint32_t cap,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total, uint32_t cap,
                  const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
                  uint32_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
-  emit_keys(n_dev, n_max, toff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
+  emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
             s);
 }
 
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* total, uint32_t cap,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total, uint32_t cap,
                  const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
                  uint16_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
-  emit_keys(n_dev, n_max, toff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
+  emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
             s);
 }
 

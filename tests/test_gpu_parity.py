@@ -1465,3 +1465,29 @@ def test_backward_one_wave_per_tile(planes):
         a, b = torch.where(fine, a, 0.0), torch.where(fine, b, 0.0)
         assert float((a - b).norm()) <= 3e-5 * float(b.norm())
     assert planes != "loss" or abs(loss_one - float(loss)) <= 1e-5 * float(loss)
+
+
+@pytest.mark.parametrize("n,views", [(1, 3), (63, 17), (257, 33), (65700, 64)])
+def test_pair_listing_and_places(n, views):
+    """Pairs are listed by units of 64 primitives and 16 views at a time, pass a
+    single-precision bound of the temporal filter, and are compacted by
+    256-pair groups (in two levels beyond 16384 of them: 257 a view in the last
+    case). Every view equals its own render bit for bit, so no pair is lost,
+    doubled or out of order; quaternions scaled by powers of two, whose squares
+    leave single precision, change no bit either."""
+    # short-lived primitives: most pairs are filtered
+    sc = _big_splat_scene(67, n, grow=0.0 if n > 1000 else 0.4, sh=1, to=1, mu_log_t=-3.5)
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.ring_camera(0.07 * v, 45, 37) for v in range(views)]
+    times = [(v * 7 % 31) / 31.0 for v in range(views)]
+    rgb, dep, alp = r.render(cams, times)
+    act = r.stats()["active_per_view"]
+    hw = 45 * 37
+    for v in range(views) if n < 1000 else (0, 1, 15, 16, 31, 62, 63):
+        one = r.render([cams[v]], [times[v]])
+        for got, want, k in zip((rgb, dep, alp), one, (3, 1, 1)):
+            assert torch.equal(got[k * hw * v:k * hw * (v + 1)], want), (v, k)
+        assert r.stats()["active_per_view"] == [act[v]]
+    sc.q_left[::2] *= np.float32(2.0**66)
+    sc.q_right[::3] *= np.float32(2.0**-66)
+    assert torch.equal(PT.gpu_setup(sc)[0].render(cams, times)[0], rgb)
