@@ -155,7 +155,8 @@ constexpr int kNABufs = 31;
 constexpr size_t na_total_bytes() {
   // an upper bound of the carved total (each buffer 256-byte aligned)
   return (sizeof(ViewDev) * kMaxViews + 256) + (84 * kNAGroups + 1024) + 7 * (4 * kNAPairs + 256) +
-         2 * (48 * kNAPairs + 256) + (16 * kNAPairs + 256) + (5 * kNAPairs + 512) + (4 * (kNAPairs / 256 + 4) + 256) + (4 * (256 * kNASortBlocks + 256) + 256) +
+         2 * (48 * kNAPairs + 256) + (16 * kNAPairs + 256) + (5 * kNAPairs + 512) + (4 * (kNAPairs / 256 + 4) + 256) +
+         (4 * (256 * kNASortBlocks + 256) + 256) +
          4 * (4 * kNAInstances + 256) + (8 * kNATiles + 256) + 4 * (4 * kNATiles + 256) + 2 * (4 * kNAPixels + 256) +
          (4 * kCntWords + 256);
 }
@@ -341,7 +342,8 @@ RenderParams make_params(g4d_ctx* c, int n_views) {
 }
 
 PairBits pair_bits(g4d_ctx* c) {
-  return PairBits{(int)c->n, 4 * pair_groups((int)c->n), P<uint32_t>(c->pactive), P<uint64_t>(c->plisted), P<uint32_t>(c->pfirst)};
+  return PairBits{(int)c->n, 4 * pair_groups((int)c->n), P<uint32_t>(c->pactive), P<uint64_t>(c->plisted),
+                  P<uint32_t>(c->pfirst)};
 }
 
 // The main stream waits for a colour pass still running on the side stream.
@@ -513,10 +515,7 @@ g4d_status bin_tiles(g4d_ctx* c, int tiles, uint32_t a_max, uint32_t cap) {
   const uint32_t* ids = P<uint32_t>(c->cval);
   const Record* rs = P<Record>(c->rec_sorted);
   const ViewDev* vd = P<ViewDev>(c->views_d);
-  // a round of more instances than the last-level cache holds (2^26, ~400 MB
-  // of keys and values in flight) sorts faster on three workgroups per CU
-  // (768 on 256 CUs: fewer partial cache lines open at once) than on five
-  const int g_tile = radix_grid(cap, cap > (1u << 26) ? std::min(c->sort_blocks, 768) : c->sort_blocks);
+  const int g_tile = radix_grid(cap, c->sort_blocks);
   uint32_t* rsc = P<uint32_t>(c->radix_scratch);
   uint2* rg = P<uint2>(c->ranges);
   uint2* rg_init = passes ? rg : nullptr;
@@ -524,14 +523,14 @@ g4d_status bin_tiles(g4d_ctx* c, int tiles, uint32_t a_max, uint32_t cap) {
   // 16-bit keys take a quarter off the sort's bytes per instance
   if (tile_bits <= 16) {
     uint16_t *k16 = static_cast<uint16_t*>(ek), *a16 = static_cast<uint16_t*>(ak);
-    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), P<uint32_t>(c->scan_scratch), cnt + kCntI, cap, rs, ids, (int)c->n, vd,
-                c->ellipse_cull, k16, ev, rg_init, (uint32_t)tiles, s);
+    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), P<uint32_t>(c->scan_scratch), cnt + kCntI, cap, rs,
+                ids, (int)c->n, vd, c->ellipse_cull, k16, ev, rg_init, (uint32_t)tiles, s);
     if (passes) radix_sort16(k16, ev, a16, av, cnt + kCntI, cap, 0, tile_bits, g_tile, rsc, s, rg, (uint32_t)tiles);
     else launch_ranges(cnt + kCntI, cap, k16, rg, s);
   } else {
     uint32_t *k32 = static_cast<uint32_t*>(ek), *a32 = static_cast<uint32_t*>(ak);
-    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), P<uint32_t>(c->scan_scratch), cnt + kCntI, cap, rs, ids, (int)c->n, vd,
-                c->ellipse_cull, k32, ev, rg_init, (uint32_t)tiles, s);
+    launch_emit(cnt + kCntA, a_max, P<uint32_t>(c->toff), P<uint32_t>(c->scan_scratch), cnt + kCntI, cap, rs,
+                ids, (int)c->n, vd, c->ellipse_cull, k32, ev, rg_init, (uint32_t)tiles, s);
     radix_sort(k32, ev, a32, av, cnt + kCntI, cap, 0, tile_bits, g_tile, rsc, s, /*copy_back=*/false, rg,
                (uint32_t)tiles);
   }

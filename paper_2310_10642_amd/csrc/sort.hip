@@ -100,7 +100,8 @@ __device__ __forceinline__ void row_span(const Footprint& f, uint32_t ty, bool e
   xb = (uint32_t)fminf(fmaxf(tb, (float)xa), fx1);
 }
 
-// Exclusive scan of one value per thread across a 256-thread block.
+// Exclusive scan of one value per thread across a block of T threads.
+template <int T = kThreads>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s_wave, uint32_t& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t x = v;
@@ -114,7 +115,7 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
   uint32_t base = 0;
   total = 0;
 #pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
+  for (int w = 0; w < T / 64; ++w) {
     const uint32_t c = s_wave[w];
     base += (w < wave) ? c : 0u;
     total += c;
@@ -244,36 +245,36 @@ __device__ __forceinline__ uint32_t sort_block() {
   return (g & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (g >> 3) + (blockIdx.x >> 3);
 }
 
-__device__ __forceinline__ void block_range(uint32_t n, int grid, uint32_t& t0, uint32_t& t1) {
-  const uint32_t tiles = (n + kTileElems - 1) / kTileElems;
+__device__ __forceinline__ void block_range(uint32_t n, uint32_t tile, int grid, uint32_t& t0, uint32_t& t1) {
+  const uint32_t tiles = (n + tile - 1) / tile;
   const uint32_t tpb = (tiles + grid - 1) / grid;
   t0 = min(sort_block() * tpb, tiles);
   t1 = min(t0 + tpb, tiles);
 }
 
 // K: uint32_t, or uint16_t for keys below 2^16 (the tile ids of a round).
-template <typename K>
-__global__ void __launch_bounds__(kThreads) k_rs_upsweep(const K* __restrict__ keys, const uint32_t* n_dev,
-                                                          uint32_t n_max, int shift, int bits,
-                                                          uint32_t* __restrict__ counts) {
-  __shared__ uint32_t hist[4][256];
+// T threads, 16 keys each per tile (the scatter's tile).
+template <typename K, int T>
+__global__ void __launch_bounds__(T) k_rs_upsweep(const K* __restrict__ keys, const uint32_t* n_dev, uint32_t n_max,
+                                                   int shift, int bits, uint32_t* __restrict__ counts) {
+  constexpr int kWaves = T / 64, kElems = T * kItems;
+  __shared__ uint32_t hist[kWaves][256];
   const uint32_t n = dev_n(n_dev, n_max);
   const int wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) hist[w][threadIdx.x] = 0u;
+  for (int i = threadIdx.x; i < kWaves * 256; i += T) hist[i >> 8][i & 255] = 0u;
   __syncthreads();
   uint32_t t0, t1;
-  block_range(n, gridDim.x, t0, t1);
+  block_range(n, kElems, gridDim.x, t0, t1);
   const uint32_t mask = (1u << bits) - 1u;
   for (uint32_t t = t0; t < t1; ++t) {
-    const size_t tb = (size_t)t * kTileElems;
-    if (tb + kTileElems <= n) {
+    const size_t tb = (size_t)t * kElems;
+    if (tb + kElems <= n) {
       // full tile: 16-byte loads (four, or two of 16-bit keys), all in flight together
       constexpr int kVec = 16 / (int)sizeof(K);
       uint4 q[kItems / kVec];
 #pragma unroll
       for (int i = 0; i < kItems / kVec; ++i)
-        q[i] = reinterpret_cast<const uint4*>(keys + tb)[i * kThreads + threadIdx.x];
+        q[i] = reinterpret_cast<const uint4*>(keys + tb)[i * T + threadIdx.x];
 #pragma unroll
       for (int i = 0; i < kItems / kVec; ++i) {
         const uint32_t w[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
@@ -289,14 +290,19 @@ __global__ void __launch_bounds__(kThreads) k_rs_upsweep(const K* __restrict__ k
       }
     } else {
       for (int i = 0; i < kItems; ++i) {
-        const size_t idx = tb + (size_t)i * kThreads + threadIdx.x;
+        const size_t idx = tb + (size_t)i * T + threadIdx.x;
         if (idx < n) atomicAdd(&hist[wave][((uint32_t)keys[idx] >> shift) & mask], 1u);
       }
     }
   }
   __syncthreads();
   const uint32_t d = threadIdx.x;
-  counts[(size_t)d * gridDim.x + sort_block()] = hist[0][d] + hist[1][d] + hist[2][d] + hist[3][d];
+  if (T == 256 || d < 256u) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) c += hist[w][d];
+    counts[(size_t)d * gridDim.x + sort_block()] = c;
+  }
 }
 
 // One 256-thread block per digit: exclusive scan of counts[digit][0..grid) in
@@ -331,31 +337,34 @@ __global__ void __launch_bounds__(kThreads) k_rs_rowscan(uint32_t* __restrict__ 
   if (threadIdx.x == 0) digit_tot[blockIdx.x] = carry;
 }
 
-// LDS of the stable scatter of one digit pass (30.7 KB with 16-bit keys, five
-// workgroups per CU; 39.4 KB with 32-bit keys, four).
-template <typename K>
+// LDS of the stable scatter of one digit pass by T threads, 16 pairs each
+// (T = 256: 30.7 KB with 16-bit keys, five workgroups per CU; 39.4 KB with
+// 32-bit keys, four; T = 512: 59.4 KB with 16-bit keys, two).
+template <typename K, int T>
 struct ScatterShared {
-  K k[kTileElems];                        // the tile reordered by digit
-  uint32_t v[kTileElems];
-  uint32_t wcnt[4][256];                  // per wave and digit: count, then start
-  uint32_t run[256];                      // per digit: next output position of the block
-  uint32_t tstart[256];                   // per digit: start of its run in the reordered tile
-  uint32_t wave[4];
+  static constexpr int kWaves = T / 64;
+  static constexpr int kElems = T * kItems;
+  K k[kElems];                 // the tile reordered by digit
+  uint32_t v[kElems];
+  uint32_t wcnt[kWaves][256];  // per wave and digit: count, then start
+  uint32_t run[256];           // per digit: next output position of the block
+  uint32_t tstart[256];        // per digit: start of its run in the reordered tile
+  uint32_t wave[kWaves];
 };
 
 // Output positions of the block's digit runs: run[d] = (pairs of smaller
 // digits in the whole pass) + (pairs of digit d in earlier blocks), from the
 // per-(digit, block) exclusive scan `counts` and the digit totals.
-template <typename K>
-__device__ __forceinline__ void scatter_begin(ScatterShared<K>& sh, const uint32_t* __restrict__ counts,
+template <typename K, int T>
+__device__ __forceinline__ void scatter_begin(ScatterShared<K, T>& sh, const uint32_t* __restrict__ counts,
                                               const uint32_t* __restrict__ digit_tot, uint32_t grid, uint32_t block) {
   const uint32_t dg = threadIdx.x;
   uint32_t tot;
-  const uint32_t base = block_exclusive_scan(digit_tot[dg], sh.wave, tot);
-  sh.run[dg] = base + counts[(size_t)dg * grid + block];
+  const uint32_t base = block_exclusive_scan<T>(dg < 256u ? digit_tot[dg] : 0u, sh.wave, tot);
+  if (dg < 256u) sh.run[dg] = base + counts[(size_t)dg * grid + block];
 }
 
-// Stable scatter of one tile of up to 4096 (key, value) pairs: wave w holds
+// Stable scatter of one tile of up to 16 T (key, value) pairs: wave w holds
 // pairs [1024 w, 1024 w + 1024) of the tile, 64 at a time, step i in k[i],
 // v[i]; the first nvalid pairs of the tile are valid. A lane's rank among
 // equal digits comes from a ballot match over the digit bits; the tile is
@@ -365,21 +374,22 @@ __device__ __forceinline__ void scatter_begin(ScatterShared<K>& sh, const uint32
 // whole key) the keys are not written: each key's first and last position
 // bound its range instead (a key >= n_ranges, which a consistent sort never
 // produces, is skipped).
-// FULL: the tile holds kTileElems valid pairs (the validity tests compile out).
-template <bool FULL, typename K>
-__device__ __forceinline__ void scatter_tile(ScatterShared<K>& sh, uint32_t (&k)[kItems],
+// FULL: the tile holds 16 T valid pairs (the validity tests compile out).
+template <bool FULL, typename K, int T>
+__device__ __forceinline__ void scatter_tile(ScatterShared<K, T>& sh, uint32_t (&k)[kItems],
                                              const uint32_t (&v)[kItems], uint32_t nvalid, int shift, int bits,
                                              uint32_t n_out, K* __restrict__ keys_out,
                                              uint32_t* __restrict__ vals_out, uint2* __restrict__ ranges,
                                              uint32_t n_ranges) {
+  constexpr int kWaves = T / 64, kElems = T * kItems;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t mask = (1u << bits) - 1u;
   const uint32_t dg = threadIdx.x;
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < 4; ++w) sh.wcnt[w][threadIdx.x] = 0u;
+  for (int w = 0; w < 256 / 64; ++w) sh.wcnt[wave][w * 64 + lane] = 0u;
   __syncthreads();
-  const uint32_t base = (uint32_t)wave * (kTileElems / 4);
+  const uint32_t base = (uint32_t)wave * (kItems * 64);
   constexpr bool kPacked = sizeof(K) == 2;
   uint32_t rank[kItems];
 #pragma unroll
@@ -422,15 +432,25 @@ __device__ __forceinline__ void scatter_tile(ScatterShared<K>& sh, uint32_t (&k)
   }
   __syncthreads();
   // per digit: tile-local start, then each wave's start inside it
-  const uint32_t c0 = sh.wcnt[0][dg], c1 = sh.wcnt[1][dg], c2 = sh.wcnt[2][dg], c3 = sh.wcnt[3][dg];
-  const uint32_t ctot = c0 + c1 + c2 + c3;
+  uint32_t c[kWaves], ctot = 0;
+  if (T == 256 || dg < 256u) {
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      c[w] = sh.wcnt[w][dg];
+      ctot += c[w];
+    }
+  }
   uint32_t all;
-  const uint32_t ts = block_exclusive_scan(ctot, sh.wave, all);  // contains barriers
-  sh.wcnt[0][dg] = ts;
-  sh.wcnt[1][dg] = ts + c0;
-  sh.wcnt[2][dg] = ts + c0 + c1;
-  sh.wcnt[3][dg] = ts + c0 + c1 + c2;
-  sh.tstart[dg] = ts;
+  const uint32_t ts = block_exclusive_scan<T>(ctot, sh.wave, all);  // contains barriers
+  if (T == 256 || dg < 256u) {
+    uint32_t at = ts;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      sh.wcnt[w][dg] = at;
+      at += c[w];
+    }
+    sh.tstart[dg] = ts;
+  }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
@@ -439,17 +459,17 @@ __device__ __forceinline__ void scatter_tile(ScatterShared<K>& sh, uint32_t (&k)
       const uint32_t key = kPacked ? (k[i] & 0xFFFFu) : k[i];
       const uint32_t d = (key >> shift) & mask;
       const uint32_t lp = sh.wcnt[wave][d] + (kPacked ? k[i] >> 16 : rank[i]);
-      if (lp < (uint32_t)kTileElems) {
+      if (lp < (uint32_t)kElems) {
         sh.k[lp] = (K)key;
         sh.v[lp] = v[i];
       }
     }
   }
   __syncthreads();
-  const uint32_t nt = FULL ? (uint32_t)kTileElems : min(nvalid, (uint32_t)kTileElems);
+  const uint32_t nt = FULL ? (uint32_t)kElems : min(nvalid, (uint32_t)kElems);
 #pragma unroll 4
   for (int i = 0; i < kItems; ++i) {
-    const uint32_t lp = (uint32_t)i * kThreads + threadIdx.x;
+    const uint32_t lp = (uint32_t)i * T + threadIdx.x;
     if (lp < nt) {
       const uint32_t key = sh.k[lp];
       const uint32_t d = (key >> shift) & mask;
@@ -470,48 +490,49 @@ __device__ __forceinline__ void scatter_tile(ScatterShared<K>& sh, uint32_t (&k)
     }
   }
   __syncthreads();
-  sh.run[dg] += ctot;
+  if (T == 256 || dg < 256u) sh.run[dg] += ctot;
 }
 
 // One digit pass over the pairs in memory: each block takes its range of
-// 4096-pair tiles in turn.
-template <typename K>
-__global__ void __launch_bounds__(kThreads) k_rs_downsweep(const K* __restrict__ keys_in,
-                                                            const uint32_t* __restrict__ vals_in,
-                                                            K* __restrict__ keys_out,
-                                                            uint32_t* __restrict__ vals_out, const uint32_t* n_dev,
-                                                            uint32_t n_max, int shift, int bits,
-                                                            const uint32_t* __restrict__ counts,
-                                                            const uint32_t* __restrict__ digit_tot,
-                                                            uint2* __restrict__ ranges, uint32_t n_ranges) {
-  __shared__ ScatterShared<K> sh;
+// scatter tiles in turn.
+template <typename K, int T>
+__global__ void __launch_bounds__(T) k_rs_downsweep(const K* __restrict__ keys_in,
+                                                     const uint32_t* __restrict__ vals_in, K* __restrict__ keys_out,
+                                                     uint32_t* __restrict__ vals_out, const uint32_t* n_dev,
+                                                     uint32_t n_max, int shift, int bits,
+                                                     const uint32_t* __restrict__ counts,
+                                                     const uint32_t* __restrict__ digit_tot,
+                                                     uint2* __restrict__ ranges, uint32_t n_ranges) {
+  __shared__ ScatterShared<K, T> sh;
+  constexpr uint32_t kElems = ScatterShared<K, T>::kElems;
   const uint32_t n = dev_n(n_dev, n_max);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   scatter_begin(sh, counts, digit_tot, gridDim.x, sort_block());
   uint32_t t0, t1;
-  block_range(n, gridDim.x, t0, t1);
-  for (uint32_t t = t0; t < t1; ++t) {
-    const size_t base = (size_t)t * kTileElems + (size_t)wave * (kTileElems / 4);
+  block_range(n, kElems, gridDim.x, t0, t1);
+  const uint32_t t_full = min(t1, n / kElems);
+  for (uint32_t t = t0; t < t_full; ++t) {
+    // a full tile (all but the last): no per-key bounds test
     uint32_t k[kItems], v[kItems];
-    const uint32_t nvalid = (uint32_t)min((size_t)kTileElems, (size_t)n - (size_t)t * kTileElems);
-    if (nvalid == (uint32_t)kTileElems) {
-      // a full tile (all but the last): no per-key bounds test
+    const size_t base = (size_t)t * kElems + (size_t)wave * (kItems * 64);
 #pragma unroll
-      for (int i = 0; i < kItems; ++i) {
-        const size_t idx = base + (size_t)i * 64 + lane;
-        k[i] = (uint32_t)keys_in[idx];
-        v[i] = vals_in[idx];
-      }
-      scatter_tile<true>(sh, k, v, nvalid, shift, bits, n, keys_out, vals_out, ranges, n_ranges);
-    } else {
-#pragma unroll
-      for (int i = 0; i < kItems; ++i) {
-        const size_t idx = base + (size_t)i * 64 + lane;
-        k[i] = (idx < n) ? (uint32_t)keys_in[idx] : 0u;
-        v[i] = (idx < n) ? vals_in[idx] : 0u;
-      }
-      scatter_tile<false>(sh, k, v, nvalid, shift, bits, n, keys_out, vals_out, ranges, n_ranges);
+    for (int i = 0; i < kItems; ++i) {
+      const size_t idx = base + (size_t)i * 64 + lane;
+      k[i] = (uint32_t)keys_in[idx];
+      v[i] = vals_in[idx];
     }
+    scatter_tile<true>(sh, k, v, kElems, shift, bits, n, keys_out, vals_out, ranges, n_ranges);
+  }
+  if (t0 < t1 && t_full < t1) {  // the block of the partial last tile
+    uint32_t k[kItems], v[kItems];
+    const size_t base = (size_t)t_full * kElems + (size_t)wave * (kItems * 64);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const size_t idx = base + (size_t)i * 64 + lane;
+      k[i] = (idx < n) ? (uint32_t)keys_in[idx] : 0u;
+      v[i] = (idx < n) ? vals_in[idx] : 0u;
+    }
+    scatter_tile<false>(sh, k, v, n - t_full * kElems, shift, bits, n, keys_out, vals_out, ranges, n_ranges);
   }
 }
 
@@ -877,7 +898,7 @@ int radix_passes(int bit0, int bit1) { return bit1 > bit0 ? (bit1 - bit0 + 7) / 
 
 // The digit passes, ping-ponging between the two buffer pairs; returns the
 // pair that holds the result.
-template <typename K>
+template <typename K, int T = kThreads>
 std::pair<K*, uint32_t*> radix_passes_run(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt,
                                           const uint32_t* n_dev, uint32_t n_max, int bit0, int bit1, int grid,
                                           uint32_t* scratch, hipStream_t s, uint2* last_ranges,
@@ -886,9 +907,9 @@ std::pair<K*, uint32_t*> radix_passes_run(K* keys, uint32_t* vals, K* keys_alt, 
   uint32_t *vin = vals, *vout = vals_alt;
   for (int b = bit0; b < bit1; b += 8) {
     const int bits = (bit1 - b) < 8 ? (bit1 - b) : 8;
-    hipLaunchKernelGGL(k_rs_upsweep<K>, dim3(grid), dim3(kThreads), 0, s, kin, n_dev, n_max, b, bits, scratch);
+    hipLaunchKernelGGL((k_rs_upsweep<K, T>), dim3(grid), dim3(T), 0, s, kin, n_dev, n_max, b, bits, scratch);
     hipLaunchKernelGGL(k_rs_rowscan, dim3(256), dim3(kThreads), 0, s, scratch, grid, scratch + (size_t)256 * grid);
-    hipLaunchKernelGGL(k_rs_downsweep<K>, dim3(grid), dim3(kThreads), 0, s, kin, vin, kout, vout, n_dev, n_max, b,
+    hipLaunchKernelGGL((k_rs_downsweep<K, T>), dim3(grid), dim3(T), 0, s, kin, vin, kout, vout, n_dev, n_max, b,
                        bits, scratch, scratch + (size_t)256 * grid, b + 8 >= bit1 ? last_ranges : nullptr,
                        b + 8 >= bit1 && last_ranges ? n_ranges : 0u);
     std::swap(kin, kout);
@@ -910,8 +931,17 @@ void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* va
 void radix_sort16(uint16_t* keys, uint32_t* vals, uint16_t* keys_alt, uint32_t* vals_alt, const uint32_t* n_dev,
                   uint32_t n_max, int bit0, int bit1, int grid, uint32_t* scratch, hipStream_t s,
                   uint2* last_ranges, uint32_t n_ranges) {
-  radix_passes_run(keys, vals, keys_alt, vals_alt, n_dev, n_max, bit0, bit1, grid, scratch, s, last_ranges,
-                   n_ranges);
+  // from 2^24 instances on, two 512-thread workgroups per CU with tiles of 8192:
+  // digit runs of 32 instances write half as many partial cache lines, and
+  // fewer lines are open at once, than with five 256-thread ones (per pass:
+  // 109 -> 101 us for 26M instances, 186 -> 174 for 44M, 368 -> 325 for 80M,
+  // 1139 -> 980 for 236M; equal at 14M, and at 3.4M 18.4 -> 21.4)
+  if (n_max >= 1u << 24)
+    radix_passes_run<uint16_t, 512>(keys, vals, keys_alt, vals_alt, n_dev, n_max, bit0, bit1, std::min(grid, 512),
+                                    scratch, s, last_ranges, n_ranges);
+  else
+    radix_passes_run(keys, vals, keys_alt, vals_alt, n_dev, n_max, bit0, bit1, grid, scratch, s, last_ranges,
+                     n_ranges);
 }
 
 void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
@@ -929,8 +959,8 @@ void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, c
 }
 
 template <typename K>
-void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total, uint32_t cap,
-               const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact, K* ikey,
+void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
+               const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact, K* ikey,
                uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
   if (n_max == 0) {
     if (ranges_init) launch_ranges_init(ranges_init, tiles, s);
@@ -940,15 +970,15 @@ void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, cons
                      cap, rec_sorted, ids, (uint32_t)n_prims, views, exact, ikey, ival, ranges_init, tiles);
 }
 
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total, uint32_t cap,
-                 const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
+                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
                  uint32_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
   emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
             s);
 }
 
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total, uint32_t cap,
-                 const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
+                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
                  uint16_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
   emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
             s);

@@ -1491,3 +1491,22 @@ def test_pair_listing_and_places(n, views):
     sc.q_left[::2] *= np.float32(2.0**66)
     sc.q_right[::3] *= np.float32(2.0**-66)
     assert torch.equal(PT.gpu_setup(sc)[0].render(cams, times)[0], rgb)
+
+
+@pytest.mark.parametrize("n", [3300, 3601])
+def test_large_tile_sort(n):
+    """From 2^24 instances on the tile sort takes wider workgroups: six views of
+    some 3M instances each (primitives that cover the whole image) equal the
+    same views in rounds below the line, bit for bit."""
+    from paper_2310_10642_amd import g4d
+    r, _ = PT.gpu_setup(_big_splat_scene(71, n, grow=3.0, sh=1, to=1, mu_log_t=1.0))
+    cams = [scenegen.ring_camera(0.3 * v, 512, 512) for v in range(6)]
+    times = [0.1 * v for v in range(6)]
+    one = r.render(cams, times)
+    st = r.stats()
+    assert st["rounds"] == 1 and st["instances"] >= 1 << 24
+    r.set_tuning(g4d.G4D_TUNE_ROUND_INSTANCES, 1 << 23)
+    many = r.render(cams, times)
+    assert r.stats()["rounds"] in (3, 6)
+    for a, b in zip(one, many):
+        assert torch.equal(a, b)
