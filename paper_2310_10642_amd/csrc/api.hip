@@ -413,7 +413,14 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
   if ((st = ensure(c, c->pany, (size_t)c->n))) return st;
   if ((st = ensure(c, c->plist, 4 * (size_t)c->n))) return st;
   if ((st = ensure(c, c->scan_scratch, 4 * scan_scratch_words(vn)))) return st;
-  if ((st = ensure(c, c->radix_scratch, 4 * radix_scratch_words(c->sort_blocks)))) return st;
+  // the depth sort is sized from the active records seen so far
+  const uint64_t est = c->active_hint ? std::min<uint64_t>(vn, (uint64_t)c->active_hint * nv * 5 / 4 + 4096) : vn;
+  // up to 192 tiles of 4096 the one-launch passes (a workgroup waits for the
+  // counts of all earlier tiles: see k_rs_chain for both sides), for up to
+  // 8192 pairs the one-workgroup sort
+  const bool chained = vn > 8192 && est <= (3u << 18) && vn <= (size_t(1) << 24);
+  const size_t chain_words = chained ? chain_scratch_words(vn) : 0;
+  if ((st = ensure(c, c->radix_scratch, 4 * std::max(radix_scratch_words(c->sort_blocks), chain_words)))) return st;
   RenderParams p = make_params(c, nv);
   uint32_t* cnt = P<uint32_t>(c->counters);
   if (count) p.nonfinite = cnt + kCntNF + v0;
@@ -424,7 +431,7 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
   //    gather, on the second stream)
   stage_begin(c);
   launch_preprocess(p, pair_bits(c), P<uint32_t>(c->gcount), P<uint32_t>(c->dkey),
-                    P<Record>(c->rec), P<float4>(c->cdir), s);
+                    P<Record>(c->rec), P<float4>(c->cdir), P<uint32_t>(c->radix_scratch), (uint32_t)chain_words, s);
   stage_end(c, G4D_STAGE_PREPROCESS);
   // the records' colours on the second stream, beside the scans and the
   // depth sort (joined before the gather copies the records)
@@ -434,15 +441,15 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
   // per-view counts: at the round's place for a sync-free render, which
   // reads them only after its last round
   launch_compact(pair_bits(c), P<uint32_t>(c->gcount), nv, P<uint32_t>(c->dkey), P<uint32_t>(c->ckey),
-                 P<uint32_t>(c->cval), cnt + kCntA,
+                 P<uint32_t>(c->cval), chained ? P<uint32_t>(c->radix_scratch) : nullptr, cnt + kCntA,
                  cnt + kCntViews + (c->totals_on_device ? v0 : 0), P<uint32_t>(c->scan_scratch), s);
-  // 3. stable sort by depth; its grid is sized from the active records seen
-  // so far (any grid gives the same order: blocks take ranges of the count
-  // the device holds)
-  const uint64_t est = c->active_hint ? std::min<uint64_t>(vn, (uint64_t)c->active_hint * nv * 5 / 4 + 4096) : vn;
-  const int g_depth = radix_grid((uint32_t)est, c->sort_blocks);
-  radix_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2), cnt + kCntA,
-             (uint32_t)vn, 0, 32, g_depth, P<uint32_t>(c->radix_scratch), s);
+  // 3. stable sort by depth (any grid gives the same order)
+  if (chained)
+    chain_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2), cnt + kCntA,
+               (uint32_t)vn, (uint32_t)est, P<uint32_t>(c->radix_scratch), s);
+  else
+    radix_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2), cnt + kCntA,
+               (uint32_t)vn, 0, 32, radix_grid((uint32_t)est, c->sort_blocks), P<uint32_t>(c->radix_scratch), s);
   // 4. depth-ordered records, slot map, tiles per record; 5. instance offsets
   if ((st = join_side(c))) return st;
   launch_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->cval), pair_bits(c), P<Record>(c->rec),

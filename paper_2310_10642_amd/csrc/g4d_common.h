@@ -116,8 +116,9 @@ __device__ __forceinline__ uint32_t pair_place(const PairBits& pb, uint32_t view
 // ---- launchers (preprocess.hip) ----
 // group_count: the active pairs of each view's groups; cdir: view direction,
 // t - mu_t. dkey, rec and cdir are written for the active pairs.
+// zero[0..n_zero) is set to zero (nothing if null).
 void launch_preprocess(const RenderParams& p, const PairBits& pb, uint32_t* group_count, uint32_t* dkey,
-                       Record* rec, float4* cdir, hipStream_t s);
+                       Record* rec, float4* cdir, uint32_t* zero, uint32_t n_zero, hipStream_t s);
 // Lists the primitives active in some view (p.plist), then the 4DSH colour of
 // every active pair into its record, before the gather orders the records by
 // depth; nothing in flow mode.
@@ -141,9 +142,18 @@ void launch_image_loss(int kind, uint64_t n, const float* img, const float* tgt,
 size_t scan_scratch_words(size_t n_max);
 // The active pairs in (view, primitive) order: ckey[i] = dkey[place], cval[i] =
 // view * n + primitive; their number in *total, and after each view's last in view_end[view].
-// scratch: scan scratch words.
+// scratch: scan scratch words. hist: null, or 4 * 256 zeroed words that get the
+// keys' digit counts.
 void launch_compact(const PairBits& pb, const uint32_t* count, int n_views, const uint32_t* dkey, uint32_t* ckey,
-                    uint32_t* cval, uint32_t* total, uint32_t* view_end, uint32_t* scratch, hipStream_t s);
+                    uint32_t* cval, uint32_t* hist, uint32_t* total, uint32_t* view_end, uint32_t* scratch,
+                    hipStream_t s);
+// Stable sort of the n (from n_dev) pairs by 32-bit keys in four single-launch
+// passes; the result is in (keys, vals). The scratch words start zeroed but
+// for the keys' digit counts in the first 4 * 256 (the compaction's hist).
+// n_est sizes the grid (any gives the same result).
+size_t chain_scratch_words(size_t n_max);
+void chain_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, const uint32_t* n_dev,
+                uint32_t n_max, uint32_t n_est, uint32_t* scratch, hipStream_t s);
 // LSD radix sort of (key, value) pairs on bits [bit0, bit1) in 8-bit passes
 // that ping-pong via alt; the result ends in keys/vals, copied back after an
 // odd number of passes unless copy_back is false (then it is in the alt pair).
@@ -176,11 +186,13 @@ void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, c
 // Keys are 16-bit when the round's tile ids are below 2^16, else 32-bit. With
 // ranges_init, the launch also sets ranges_init[0..tiles) to (~0u, 0), the
 // start state of the ranges the sort's last pass fills.
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total,
-                 uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
+                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims,
+                 const ViewDev* views, bool exact,
                  uint32_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s);
-void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff, const uint32_t* total,
-                 uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
+                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims,
+                 const ViewDev* views, bool exact,
                  uint16_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s);
 void launch_ranges(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ikey, uint2* ranges, hipStream_t s);
 void launch_ranges(const uint32_t* n_dev, uint32_t n_max, const uint16_t* ikey, uint2* ranges, hipStream_t s);

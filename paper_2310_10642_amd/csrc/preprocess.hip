@@ -80,7 +80,8 @@ struct PreWave {
 __global__ void __launch_bounds__(256, 3) k_preprocess(RenderParams p, float cull2, PairBits pb,
                                                        uint32_t* __restrict__ group_count,
                                                        uint32_t* __restrict__ dkey,
-                                                       Record* __restrict__ rec, float4* __restrict__ cdir) {
+                                                       Record* __restrict__ rec, float4* __restrict__ cdir,
+                                                       uint32_t* __restrict__ zero, uint32_t n_zero) {
   __shared__ PreWave s_waves[4];
   __shared__ ViewDev s_view[kPreViews];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -89,7 +90,9 @@ __global__ void __launch_bounds__(256, 3) k_preprocess(RenderParams p, float cul
   const int gidx = (int)(unit * 64) + lane;
   const double t_cull = p.t_cull, near = p.near_plane;
   const uint64_t lower = (1ull << lane) - 1ull;
-  if (blockIdx.x == 0 && tid == 0) *p.plist_n = 0u;  // for the listing of the active primitives
+  // for the launches that follow: the active primitives' number, the sort's words
+  if (blockIdx.x == 0 && tid == 0) *p.plist_n = 0u;
+  for (uint32_t i = blockIdx.x * 256 + tid; i < n_zero; i += gridDim.x * 256) zero[i] = 0u;
   float s44 = 0.f, mu_t = 0.f;
   bool usable = false, any = false;
   float4 ls = make_float4(0.f, 0.f, 0.f, 0.f), qlf = ls, qrf = ls;
@@ -402,13 +405,13 @@ __global__ void __launch_bounds__(256) k_colour(RenderParams p, PairBits pb,
 }  // namespace
 
 void launch_preprocess(const RenderParams& p, const PairBits& pb, uint32_t* group_count, uint32_t* dkey,
-                       Record* rec, float4* cdir, hipStream_t s) {
+                       Record* rec, float4* cdir, uint32_t* zero, uint32_t n_zero, hipStream_t s) {
   if (p.n == 0) return;
   // -2 log t_cull, enlarged past every rounding of the FP32 test (infinite, so
   // that every pair is listed, for t_cull = 0)
   const float cull2 = (float)(-2.0 * std::log((double)p.t_cull) * 1.001 + 1e-5);
   hipLaunchKernelGGL(k_preprocess, dim3(pair_groups(p.n)), dim3(256), 0, s, p, cull2, pb, group_count, dkey, rec,
-                     cdir);
+                     cdir, zero, n_zero);
 }
 
 // Workgroups of the kernels that walk the active-primitive list (64 listed

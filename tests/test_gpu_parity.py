@@ -1510,3 +1510,32 @@ def test_large_tile_sort(n):
     assert r.stats()["rounds"] in (3, 6)
     for a, b in zip(one, many):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,views", [(1, 1), (1024, 1), (1025, 1), (4097, 1), (8192, 1), (8193, 1), (2731, 3), (9000, 5),
+                                     (40960, 8), (130000, 8)])
+def test_small_sorts(n, views):
+    """The sorts of few pairs: one workgroup of 1, 4 or 8 pairs a thread up to 8192,
+    chained one-launch passes beyond, the three-launch passes past 3 * 2^18. Pairs
+    at the depth of others (copies of primitives) keep their order: the records
+    are in order of (depth, view, primitive), every tile's list in order of the
+    records, on the first render and on the next (whose grid is another)."""
+    sc = _big_splat_scene(73, n, grow=0.3 if n < 10000 else -1.5, sh=1, to=1, mu_log_t=1.0)
+    sc.means4[n // 2:2 * (n // 2)] = sc.means4[:n // 2]
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.ring_camera(0.4 * v, 125, 77) for v in range(views)]
+    for _ in range(2):
+        r.render(cams, [0.5] * views)
+        z, ids = r.debug("records")[:, 2], r.debug("ids").astype(np.int64)
+        assert len(ids) == r.stats()["active_total"] and len(np.unique(ids)) == len(ids)
+        if len(ids) > 1:
+            dz, di = np.diff(z), np.diff(ids)
+            assert (dz >= 0).all() and (di[dz == 0] > 0).all()
+        vals, ranges = r.debug("tile_vals").astype(np.int64), r.debug("ranges").astype(np.int64)
+        assert (ranges[:, 1] - ranges[:, 0]).sum() == len(vals) == r.stats()["instances"]
+        step = np.diff(vals) > 0
+        step[ranges[ranges[:, 0] < ranges[:, 1], 1][:-1] - 1] = True  # from one list to the next
+        assert step.all()
+        order = r.debug("tile_order").astype(np.int64)
+        assert (np.sort(order) == np.arange(len(ranges))).all()
+
