@@ -1539,3 +1539,35 @@ def test_small_sorts(n, views):
         order = r.debug("tile_order").astype(np.int64)
         assert (np.sort(order) == np.arange(len(ranges))).all()
 
+
+def test_counts_beyond_the_guess():
+    """A render enqueues its binning and rasteriser for a guess at the counts from
+    earlier renders. After renders of a far camera a near one exceeds the guess
+    by far, then the other way round, and a round cap set in between cuts the
+    call into rounds: images, statistics and tile lists are those of a new
+    context, gradients up to the order of the atomic sums."""
+    from paper_2310_10642_amd import g4d
+    sc = _big_splat_scene(79, 6000, grow=0.2, sh=1, to=1, mu_log_t=0.5)
+    far = [scenegen.look_at_camera((0.0, 0.3 * v, 40.0), 160, 120) for v in range(3)]
+    near = [scenegen.look_at_camera((0.1 * v, 0.0, 2.6), 160, 120) for v in range(3)]
+    r, _ = PT.gpu_setup(sc)
+    times = [0.3, 0.5, 0.7]
+    dl = torch.from_numpy(np.random.default_rng(80).uniform(-1, 1, 3 * 3 * 160 * 120).astype(np.float32)).cuda()
+    for step, cams in enumerate((far, far, near, far, near[:1], near, near, far)):
+        t = times[:len(cams)]
+        if step == 5:
+            r.set_tuning(g4d.G4D_TUNE_ROUND_INSTANCES, 2 * near_total // 3)
+        f, _ = PT.gpu_setup(sc)
+        got, want = r.render(cams, t), f.render(cams, t)
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), step
+        sg, sw = r.stats(), f.stats()
+        if step == 2:
+            near_total = sg["instances"]
+        assert sg["rounds"] >= (2 if step in (5, 6) else 1)
+        assert {**sg, "rounds": 0} == {**sw, "rounds": 0}, step
+        if sg["rounds"] == 1:
+            assert np.array_equal(r.debug("tile_vals"), f.debug("tile_vals"))
+        d = dl[:got[0].numel()]
+        _close_grads(r.backward(d), f.backward(d))
+
