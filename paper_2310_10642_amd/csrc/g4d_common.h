@@ -253,7 +253,13 @@ void launch_split_sample(const RenderParams& p, uint64_t count, const int32_t* i
 
 // ---- launchers (util.hip) ----
 // Views reach the device through kernel arguments, never a host copy.
-void launch_set_views(const ViewDev* host, int n, ViewDev* dev, hipStream_t s);
+// The views to the device; the spans of words are set to zero by the same launch.
+constexpr int kZeroSpans = 3;
+struct ZeroWords {
+  uint32_t* p[kZeroSpans];
+  uint32_t n[kZeroSpans];
+};
+void launch_set_views(const ViewDev* host, int n, ViewDev* dev, ZeroWords zero, hipStream_t s);
 void launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t s);
 // Zeroes floats_per_item (a multiple of 4) floats per item for min(*n_dev, max_items) items.
 void launch_zero_counted(float* p, const uint32_t* n_dev, uint32_t floats_per_item, uint64_t max_items,

@@ -90,8 +90,7 @@ __global__ void __launch_bounds__(256, 3) k_preprocess(RenderParams p, float cul
   const int gidx = (int)(unit * 64) + lane;
   const double t_cull = p.t_cull, near = p.near_plane;
   const uint64_t lower = (1ull << lane) - 1ull;
-  // for the launches that follow: the active primitives' number, the sort's words
-  if (blockIdx.x == 0 && tid == 0) *p.plist_n = 0u;
+  // the words of the sort that follows
   for (uint32_t i = blockIdx.x * 256 + tid; i < n_zero; i += gridDim.x * 256) zero[i] = 0u;
   float s44 = 0.f, mu_t = 0.f;
   bool usable = false, any = false;

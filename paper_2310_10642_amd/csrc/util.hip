@@ -13,9 +13,12 @@ struct ViewChunk {
   ViewDev v[kViewChunk];
 };
 
-__global__ void k_set_views(ViewChunk chunk, int count, ViewDev* __restrict__ out) {
+__global__ void k_set_views(ViewChunk chunk, int count, ViewDev* __restrict__ out, ZeroWords zero) {
   const int i = threadIdx.x;
   if (i < count) out[i] = chunk.v[i];
+#pragma unroll
+  for (int k = 0; k < kZeroSpans; ++k)
+    for (uint32_t j = i; j < zero.n[k]; j += 64) zero.p[k][j] = 0u;
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, uint64_t n, uint32_t value) {
@@ -69,12 +72,13 @@ unsigned stride_grid(uint64_t n, unsigned cap) {
 
 }  // namespace
 
-void launch_set_views(const ViewDev* host, int n, ViewDev* dev, hipStream_t s) {
+void launch_set_views(const ViewDev* host, int n, ViewDev* dev, ZeroWords zero, hipStream_t s) {
   for (int v0 = 0; v0 < n; v0 += kViewChunk) {
     ViewChunk c{};
     const int cnt = (n - v0) < kViewChunk ? (n - v0) : kViewChunk;
     for (int i = 0; i < cnt; ++i) c.v[i] = host[v0 + i];
-    hipLaunchKernelGGL(k_set_views, dim3(1), dim3(64), 0, s, c, cnt, dev + v0);
+    hipLaunchKernelGGL(k_set_views, dim3(1), dim3(64), 0, s, c, cnt, dev + v0, zero);
+    zero = ZeroWords{};
   }
 }
 
