@@ -393,7 +393,7 @@ int round_tiles(const g4d_ctx* c, int v0, int v1) {
 // records in that order and scan their tile counts. Counts stay on the device.
 // count: the pairs culled for a non-finite parameter are counted per view
 // (a render; not the binning again of a backward).
-g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
+g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = false) {
   g4d_status st = join_side(c);  // the last colour pass writes buffers reused below
   if (st) return st;
   c->bound = -1;
@@ -468,24 +468,22 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count) {
                (uint32_t)vn, 0, 32, radix_grid((uint32_t)est, c->sort_blocks), P<uint32_t>(c->radix_scratch), s);
   // 4. depth-ordered records, slot map, tiles per record; 5. instance offsets
   if ((st = join_side(c))) return st;
+  static_assert(kCntA == 0 && kCntI == 1 && kCntInst64 == 2, "HostCounts::counts");
+  const HostCounts host{to_host ? c->counters_h : nullptr, c->counters_h + kCntViews, cnt + kCntViews, nv};
   launch_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->cval), pair_bits(c), P<Record>(c->rec),
                 P<Record>(c->rec_sorted), P<int32_t>(c->slot), P<uint32_t>(c->toff), c->ellipse_cull,
-                P<uint32_t>(c->scan_scratch), cnt + kCntI, cnt + kCntInst64, s);
+                P<uint32_t>(c->scan_scratch), cnt + kCntI, cnt + kCntInst64, host, s);
   stage_end(c, G4D_STAGE_BINNING);
   HIPCHK(c, hipGetLastError());
+  if (to_host) {
+    if (!vn) HIPCHK(c, hipMemcpyAsync(c->counters_h, cnt, sizeof(uint32_t) * (kCntViews + nv), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipEventRecord(c->ev_counts, s));
+  }
   return G4D_OK;
 }
 
-// Copies a round's active count, instance total and per-view counts to the host.
-g4d_status post_counts(g4d_ctx* c, int v0, int nv) {
-  uint32_t* cnt = P<uint32_t>(c->counters);
-  const int vb = kCntViews + (c->totals_on_device ? v0 : 0);  // where enqueue_pairs put the view counts
-  HIPCHK(c, hipMemcpyAsync(c->counters_h, cnt, sizeof(uint32_t) * (vb + nv), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipEventRecord(c->ev_counts, c->stream));
-  return G4D_OK;
-}
-
-// Waits for that copy and takes the counts.
+// Waits for a round's active count, instance total and per-view counts on their
+// way to the host (enqueue_pairs, read_pairs) and takes them.
 g4d_status take_counts(g4d_ctx* c, int v0, int nv, uint32_t& A, uint64_t& inst64) {
   const int vb = kCntViews + (c->totals_on_device ? v0 : 0);
   HIPCHK(c, hipEventSynchronize(c->ev_counts));
@@ -499,9 +497,14 @@ g4d_status take_counts(g4d_ctx* c, int v0, int nv, uint32_t& A, uint64_t& inst64
   return G4D_OK;
 }
 
+// Reads a round's active count, instance total and per-view counts
+// (synchronises the stream).
 g4d_status read_pairs(g4d_ctx* c, int v0, int nv, uint32_t& A, uint64_t& inst64) {
-  const g4d_status st = post_counts(c, v0, nv);
-  return st ? st : take_counts(c, v0, nv, A, inst64);
+  const int vb = kCntViews + (c->totals_on_device ? v0 : 0);  // where enqueue_pairs put the view counts
+  HIPCHK(c, hipMemcpyAsync(c->counters_h, P<uint32_t>(c->counters), sizeof(uint32_t) * (vb + nv),
+                           hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipEventRecord(c->ev_counts, c->stream));
+  return take_counts(c, v0, nv, A, inst64);
 }
 
 // Views [v0, v0 + k) cut to at most kRoundTiles tiles (at least one view).
@@ -1015,8 +1018,7 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
       const uint64_t i_cap = std::min(std::min<uint64_t>(arena_instances(c), inst_cap),
                                       (uint64_t)(c->inst_hint * 1.25 * tiles_k) + 4096);
       ahead = c->active_hint > 0 && c->inst_hint > 0.0 && i_cap > 0 && !capturing(c);
-      if ((st = enqueue_pairs(c, v0, v0 + k, true))) return st;
-      if ((st = post_counts(c, v0, k))) return st;
+      if ((st = enqueue_pairs(c, v0, v0 + k, true, /*to_host=*/true))) return st;
       if (ahead) {
         if ((st = bin_tiles(c, tiles_k, a_cap, (uint32_t)i_cap))) return st;
         const g4d_ctx::Round guess{v0, v0 + k, tiles_k, a_cap, (uint32_t)i_cap};

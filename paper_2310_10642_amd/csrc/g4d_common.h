@@ -174,6 +174,15 @@ void radix_sort16(uint16_t* keys, uint32_t* vals, uint16_t* keys_alt, uint32_t* 
                   uint2* last_ranges = nullptr, uint32_t n_ranges = 0);
 void launch_ranges_init(uint2* ranges, uint32_t tiles, hipStream_t s);
 void launch_ranges_fix(uint2* ranges, uint32_t tiles, hipStream_t s);
+// Pinned host words that get the counts by the launch that finds them (nothing
+// if null, or for no pairs): the records, the instance total, and as 64 bits,
+// and a copy of view_end.
+struct HostCounts {
+  uint32_t* counts;  // [4]
+  uint32_t* views;   // [n_views]
+  const uint32_t* view_end;
+  int n_views;
+};
 // Depth-ordered records, slot map (view*n + index -> depth position; of active pairs), and
 // the place of each record's first instance: toff[d] from its 256-record
 // block's start boff[d / 256]. The instance total in *total, and as 64 bits (to
@@ -181,7 +190,7 @@ void launch_ranges_fix(uint2* ranges, uint32_t tiles, hipStream_t s);
 // exact: count only the rectangle's tiles the record's alpha-floor ellipse reaches.
 void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
                    const Record* rec, Record* rec_sorted, int32_t* slot, uint32_t* toff, bool exact, uint32_t* boff,
-                   uint32_t* total, uint32_t* total64, hipStream_t s);
+                   uint32_t* total, uint32_t* total64, const HostCounts& host, hipStream_t s);
 // Instances beyond min(*total, cap) are not written; exact as for launch_gather.
 // Keys are 16-bit when the round's tile ids are below 2^16, else 32-bit. With
 // ranges_init, the launch also sets ranges_init[0..tiles) to (~0u, 0), the

@@ -776,7 +776,8 @@ constexpr int kOffsetThreads = 1024;
 __global__ void __launch_bounds__(kOffsetThreads) k_block_offsets(const uint32_t* n_dev, uint32_t n_max,
                                                                    uint32_t* __restrict__ bsum,
                                                                    uint32_t* __restrict__ total,
-                                                                   unsigned long long* __restrict__ total64) {
+                                                                   unsigned long long* __restrict__ total64,
+                                                                   HostCounts host) {
   __shared__ uint64_t s_wave[2][kOffsetThreads / 64];
   const uint32_t nb = (dev_n(n_dev, n_max) + kThreads - 1) / kThreads;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -829,6 +830,15 @@ __global__ void __launch_bounds__(kOffsetThreads) k_block_offsets(const uint32_t
   if (threadIdx.x == 0) {
     *total = (uint32_t)carry;
     *total64 = carry;
+  }
+  if (host.counts) {
+    if (threadIdx.x == 0) {
+      host.counts[0] = dev_n(n_dev, n_max);
+      host.counts[1] = (uint32_t)carry;
+      host.counts[2] = (uint32_t)carry;
+      host.counts[3] = (uint32_t)(carry >> 32);
+    }
+    for (int v = threadIdx.x; v < host.n_views; v += kOffsetThreads) host.views[v] = host.view_end[v];
   }
 }
 
@@ -1217,7 +1227,7 @@ void radix_sort16(uint16_t* keys, uint32_t* vals, uint16_t* keys_alt, uint32_t* 
 
 void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
                    const Record* rec, Record* rec_sorted, int32_t* slot, uint32_t* toff, bool exact, uint32_t* boff,
-                   uint32_t* total, uint32_t* total64, hipStream_t s) {
+                   uint32_t* total, uint32_t* total64, const HostCounts& host, hipStream_t s) {
   if (n_max == 0) {
     launch_fill_u32(total, 1, 0u, s);
     launch_fill_u32(total64, 2, 0u, s);
@@ -1226,7 +1236,7 @@ void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, c
   hipLaunchKernelGGL(k_gather, dim3(grid_for(n_max, kThreads)), dim3(kThreads), 0, s, n_dev, n_max, ids, pb,
                      rec, rec_sorted, slot, toff, exact, boff);
   hipLaunchKernelGGL(k_block_offsets, dim3(1), dim3(kOffsetThreads), 0, s, n_dev, n_max, boff, total,
-                     reinterpret_cast<unsigned long long*>(total64));
+                     reinterpret_cast<unsigned long long*>(total64), host);
 }
 
 template <typename K>
