@@ -232,12 +232,14 @@ struct Blend {
 // A staged list entry.
 struct Entry {
   float u, v, A, B, C, l2o, z, r, g, b;
+  uint32_t pos;
 };
 template <bool DEPTH>
 __device__ __forceinline__ Entry staged_entry(const Record& s) {
   const float4 a = s.a;
   const float2 b = make_float2(s.b.x, s.b.y);
-  return Entry{a.x, a.y, a.z, a.w, b.x, b.y, DEPTH ? s.b.z : 0.f, s.c.x, s.c.y, s.c.z};
+  const float4 c = s.c;
+  return Entry{a.x, a.y, a.z, a.w, b.x, b.y, DEPTH ? s.b.z : 0.f, c.x, c.y, c.z, __float_as_uint(c.w)};
 }
 
 // One entry over one quadrant: p2 = log2 alpha, pos its list position + 1. done
@@ -309,7 +311,9 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
                                                               float* __restrict__ pix_t,
                                                               uint32_t* __restrict__ pix_last) {
   constexpr int kWaves = 4 / NQ;
-  __shared__ Record s_rec[kWaves][64];  // staged: (u, v, A, B) (C, log2 opacity, z, -) (r, g, b, -)
+  // staged: (u, v, A, B) (C, log2 opacity, z, -) (r, g, b, list position + 1);
+  // the walk reads up to four entries past the last
+  __shared__ Record s_rec[kWaves][68];
   __shared__ uint32_t s_item;
   int tile;
   for (bool first = true; next_item(order, n_items, queue, &s_item, first, tile); first = false) {
@@ -337,14 +341,21 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
   for (uint32_t b0 = 0; b0 < count; b0 += 64) {
     uint32_t hits = 0u;  // per lane: the quadrants its entry can touch
     if (b0 + lane < count) {
-      Record& r = s_rec[wave][lane];
       float4 sa, sb, sc;
       stage_record(recs[d], sa, sb, sc);
-      r.a = sa;
-      r.b = sb;
-      r.c = sc;
 #pragma unroll
       for (int q = 0; q < NQ; ++q) hits |= !cull || quadrant_hit(sa, sb, tile_x0, tile_y0, q0 + q) ? 1u << q : 0u;
+      // one quadrant: the entries that touch it, without gaps
+      const uint64_t in = __ballot(hits != 0u);
+      const uint32_t slot =
+          NQ == 1 ? __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u)) : lane;
+      if (NQ > 1 || hits) {
+        sc.w = __uint_as_float(b0 + lane + 1);
+        Record& r = s_rec[wave][slot];
+        r.a = sa;
+        r.b = sb;
+        r.c = sc;
+      }
     }
     d = b0 + 64 + lane < count ? list[b0 + 64 + lane] : 0u;  // the next entries' records
     uint32_t live = 0u;  // the quadrants with a pixel still going
@@ -352,11 +363,10 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
     for (int q = 0; q < NQ; ++q) live |= __any(s[q].floor < 0.f) ? 1u << q : 0u;
     if (!live) break;
     uint64_t any = __ballot(hits & live);
+    int left = __popcll(any);  // (one quadrant) entries to walk
     __builtin_amdgcn_wave_barrier();  // (compiler only: the wave's LDS accesses are in order)
     const auto walk = [&](const Entry& e, int j) {
-      const uint32_t touch = __builtin_amdgcn_readlane(hits, j) & live;
-      uint32_t pos = b0 + j + 1;
-      asm("" : "+v"(pos));  // a vector register from here on
+      const uint32_t touch = NQ == 1 ? 1u : __builtin_amdgcn_readlane(hits, j) & live;
       const float dx[2] = {fx[0] - e.u, fx[1] - e.u};
       float row1[2], row2[2];
 #pragma unroll
@@ -370,29 +380,41 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
         if (NQ > 1 && !__builtin_expect((touch >> q) & 1u, 1)) continue;
         const float dq = dx[q & 1];
         const float p2 = fmaf(dq, fmaf(e.A, dq, row1[q >> 1]), row2[q >> 1]);
-        blend<DEPTH>(s[q], p2, e, pos, [&] {
+        blend<DEPTH>(s[q], p2, e, e.pos, [&] {
           live &= ~(1u << q);
-          any &= __ballot(hits & live);
+          if (NQ == 1) left = 0;
+          else any &= __ballot(hits & live);
         });
       }
     };
     const Record* stage = s_rec[wave];
     if constexpr (NQ == 1) {
-      // few waves: the next entry's LDS reads are in flight while one is blended
-      if (any) {
-        int j0 = lowest(any), j1;
-        Entry e0 = staged_entry<DEPTH>(stage[j0]), e1;
+      // few waves, so the longest list's instructions one after the other are
+      // the launch's time: the entries lie without gaps (no bit scan: one view of
+      // 300k primitives 97 -> 84 us), and the next one's LDS reads are in flight
+      // while one is blended
+      int off = 0;
+      asm("" : "+v"(off));  // a vector register: the LDS address
+      const auto at = [&](int k) {
+        return staged_entry<DEPTH>(reinterpret_cast<const Record*>(reinterpret_cast<const char*>(stage) + off)[k]);
+      };
+      if (left) {
+        Entry e0 = at(0), e1;
         for (;;) {
-          any &= ~(1ull << j0);
-          j1 = lowest(any) & 63;
-          e1 = staged_entry<DEPTH>(stage[j1]);
-          walk(e0, j0);
-          if (!any) break;
-          any &= ~(1ull << j1);
-          j0 = lowest(any) & 63;
-          e0 = staged_entry<DEPTH>(stage[j0]);
-          walk(e1, j1);
-          if (!any) break;
+          e1 = at(1);
+          walk(e0, 0);
+          if (left < 2) break;
+          e0 = at(2);
+          walk(e1, 0);
+          if (left < 3) break;
+          e1 = at(3);
+          walk(e0, 0);
+          if (left < 4) break;
+          e0 = at(4);
+          walk(e1, 0);
+          if (left < 5) break;
+          off += 4 * (int)sizeof(Record);
+          left -= 4;
         }
       }
     } else {
@@ -1173,14 +1195,15 @@ void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* que
   // Quadrants per wave, by the waves that the launch would have (8192 stay
   // resident): wider waves share more work per entry, but leave a small launch
   // too few waves and a long tail. Measured (us, one / two / four quadrants per
-  // wave; 300k primitives at 1352x1014): 5.4k tiles 97 / 114 / 173, 10.9k 152 /
-  // 147 / 196, 21.8k 281 / 224 / 256, 32.6k 420 / 325 / 338 (with depth), 43.5k
-  // 446 / 376 / 351.
+  // wave; 300k primitives at 1352x1014): 5.4k tiles 84 / 114 / 173, 10.9k 133 /
+  // 147 / 196, 16.3k 190 / 187, 21.8k 260 / 229 / 256, 32.6k 420 / 325 / 338 (with
+  // depth), 43.5k 446 / 376 / 351; without depth 10.9k 118 / 144, 16.3k 162 / 172,
+  // 21.8k 212 / 211, 32.6k 320 / 293.
 #define G4D_FWD(D, NQ)                                                                                            \
   launch_fwd<D, NQ>(total_tiles, order, queue, blocks, n_views, views, ranges, ival, rec_sorted, bg, channels, cull, \
                     out_rgb, out_depth, out_alpha, pix_t, pix_last, s)
   const bool d = out_depth != nullptr;
-  if (total_tiles < 8192) {
+  if (total_tiles < 2 * 8192) {
     if (d) G4D_FWD(true, 1); else G4D_FWD(false, 1);
   } else if (total_tiles < 5 * 8192) {
     if (d) G4D_FWD(true, 2); else G4D_FWD(false, 2);

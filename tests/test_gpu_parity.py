@@ -1397,11 +1397,11 @@ def test_nonfinite_parameters_are_culled_and_counted():
         assert np.linalg.norm(a[keep] - b) <= 1e-5 * nb, name
 
 
-@pytest.mark.parametrize("views", [683, 3414])
+@pytest.mark.parametrize("views", [683, 1366, 3414])
 def test_forward_quadrants_per_wave(views):
     """The forward rasteriser gives a wave one, two or four quadrants by the
-    launch's tile count (12 tiles a view here, ragged at both edges: 8196 and
-    40968 tiles, just past its two lines). Every view equals its own small
+    launch's tile count (12 tiles a view here, ragged at both edges: 8196 tiles, then
+    16392 and 40968, just past its two lines). Every view equals its own small
     render bit for bit, with and without the depth plane, all in one launch
     and taken from the tile queue."""
     from paper_2310_10642_amd import g4d
