@@ -29,8 +29,9 @@
 // A reduce-scatter per group combines the columns, leaving each of ten lanes
 // of a primitive with one value of its gradient line, and those lanes add the
 // tile's share with one FP64 atomic instruction into one 128-byte line. There
-// are two kernels: one wave per tile (large launches), and four waves per tile
-// in step at barriers, batches of 12 primitives (small ones).
+// are two kernels: one wave per tile (large launches), and several waves per
+// tile in step at barriers: four, batches of 12 primitives (small launches), or
+// eight in two roles, batches of 16 (the smallest).
 #include <algorithm>
 #include <type_traits>
 
@@ -48,14 +49,6 @@ using shade::sc_fma;
 // 1330 us without statistics, 1568 with the store, 1345 with the count).
 constexpr int kBlendedSlot = 15;
 
-// List entries per backward batch. 12 rather than 16: the per-(primitive,
-// pixel) buffers then take 26 KB, the workgroup 31.6 KB of LDS, and with at
-// most 96 VGPRs (the launch bound) five workgroups share a CU instead of four;
-// the backward is bound by issue stalls more than by its instruction count,
-// so the fifth wave per SIMD outweighs the third more barriers per entry. The
-// batch's 12 primitives also leave wave 0 free for the staging in phase 2.
-constexpr int kBwdBatch = 12;
-static_assert(kBwdBatch == 12, "phase 2 maps the batch's primitives onto waves 1-3, four each");
 // Backward LDS slots of one primitive's per-pixel values: pixel (row, col) of
 // the tile sits at 16 row + (col ^ 8 [(row >> 1) & 1]); the x-halves of rows
 // 2-3 of every four are swapped so that a wave's 8x8 quadrant (4 rows per
@@ -530,20 +523,36 @@ __device__ __forceinline__ void phase2_line(G (&q)[10], bool live, int j2, int c
 // HAS_D / HAS_A: whether dL/d(depth) and dL/d(alpha) are given (otherwise
 // their terms are compiled out). With loss.kind set, dl_rgb is the rendered
 // image and the image loss is folded in (LossArgs).
-template <bool HAS_D, bool HAS_A>
-__global__ void __launch_bounds__(256, 5) k_raster_backward(
-    const uint32_t* __restrict__ order, uint32_t n_items, uint32_t* queue, int n_views, const ViewDev* __restrict__ views, const uint2* __restrict__ ranges, const uint32_t* __restrict__ ival,
+template <bool HAS_D, bool HAS_A, bool PIPE>
+__global__ void __launch_bounds__(PIPE ? 512 : 256, PIPE ? 4 : 5) k_raster_backward(
+    const uint32_t* __restrict__ order, uint32_t n_items, uint32_t* queue, int n_views,
+    const ViewDev* __restrict__ views, const uint2* __restrict__ ranges, const uint32_t* __restrict__ ival,
     const Record* __restrict__ recs, float bg0, float bg1, float bg2, const float* __restrict__ dl_rgb,
     const float* __restrict__ dl_depth, const float* __restrict__ dl_alpha, const float* __restrict__ pix_t,
     const uint32_t* __restrict__ pix_last, double* __restrict__ grad2d, bool mark_blended, bool cull,
     LossArgs loss) {
-  __shared__ float4 s_a2[2][kBwdBatch], s_b2[2][kBwdBatch], s_c2[2][kBwdBatch];
-  __shared__ uint32_t s_d2[2][kBwdBatch];
-  __shared__ uint32_t s_qm2[2][kBwdBatch];
-  __shared__ uint32_t s_ill2[2];  // per staged batch: bit j when entry j's footprint is ill-conditioned
-  __shared__ uint32_t s_act[4];  // per quadrant: bit j when entry j blended somewhere in it
-  __shared__ float s_g[kBwdBatch * kGwStride];   // dL/dpower per (primitive, pixel)
-  __shared__ float s_w[kBwdBatch * kGwStride];   // a_i T_i per (primitive, pixel)
+  // Entries per batch, staged batches and batches' products in LDS, the wave
+  // that stages.
+  //
+  // Four waves: 12 entries rather than 16: the per-(primitive, pixel) buffers
+  // then take 26 KB, the workgroup 31.6 KB of LDS, and with at most 96 VGPRs
+  // (the launch bound) five workgroups share a CU instead of four; the backward
+  // is bound by issue stalls more than by its instruction count, so the fifth
+  // wave per SIMD outweighs the third more barriers per entry. The batch's 12
+  // primitives also leave wave 0 free for the staging in phase 2.
+  //
+  // PIPE, eight waves in two roles, phase 2 of a batch beside phase 1 of the
+  // next: the longest list's batches, one after the other, are the time of a
+  // launch of few tiles. 76 KB of LDS, two workgroups per CU. Batches of 12 took
+  // 39 us and of 8 (four workgroups per CU) 53 where 16 take 32.
+  constexpr int kBatch = PIPE ? 16 : 12, kStages = PIPE ? 3 : 2, kProducts = PIPE ? 2 : 1, kStager = PIPE ? 4 : 0;
+  __shared__ float4 s_a2[kStages][kBatch], s_b2[kStages][kBatch], s_c2[kStages][kBatch];
+  __shared__ uint32_t s_d2[kStages][kBatch];
+  __shared__ uint32_t s_qm2[kStages][kBatch];
+  __shared__ uint32_t s_ill2[kStages];  // per staged batch: bit j when entry j's footprint is ill-conditioned
+  __shared__ uint32_t s_act2[kProducts][4];  // per quadrant: bit j when entry j blended somewhere in it
+  __shared__ float s_g2[kProducts][kBatch * kGwStride];  // dL/dpower per (primitive, pixel)
+  __shared__ float s_w2[kProducts][kBatch * kGwStride];  // a_i T_i per (primitive, pixel)
   __shared__ float4 s_pix[256];
   __shared__ uint32_t s_max;
   __shared__ uint32_t s_item;
@@ -555,12 +564,13 @@ __global__ void __launch_bounds__(256, 5) k_raster_backward(
   const ViewDev& vw = views[vi];
   const int lt = tile - vw.tile_base;
   const int tx = lt % vw.tiles_x, ty = lt / vw.tiles_x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int lx = (wave & 1) * 8 + (lane & 7), ly = (wave >> 1) * 8 + (lane >> 3);
+  const int wave = PIPE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const bool blends = !PIPE || wave < 4;
+  const int lx = (wave & 1) * 8 + (lane & 7), ly = (wave >> 1 & 1) * 8 + (lane >> 3);
   const int p_self = ly * 16 + lx;                  // row-major pixel index within the tile
   const int q_self = gw_slot(ly, lx);               // this pixel's slot in s_g / s_w
   const int px = tx * kTile + lx, py = ty * kTile + ly;
-  const bool inside = px < vw.width && py < vw.height;
+  const bool inside = blends && px < vw.width && py < vw.height;
   const float fx = px + 0.5f, fy = py + 0.5f;
   const float tile_x0 = (float)(tx * kTile), tile_y0 = (float)(ty * kTile);
   const uint2 rg = ranges[tile];
@@ -592,8 +602,8 @@ __global__ void __launch_bounds__(256, 5) k_raster_backward(
     T = pix_t[pix];
     last = pix_last[pix];
   }
-  s_pix[p_self] = make_float4(gC0, gC1, gC2, gD);
-  if (loss.kind) {
+  if (blends) s_pix[p_self] = make_float4(gC0, gC1, gC2, gD);
+  if (loss.kind && blends) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
     if (lane == 0) s_loss[wave] = lsum;
@@ -613,20 +623,20 @@ __global__ void __launch_bounds__(256, 5) k_raster_backward(
   __syncthreads();
   const int max_last = (int)s_max;
 
-  const int c2 = threadIdx.x & 15;  // phase 2: pixel column
-  const int b_first = ((max_last + kBwdBatch - 1) / kBwdBatch - 1) * kBwdBatch;
-  // Staging pipeline (threads < 16): the record of the batch after the one in
-  // LDS and the list index of the batch after that are in flight, so no wait
-  // covers a load issued in the same batch.
+  const int c2 = lane & 15;  // phase 2: pixel column
+  const int b_first = ((max_last + kBatch - 1) / kBatch - 1) * kBatch;
+  // Staging pipeline (lanes < kBatch of one wave): the record of the batch
+  // after the one in LDS and the list index of the batch after that are in
+  // flight, so no wait covers a load issued in the same batch.
   Record nxt;
   uint32_t nxt_d = 0, nn_d = 0;
-  // Run by the whole of wave 0: lanes < 16 stage entry e0 + lane; then four
+  // Run by the whole wave: lanes < kBatch stage entry e0 + lane; then four
   // lanes per entry test its quadrants on the staged values (taken from the
   // staging lane by a shuffle) and a ballot gathers the four bits.
   auto stage = [&](int e0, int bb) {
-    const int t = (int)threadIdx.x;
+    const int t = lane;
     const float l2o = staged_log2_opacity(nxt);
-    if (t < kBwdBatch && e0 + t < count) {
+    if (t < kBatch && e0 + t < count) {
       stage_split(nxt, l2o, &s_a2[bb][t], &s_b2[bb][t], &s_c2[bb][t]);
       s_d2[bb][t] = nxt_d;
     }
@@ -640,41 +650,40 @@ __global__ void __launch_bounds__(256, 5) k_raster_backward(
     qb.y = __shfl(l2o, src, 64);
     const bool hit = e0 + src < count && (!cull || quadrant_hit(qa, qb, tile_x0, tile_y0, t & 3));
     const uint64_t bits = __ballot(hit);
-    if (t < kBwdBatch) s_qm2[bb][t] = (uint32_t)(bits >> (4 * t)) & 0xFu;
-    const uint64_t ill = __ballot(t < kBwdBatch && e0 + t < count && ill_conditioned(nxt));
+    if (t < kBatch) s_qm2[bb][t] = (uint32_t)(bits >> (4 * t)) & 0xFu;
+    const uint64_t ill = __ballot(t < kBatch && e0 + t < count && ill_conditioned(nxt));
     if (t == 0) s_ill2[bb] = (uint32_t)ill & 0xFFFFu;
   };
-  if (wave == 0 && b_first >= 0) {
-    if (threadIdx.x < kBwdBatch && b_first + (int)threadIdx.x < count) {
-      nxt_d = ival[rg.x + b_first + threadIdx.x];
+  if (wave == kStager && b_first >= 0) {
+    if (lane < kBatch && b_first + lane < count) {
+      nxt_d = ival[rg.x + b_first + lane];
       nxt = recs[nxt_d];
     }
     stage(b_first, 0);
-    const int e1 = b_first - kBwdBatch + (int)threadIdx.x;
-    if (threadIdx.x < kBwdBatch && e1 >= 0) {
+    const int e1 = b_first - kBatch + lane;
+    if (lane < kBatch && e1 >= 0) {
       nxt_d = ival[rg.x + e1];
       nxt = recs[nxt_d];
     }
-    const int e2n = e1 - kBwdBatch;
-    if (threadIdx.x < kBwdBatch && e2n >= 0) nn_d = ival[rg.x + e2n];
+    const int e2n = e1 - kBatch;
+    if (lane < kBatch && e2n >= 0) nn_d = ival[rg.x + e2n];
   }
-  int buf = 0;
-  for (int b0 = b_first; b0 >= 0; b0 -= kBwdBatch, buf ^= 1) {
+  // ---- phase 1: this lane's pixel, back to front over the batch from b0 in
+  // stage buffer sb, the products to buffer pb ----
+  const auto phase1 = [&](int b0, int sb, int pb) {
     // the stage buffer's first entry as a vector register, so each entry's
-    // LDS reads in phase 1 are immediate offsets from it
+    // LDS reads are immediate offsets from it
     int bv;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(bv) : "s"(buf * kBwdBatch));
+    asm volatile("v_mov_b32 %0, %1" : "=v"(bv) : "s"(sb * kBatch));
     const float4* s_a = &s_a2[0][0] + bv;
     const float4* s_b = &s_b2[0][0] + bv;
     const float4* s_c = &s_c2[0][0] + bv;
-    const uint32_t* s_d = s_d2[buf];
-    const uint32_t* s_qm = s_qm2[buf];
-    __syncthreads();
-    // ---- phase 1: this lane's pixel, back to front over the batch ----
+    const uint32_t* s_qm = s_qm2[sb];
+    float *s_g = s_g2[pb], *s_w = s_w2[pb];
     // entries that can reach this wave's quadrant before its last contributor
     uint32_t todo;
     {
-      const uint32_t qm = lane < kBwdBatch ? s_qm[lane] : 0u;
+      const uint32_t qm = lane < kBatch ? s_qm[lane] : 0u;
       todo = (uint32_t)__ballot(((qm >> wave) & 1u) && (uint32_t)(b0 + lane) < wave_last);
     }
     uint32_t blended = 0u;
@@ -702,69 +711,103 @@ __global__ void __launch_bounds__(256, 5) k_raster_backward(
     };
     // back to front over the set entries; j is a constant in every unrolled
     // step, so the LDS addresses are immediate offsets
-    if ((uint32_t)b0 + kBwdBatch <= wave_first_last) {
+    if ((uint32_t)b0 + kBatch <= wave_first_last) {
 #pragma unroll
-      for (int j = kBwdBatch - 1; j >= 0; --j) {
+      for (int j = kBatch - 1; j >= 0; --j) {
         if (!((todo >> j) & 1u)) continue;
         entry(j, s_a[j], s_b[j], s_c[j], std::false_type{});
       }
     } else {
 #pragma unroll
-      for (int j = kBwdBatch - 1; j >= 0; --j) {
+      for (int j = kBatch - 1; j >= 0; --j) {
         if (!((todo >> j) & 1u)) continue;
         entry(j, s_a[j], s_b[j], s_c[j], std::true_type{});
       }
     }
-    if (lane == 0) s_act[wave] = blended;
-    __syncthreads();
-    // ---- phase 2: primitive j2, pixel column c2, rows of active quadrants ----
-    // Waves 1-3 take primitives 4 (w - 1) .. 4 (w - 1) + 3; wave 0, which
-    // stages the next batch below, takes none, so the waves reach the next
-    // barrier together.
-    const int rank = wave - 1;
+    if (lane == 0) s_act2[pb][wave] = blended;
+  };
+  // ---- phase 2: primitive j2 = 4 rank + lane / 16, pixel column c2, rows of
+  // active quadrants: the lane's value of the gradient line, if any ----
+  const auto phase2 = [&](int rank, bool live, int sb, int pb, int& slot_q, double& val, uint32_t& d_atom) {
     const int j2 = 4 * rank + (lane >> 4);
-    const bool p2 = wave > 0;  // wave-uniform
-    const int e2 = b0 + j2;
-    const bool live = p2 && e2 < count;
-    int slot_q = -1;
-    double val = 0.0;
-    uint32_t d_atom = 0u;
-    if (p2) {
-      // FP64 sums for the waves whose four primitives include an
-      // ill-conditioned footprint (wave-uniform)
-      if ((s_ill2[buf] >> (4 * rank)) & 0xFu) {
-        double q[10];
-        phase2_line<double, HAS_D>(q, live, j2, c2, tx, ty, s_a, s_b, s_act, s_g, s_w, s_pix);
-        val = row16_reduce_scatter10(q, c2, slot_q);
-      } else {
-        float q[10];
-        phase2_line<float, HAS_D>(q, live, j2, c2, tx, ty, s_a, s_b, s_act, s_g, s_w, s_pix);
-        val = (double)row16_reduce_scatter10(q, c2, slot_q);
-      }
-      // the record blended in this tile: one more lane counts it in the
-      // gradient line's last value
-      if (mark_blended && c2 == 15 && (((s_act[0] | s_act[1] | s_act[2] | s_act[3]) >> j2) & 1u)) {
-        slot_q = kBlendedSlot;
-        val = 1.0;
-      }
-      d_atom = s_d[j2];
+    // FP64 sums for the waves whose four primitives include an
+    // ill-conditioned footprint (wave-uniform)
+    if ((s_ill2[sb] >> (4 * rank)) & 0xFu) {
+      double q[10];
+      phase2_line<double, HAS_D>(q, live, j2, c2, tx, ty, s_a2[sb], s_b2[sb],
+                                  s_act2[pb], s_g2[pb], s_w2[pb], s_pix);
+      val = row16_reduce_scatter10(q, c2, slot_q);
+    } else {
+      float q[10];
+      phase2_line<float, HAS_D>(q, live, j2, c2, tx, ty, s_a2[sb], s_b2[sb],
+                                  s_act2[pb], s_g2[pb], s_w2[pb], s_pix);
+      val = (double)row16_reduce_scatter10(q, c2, slot_q);
     }
-    // stage the next batch into the other buffer (read by nobody until the
-    // next loop-top barrier) and advance the loads, before this batch's atomics
-    if (wave == 0 && b0 >= kBwdBatch) {
-      stage(b0 - kBwdBatch, buf ^ 1);
-      const int e1 = b0 - 2 * kBwdBatch + (int)threadIdx.x;
-      if (threadIdx.x < kBwdBatch && e1 >= 0) {
-        nxt_d = nn_d;
-        nxt = recs[nxt_d];
-      }
-      const int e2n = e1 - kBwdBatch;
-      if (threadIdx.x < kBwdBatch && e2n >= 0) nn_d = ival[rg.x + e2n];
+    // the record blended in this tile: one more lane counts it in the
+    // gradient line's last value
+    if (mark_blended && c2 == 15 && (((s_act2[pb][0] | s_act2[pb][1] | s_act2[pb][2] | s_act2[pb][3]) >> j2) & 1u)) {
+      slot_q = kBlendedSlot;
+      val = 1.0;
     }
-    // ten lanes of the primitive's row each add one value of its gradient
-    // line, so a wave's atomics for a primitive share one 128-byte line
+    d_atom = s_d2[sb][j2];
+  };
+  // stages the batch from e0 in buffer sb and advances the loads
+  const auto stage_next = [&](int e0, int sb) {
+    stage(e0, sb);
+    const int e1 = e0 - kBatch + lane;
+    if (lane < kBatch && e1 >= 0) {
+      nxt_d = nn_d;
+      nxt = recs[nxt_d];
+    }
+    const int e2n = e1 - kBatch;
+    if (lane < kBatch && e2n >= 0) nn_d = ival[rg.x + e2n];
+  };
+  // ten lanes of the primitive's row each add one value of its gradient
+  // line, so a wave's atomics for a primitive share one 128-byte line
+  const auto add_line = [&](bool live, int slot_q, double val, uint32_t d_atom) {
     if (live && slot_q >= 0 && val != 0.0)
       unsafeAtomicAdd(grad2d + (size_t)d_atom * kGrad2dStride + slot_q, val);
+  };
+  if constexpr (PIPE) {
+    // one barrier per batch: waves 0-3 blend batch b0 while waves 4-7 sum the
+    // one before, four primitives each, and wave 4 stages the next
+    int sc = 0, sp = 2, cur = 0;  // stage buffers of this batch and the one before; product buffer of this one
+    for (int b0 = b_first; b_first >= 0 && b0 > -2 * kBatch; b0 -= kBatch) {
+      const int sn = sc == 2 ? 0 : sc + 1;
+      __syncthreads();
+      if (blends) {
+        if (b0 >= 0) phase1(b0, sc, cur);
+      } else {
+        const bool live = b0 < b_first && b0 + kBatch + 4 * (wave - 4) + (lane >> 4) < count;
+        int slot_q = -1;
+        double val = 0.0;
+        uint32_t d_atom = 0u;
+        phase2(wave - 4, live, sp, cur ^ 1, slot_q, val, d_atom);
+        // (the buffer was last read before the last barrier)
+        if (wave == kStager && b0 >= kBatch) stage_next(b0 - kBatch, sn);
+        add_line(live, slot_q, val, d_atom);
+      }
+      sp = sc;
+      sc = sn;
+      cur ^= 1;
+    }
+  } else {
+    int buf = 0;
+    for (int b0 = b_first; b0 >= 0; b0 -= kBatch, buf ^= 1) {
+      __syncthreads();
+      phase1(b0, buf, 0);
+      __syncthreads();
+      // Waves 1-3 sum four primitives each; wave 0, which stages the next
+      // batch (into the other buffer, read by nobody until the next barrier),
+      // none, so the waves reach that barrier together.
+      const bool live = wave > 0 && b0 + 4 * (wave - 1) + (lane >> 4) < count;
+      int slot_q = -1;
+      double val = 0.0;
+      uint32_t d_atom = 0u;
+      if (wave > 0) phase2(wave - 1, live, buf, 0, slot_q, val, d_atom);
+      if (wave == kStager && b0 >= kBatch) stage_next(b0 - kBatch, buf ^ 1);
+      add_line(live, slot_q, val, d_atom);
+    }
   }
   }  // items
 }
@@ -1225,6 +1268,9 @@ void launch_bwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blo
   // wave. Measured (us, four waves per tile / one; 300k primitives at
   // 1352x1014): 5.4k tiles 200 / 320, 10.9k 290 / 365, 16.3k 421 / 458, 21.8k
   // 562 / 516, 32.6k 844 / 693, 43.5k 1100 / 862.
+  // Below 2048 tiles two roles of waves (four waves per tile / two roles): 300
+  // tiles 368 / 259, 690 174 / 122, 1200 199 / 143, 1900 138 / 134, 2961 162 / 165,
+  // 5.4k 205 / 229; the 5k-primitive step's 520 tiles 45.6 / 32.
   if (total_tiles >= 5 * 4096) {
     const unsigned grid = item_grid(k_raster_backward_wave<HD, HA>, 64, total_tiles, queue, blocks, s);
     hipLaunchKernelGGL((k_raster_backward_wave<HD, HA>), dim3(grid), dim3(64), 0, s, order, (uint32_t)total_tiles,
@@ -1232,10 +1278,13 @@ void launch_bwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blo
                        pix_t, pix_last, grad2d, mark_blended, cull, loss);
     return;
   }
-  const unsigned grid = item_grid(k_raster_backward<HD, HA>, 256, total_tiles, queue, blocks, s);
-  hipLaunchKernelGGL((k_raster_backward<HD, HA>), dim3(grid), dim3(256), 0, s, order, (uint32_t)total_tiles, queue,
-                     n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], dl_rgb, dl_depth, dl_alpha, pix_t,
-                     pix_last, grad2d, mark_blended, cull, loss);
+  const bool pipe = total_tiles < 2048;
+  const auto kernel = pipe ? k_raster_backward<HD, HA, true> : k_raster_backward<HD, HA, false>;
+  const unsigned threads = pipe ? 512 : 256;
+  const unsigned grid = item_grid(kernel, threads, total_tiles, queue, blocks, s);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, order, (uint32_t)total_tiles, queue, n_views, views,
+                     ranges, ival, rec_sorted, bg[0], bg[1], bg[2], dl_rgb, dl_depth, dl_alpha, pix_t, pix_last,
+                     grad2d, mark_blended, cull, loss);
 }
 }  // namespace
 

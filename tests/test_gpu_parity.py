@@ -1421,10 +1421,12 @@ def test_forward_quadrants_per_wave(views):
                 assert torch.equal(got[k * hw * v:k * hw * (v + 1)], want), (queue, v, k)
 
 
+@pytest.mark.parametrize("views", [1710, 180])
 @pytest.mark.parametrize("planes", ["rgb", "depth", "alpha", "both", "loss", "nan"])
-def test_backward_one_wave_per_tile(planes):
+def test_backward_one_wave_per_tile(planes, views):
     """A launch of 20480 or more tiles takes the one-wave-per-tile backward;
-    the same views in two halves take the four-wave one. Needle footprints
+    the same views in two halves take the four-wave one. Below 2048 tiles the
+    waves take two roles: 2160 tiles against twice 1080. Needle footprints
     (the FP64 moments) and opaque ones (the alpha clamp), ragged 61x45 images
     (12 tiles a view), odd counts of list entries.
 
@@ -1434,7 +1436,6 @@ def test_backward_one_wave_per_tile(planes):
     cancellation between terms of both signs. A non-finite output gradient
     makes the same values non-finite."""
     from paper_2310_10642_amd import g4d
-    views = 1710
     sc = _needle_scene(62, 151, 1.2, 0.8)
     sc.opacity_logit[::3] += np.float32(8.0)
     r, _ = PT.gpu_setup(sc)
@@ -1444,7 +1445,7 @@ def test_backward_one_wave_per_tile(planes):
     dl = [torch.from_numpy(rng.uniform(-1, 1, k * hw * views).astype(np.float32)).cuda() for k in (3, 1, 1)]
     if planes == "nan":
         dl[0][5 * 3 * hw + hw + 777] = float("nan")
-        dl[0][900 * 3 * hw + 1234] = float("inf")
+        dl[0][(views // 2 + 45) * 3 * hw + 1234] = float("inf")
     use = (planes in ("depth", "both"), planes in ("alpha", "both"))
 
     def run(v0, v1, grads, accumulate):
