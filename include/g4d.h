@@ -142,7 +142,7 @@ g4d_status g4d_render(g4d_ctx* ctx, int32_t n_views, const g4d_camera* cams, con
  * graph capture, serving loops, harnesses that forbid hipMalloc. Same
  * arguments, outputs and kernels as g4d_render (images are identical), but it
  * calls no hipMalloc, hipFree or other allocating routine: every scratch
- * buffer of the render lives in one fixed array per GPU (about 163 MiB,
+ * buffer of the render lives in one fixed array per GPU (about 155 MiB,
  * allocated with the library's code when it is loaded on that GPU and held
  * until the process ends). Limits: at most 2^19 primitives (one view's
  * (view, primitive) pairs per round), 2^22 tile instances per round, 2^21

@@ -140,7 +140,7 @@ void na_sizes(size_t* out) {
   const size_t sizes[] = {
       sizeof(ViewDev) * kMaxViews,                                    // views_d
       32 * kNAGroups, 32 * kNAGroups, 16 * kNAGroups, 4 * kNAGroups,  // pactive plisted pfirst gcount
-      4 * P, 4 * P, 4 * P, 4 * P, 4 * P, 4 * P,                       // dkey slot ckey cval ckey2 cval2
+      4 * P, 4 * P, 4 * P, 4 * P, 4 * P,                              // dkey ckey cval ckey2 cval2
       4 * P,                                                          // toff
       sizeof(Record) * P, sizeof(Record) * P, sizeof(float4) * P,     // rec rec_sorted cdir
       P, 4 * P,                                                       // pany plist (primitives <= P)
@@ -151,11 +151,11 @@ void na_sizes(size_t* out) {
       sizeof(uint32_t) * kCntWords};                                  // counters
   for (size_t i = 0; i < sizeof(sizes) / sizeof(sizes[0]); ++i) out[i] = sizes[i];
 }
-constexpr int kNABufs = 31;
+constexpr int kNABufs = 30;
 
 constexpr size_t na_total_bytes() {
   // an upper bound of the carved total (each buffer 256-byte aligned)
-  return (sizeof(ViewDev) * kMaxViews + 256) + (84 * kNAGroups + 1024) + 7 * (4 * kNAPairs + 256) +
+  return (sizeof(ViewDev) * kMaxViews + 256) + (84 * kNAGroups + 1024) + 6 * (4 * kNAPairs + 256) +
          2 * (48 * kNAPairs + 256) + (16 * kNAPairs + 256) + (5 * kNAPairs + 512) + (4 * (kNAPairs / 256 + 4) + 256) +
          (4 * (256 * kNASortBlocks + 256) + 256) +
          4 * (4 * kNAInstances + 256) + (8 * kNATiles + 256) + 4 * (4 * kNATiles + 256) + 2 * (4 * kNAPixels + 256) +
@@ -414,7 +414,6 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   if ((st = ensure(c, c->gcount, 4 * groups))) return st;
   const size_t places = 64 * (((size_t)c->n + 63) / 64) * nv;  // a place per pair of every unit
   if ((st = ensure(c, c->dkey, 4 * places))) return st;
-  if ((st = ensure(c, c->slot, 4 * vn))) return st;
   if ((st = ensure(c, c->rec, sizeof(Record) * places))) return st;
   if ((st = ensure(c, c->cdir, sizeof(float4) * places))) return st;
   if ((st = ensure(c, c->ckey, 4 * vn))) return st;
@@ -471,7 +470,7 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   static_assert(kCntA == 0 && kCntI == 1 && kCntInst64 == 2, "HostCounts::counts");
   const HostCounts host{to_host ? c->counters_h : nullptr, c->counters_h + kCntViews, cnt + kCntViews, nv};
   launch_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->cval), pair_bits(c), P<Record>(c->rec),
-                P<Record>(c->rec_sorted), P<int32_t>(c->slot), P<uint32_t>(c->toff), c->ellipse_cull,
+                P<Record>(c->rec_sorted), P<uint32_t>(c->toff), c->ellipse_cull,
                 P<uint32_t>(c->scan_scratch), cnt + kCntI, cnt + kCntInst64, host, s);
   stage_end(c, G4D_STAGE_BINNING);
   HIPCHK(c, hipGetLastError());
@@ -621,7 +620,7 @@ g4d_status resolve_round(g4d_ctx* c, g4d_ctx::Round& r) {
 
 // The render's scratch buffers in the carving order of na_sizes.
 void render_bufs(g4d_ctx* c, DevBuf** b) {
-  DevBuf* l[kNABufs] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey,  &c->slot,   &c->ckey,         &c->cval,
+  DevBuf* l[kNABufs] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey, &c->ckey,         &c->cval,
                         &c->ckey2,   &c->cval2, &c->toff, &c->rec,    &c->rec_sorted,   &c->cdir,
                         &c->pany,    &c->plist, &c->scan_scratch, &c->radix_scratch, &c->ikey, &c->ival, &c->ikey2, &c->ival2, &c->ranges,
                         &c->okey,    &c->oval,  &c->okey2, &c->oval2, &c->pix_t,  &c->pix_last,     &c->counters};
@@ -1101,6 +1100,7 @@ g4d_status backward_impl(g4d_ctx* c, const LossSpec& ls, const float* rgb_in, co
     const uint32_t a_max = r.A == kOnDevice ? (uint32_t)((uint64_t)c->n * nv) : r.A;
     if ((st = ensure(c, c->grad2d, sizeof(double) * kGrad2dStride * (size_t)a_max))) return st;
     if ((st = ensure(c, c->bwd_scratch, sizeof(float) * preprocess_backward_scratch_floats(a_max)))) return st;
+    if ((st = ensure(c, c->slot, 4 * (size_t)c->n * nv))) return st;
     // the gradient lines start at zero (timed with the preprocess backward,
     // which reads them)
     stage_begin(c);

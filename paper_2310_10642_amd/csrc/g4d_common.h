@@ -127,7 +127,8 @@ void launch_colour(const RenderParams& p, const PairBits& pb, const float4* cdir
 size_t preprocess_backward_scratch_floats(size_t n_records);
 // Workgroups of the kernels that walk the active-primitive list of n primitives.
 unsigned list_grid(int n);
-void launch_preprocess_backward(const RenderParams& p, const PairBits& pb, const int32_t* slot, const double* grad2d,
+// slot: space for the pairs' map view * n + index -> depth position.
+void launch_preprocess_backward(const RenderParams& p, const PairBits& pb, int32_t* slot, const double* grad2d,
                                 const uint32_t* n_records_dev, uint32_t n_records_max, const uint32_t* ids,
                                 const Record* recs, float* scratch, float* g_means4, float* g_log_scales4,
                                 float* g_q_left, float* g_q_right, float* g_opacity_logit, float* g_coeffs,
@@ -183,13 +184,12 @@ struct HostCounts {
   const uint32_t* view_end;
   int n_views;
 };
-// Depth-ordered records, slot map (view*n + index -> depth position; of active pairs), and
-// the place of each record's first instance: toff[d] from its 256-record
+// Depth-ordered records and the place of each record's first instance: toff[d] from its 256-record
 // block's start boff[d / 256]. The instance total in *total, and as 64 bits (to
 // detect 32-bit overflow) in total64[0..1]. boff: scan scratch words.
 // exact: count only the rectangle's tiles the record's alpha-floor ellipse reaches.
 void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
-                   const Record* rec, Record* rec_sorted, int32_t* slot, uint32_t* toff, bool exact, uint32_t* boff,
+                   const Record* rec, Record* rec_sorted, uint32_t* toff, bool exact, uint32_t* boff,
                    uint32_t* total, uint32_t* total64, const HostCounts& host, hipStream_t s);
 // Instances beyond min(*total, cap) are not written; exact as for launch_gather.
 // Keys are 16-bit when the round's tile ids are below 2^16, else 32-bit. With

@@ -741,7 +741,7 @@ __global__ void __launch_bounds__(kChainThreads) k_rs_chain(const uint32_t* __re
 __global__ void __launch_bounds__(kThreads) k_gather(const uint32_t* n_dev, uint32_t n_max,
                                                       const uint32_t* __restrict__ ids, PairBits pb,
                                                       const Record* __restrict__ rec,
-                                                      Record* __restrict__ rec_sorted, int32_t* __restrict__ slot,
+                                                      Record* __restrict__ rec_sorted,
                                                       uint32_t* __restrict__ toff, bool exact,
                                                       uint32_t* __restrict__ bsum) {
   __shared__ uint32_t s_wave[4];
@@ -753,7 +753,6 @@ __global__ void __launch_bounds__(kThreads) k_gather(const uint32_t* n_dev, uint
     const uint32_t id = ids[d], v = id / (uint32_t)pb.n;
     const Record r = rec[pair_place(pb, v, id - v * (uint32_t)pb.n)];
     rec_sorted[d] = r;
-    slot[id] = (int32_t)d;
     const Footprint f = footprint(r);
     for (uint32_t ty = f.y0; ty < f.y1; ++ty) {
       uint32_t xa, xb;
@@ -1230,7 +1229,7 @@ void radix_sort16(uint16_t* keys, uint32_t* vals, uint16_t* keys_alt, uint32_t* 
 }
 
 void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
-                   const Record* rec, Record* rec_sorted, int32_t* slot, uint32_t* toff, bool exact, uint32_t* boff,
+                   const Record* rec, Record* rec_sorted, uint32_t* toff, bool exact, uint32_t* boff,
                    uint32_t* total, uint32_t* total64, const HostCounts& host, hipStream_t s) {
   if (n_max == 0) {
     launch_fill_u32(total, 1, 0u, s);
@@ -1238,7 +1237,7 @@ void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, c
     return;
   }
   hipLaunchKernelGGL(k_gather, dim3(grid_for(n_max, kThreads)), dim3(kThreads), 0, s, n_dev, n_max, ids, pb,
-                     rec, rec_sorted, slot, toff, exact, boff);
+                     rec, rec_sorted, toff, exact, boff);
   hipLaunchKernelGGL(k_block_offsets, dim3(1), dim3(kOffsetThreads), 0, s, n_dev, n_max, boff, total,
                      reinterpret_cast<unsigned long long*>(total64), host);
 }
