@@ -842,17 +842,20 @@ __global__ void __launch_bounds__(kOffsetThreads) k_block_offsets(const uint32_t
 }
 
 // ---------------------------------------------------------------- emit ----
-// One block per 64 consecutive records. The block lays out its records'
-// tile rows in LDS (first tile, offset of the row's first instance by a block
-// scan of the row widths) and, chunk by chunk, an instance -> row map, then
-// writes the block's instances coalesced, one per thread in turn. A block
-// whose rows do not fit walks each instance's record rows.
-constexpr int kEmitRecs = 64;
-constexpr int kEmitRows = 1024;
-constexpr int kEmitInst = 4096;
+// One block per 64 or 128 consecutive records, whose tile rows it takes up to
+// kEmitRows at a time (one record has no more). It lays the rows out in LDS
+// (first tile, offset of the row's first instance by a block scan of the row
+// widths) and, chunk by chunk, the row of the first of every four positions of
+// the output, then a thread writes four instances at a time, walking the rows
+// between them. (One instance at a time, and a search for the record of each
+// instance of blocks with more rows: 267 us for 4M records, 80M instances, 554 for
+// 5.7M, 236M; now 192 and 412, 3.4 TB/s of writes.)
+constexpr int kEmitRows = 1024;    // 16384 pixels
+constexpr int kEmitGroups = 2048;  // fours of a chunk
 
 // K: the key type, uint16_t when the round's tile ids are below 2^16.
-template <typename K>
+// kRecs: the records of a block.
+template <typename K, int kRecs>
 __global__ void __launch_bounds__(kThreads) k_emit(const uint32_t* n_dev, uint32_t n_max,
                                                     const uint32_t* __restrict__ toff,
                                                     const uint32_t* __restrict__ boff, const uint32_t* total,
@@ -861,32 +864,32 @@ __global__ void __launch_bounds__(kThreads) k_emit(const uint32_t* n_dev, uint32
                                                     const ViewDev* __restrict__ views, bool exact,
                                                     K* __restrict__ ikey, uint32_t* __restrict__ ival,
                                                     uint2* __restrict__ ranges_init, uint32_t tiles) {
-  __shared__ uint32_t offs[kEmitRecs + 1];
-  __shared__ uint32_t s_rbase[kEmitRecs + 1];
-  __shared__ uint32_t s_tb[kEmitRecs], s_tw[kEmitRecs];
-  __shared__ Footprint s_fp[kEmitRecs];
-  __shared__ uint32_t s_row_off[kEmitRows + 1];  // first instance of each row (block-relative)
+  __shared__ uint32_t offs[kRecs + 1];
+  __shared__ uint32_t s_rbase[kRecs + 1];
+  __shared__ uint32_t s_tb[kRecs], s_tw[kRecs];
+  __shared__ Footprint s_fp[kRecs];
+  __shared__ uint32_t s_row_off[kEmitRows + 1];  // first instance of each row (from the first record's on)
   __shared__ uint32_t s_row_tile[kEmitRows];     // global tile id of the row's first instance
-  __shared__ uint8_t s_row_rec[kEmitRows];       // record of the row (block-relative, < kEmitRecs)
-  __shared__ uint16_t s_inst_row[kEmitInst];     // row of each instance of the chunk (< kEmitRows)
-  static_assert(kEmitRecs <= 256 && kEmitRows <= 65536, "narrow LDS maps: 21 KB, 7 workgroups per CU");
+  __shared__ uint8_t s_row_rec[kEmitRows];       // record of the row (block-relative, < kRecs)
+  __shared__ uint16_t s_group_row[kEmitGroups];  // row of the first instance of each four of the chunk (< kEmitRows)
+  static_assert(kRecs <= 256 && kEmitRows <= 65536, "narrow LDS maps: 18 or 22 KB, eight or seven workgroups per CU");
   __shared__ uint32_t s_wave[4];
   // the tile ranges that the sort's last pass fills start empty
   if (ranges_init)
     for (uint32_t t = blockIdx.x * kThreads + threadIdx.x; t < tiles; t += gridDim.x * kThreads)
       ranges_init[t] = make_uint2(0xFFFFFFFFu, 0u);
   const uint32_t n = dev_n(n_dev, n_max);
-  const uint32_t d0 = blockIdx.x * kEmitRecs;
+  const uint32_t d0 = blockIdx.x * kRecs;
   if (d0 >= n) return;
-  const uint32_t nrec = min((uint32_t)kEmitRecs, n - d0);
+  const uint32_t nrec = min((uint32_t)kRecs, n - d0);
   const uint32_t tot = *total;
   uint32_t h = 0;
-  if (threadIdx.x < kEmitRecs) {
+  if (threadIdx.x < kRecs) {
     const uint32_t d = d0 + threadIdx.x;
     offs[threadIdx.x] = d < n ? boff[d / kThreads] + toff[d] : tot;
     if (threadIdx.x == 0) {
-      const uint32_t e = d0 + kEmitRecs;
-      offs[kEmitRecs] = e < n ? boff[e / kThreads] + toff[e] : tot;
+      const uint32_t e = d0 + kRecs;
+      offs[kRecs] = e < n ? boff[e / kThreads] + toff[e] : tot;
     }
     if (d < n) {
       const Footprint f = footprint(rec_sorted[d]);
@@ -899,23 +902,31 @@ __global__ void __launch_bounds__(kThreads) k_emit(const uint32_t* n_dev, uint32
   }
   uint32_t rows;
   const uint32_t rb = block_exclusive_scan(h, s_wave, rows);  // contains barriers
-  if (threadIdx.x < kEmitRecs) s_rbase[threadIdx.x] = rb;
-  // each record marks its rows with its block-relative index (h = 0 past
-  // the last record), so a row finds its record with one LDS read
-  if (rows <= (uint32_t)kEmitRows)
-    for (uint32_t k = 0; k < h; ++k) s_row_rec[rb + k] = (uint8_t)threadIdx.x;
+  if (threadIdx.x < kRecs) s_rbase[threadIdx.x] = rb;
+  if (threadIdx.x == 0) s_rbase[kRecs] = rows;
   __syncthreads();
   const uint32_t lim = min(tot, cap);
-  const uint32_t start = offs[0], end = min(offs[kEmitRecs], lim);
-  if (rows <= (uint32_t)kEmitRows) {
+  for (uint32_t r0 = 0, r1; r0 < nrec; r0 = r1) {
+    // records [r0, r1): at least one, as a record has at most kEmitRows rows
+    const uint32_t row0 = s_rbase[r0];
+    r1 = nrec;
+    if (rows - row0 > (uint32_t)kEmitRows)
+      r1 = r0 + (uint32_t)__syncthreads_count(threadIdx.x >= r0 && threadIdx.x < nrec &&
+                                              s_rbase[threadIdx.x + 1] - row0 <= (uint32_t)kEmitRows);
+    const uint32_t rows_here = s_rbase[r1] - row0;
+    // each record marks its rows with its block-relative index, so a row finds
+    // its record with one LDS read
+    if (threadIdx.x >= r0 && threadIdx.x < r1)
+      for (uint32_t k = 0; k < h; ++k) s_row_rec[rb - row0 + k] = (uint8_t)threadIdx.x;
+    __syncthreads();
     uint32_t carry = 0;
-    for (uint32_t j0 = 0; j0 < rows; j0 += kThreads) {
+    for (uint32_t j0 = 0; j0 < rows_here; j0 += kThreads) {
       const uint32_t j = j0 + threadIdx.x;
       uint32_t w = 0;
-      if (j < rows) {
+      if (j < rows_here) {
         const int lo = s_row_rec[j];
         const Footprint& f = s_fp[lo];
-        const uint32_t ty = f.y0 + (j - s_rbase[lo]);
+        const uint32_t ty = f.y0 + (row0 + j - s_rbase[lo]);
         uint32_t xa, xb;
         row_span(f, ty, exact, xa, xb);
         w = xb - xa;
@@ -923,50 +934,60 @@ __global__ void __launch_bounds__(kThreads) k_emit(const uint32_t* n_dev, uint32
       }
       uint32_t tot_w;
       const uint32_t ex = block_exclusive_scan(w, s_wave, tot_w);  // contains barriers
-      if (j < rows) s_row_off[j] = carry + ex;
+      if (j < rows_here) s_row_off[j] = carry + ex;
       carry += tot_w;
     }
-    if (threadIdx.x == 0) s_row_off[rows] = carry;
+    if (threadIdx.x == 0) s_row_off[rows_here] = carry;
     __syncthreads();
-    // the block's instances in chunks of kEmitInst: each chunk's instances
-    // are mapped to their rows, then written coalesced, one per thread in turn
-    const uint32_t iend = min(end, start + carry);  // equal: the counts come from the same spans
-    for (uint32_t c0 = 0; start + c0 < iend; c0 += kEmitInst) {
-      const uint32_t c1 = min(carry, c0 + (uint32_t)kEmitInst);
-      if (c0) __syncthreads();  // the previous chunk's reads of the map are done
-      for (uint32_t j = threadIdx.x; j < rows; j += kThreads) {
-        const uint32_t a = max(s_row_off[j], c0), b = min(s_row_off[j + 1], c1);
-        for (uint32_t k = a; k < b; ++k) s_inst_row[k - c0] = (uint16_t)j;
+    // instances [start, iend); the offsets' end is start + carry, as the counts
+    // come from the same spans
+    const uint32_t start = offs[r0], iend = min(min(offs[r1], lim), start + carry);
+    const uint32_t g_end = (iend + 3) / 4;
+    for (uint32_t c0 = start / 4; c0 * 4 < iend; c0 += kEmitGroups) {
+      if (c0 != start / 4) __syncthreads();  // the previous chunk's reads of the map are done
+      const uint32_t c1 = min(c0 + (uint32_t)kEmitGroups, g_end);
+      for (uint32_t j = threadIdx.x; j < rows_here; j += kThreads) {
+        const uint32_t o0 = s_row_off[j], o1 = s_row_off[j + 1];
+        const uint32_t a = max(o0 ? (start + o0 + 3) / 4 : start / 4, c0);
+        const uint32_t b = o1 > o0 ? min((start + o1 + 3) / 4, c1) : 0u;
+        for (uint32_t g = a; g < b; ++g) s_group_row[g - c0] = (uint16_t)j;
       }
       __syncthreads();
-      const uint32_t ie = min(iend, start + c1);
-      for (uint32_t i = start + c0 + threadIdx.x; i < ie; i += kThreads) {
-        const uint32_t k = i - start, j = s_inst_row[k - c0];
-        ikey[i] = (K)(s_row_tile[j] + (k - s_row_off[j]));
-        ival[i] = d0 + s_row_rec[j];
-      }
-    }
-  } else {
-    for (uint32_t i = start + threadIdx.x; i < end; i += kThreads) {
-      int lo = 0, hi = (int)nrec - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (offs[mid] <= i) lo = mid; else hi = mid - 1;
-      }
-      const Footprint& f = s_fp[lo];
-      uint32_t k = i - offs[lo], tile = 0;
-      for (uint32_t ty = f.y0; ty < f.y1; ++ty) {
-        uint32_t xa, xb;
-        row_span(f, ty, exact, xa, xb);
-        if (k < xb - xa) {
-          tile = ty * s_tw[lo] + xa + k;
-          break;
+      for (uint32_t g = c0 + threadIdx.x; g < c1; g += kThreads) {
+        uint32_t j = s_group_row[g - c0];
+        uint32_t off = s_row_off[j], next = s_row_off[j + 1], tile = s_row_tile[j], rec = d0 + s_row_rec[j];
+        const uint32_t i0 = max(g * 4, start), i1 = min(g * 4 + 4, iend);
+        const auto step = [&](uint32_t i) {  // to instance i's row
+          while (i - start >= next) {
+            off = next;
+            next = s_row_off[++j + 1];
+            tile = s_row_tile[j];
+            rec = d0 + s_row_rec[j];
+          }
+        };
+        if (i1 - i0 == 4) {
+          uint32_t k[4], v[4];
+#pragma unroll
+          for (uint32_t q = 0; q < 4; ++q) {
+            step(i0 + q);
+            k[q] = tile + (i0 + q - start - off);
+            v[q] = rec;
+          }
+          *reinterpret_cast<uint4*>(ival + i0) = make_uint4(v[0], v[1], v[2], v[3]);
+          if constexpr (sizeof(K) == 2)
+            *reinterpret_cast<uint2*>(ikey + i0) = make_uint2(k[0] | k[1] << 16, k[2] | k[3] << 16);
+          else
+            *reinterpret_cast<uint4*>(ikey + i0) = make_uint4(k[0], k[1], k[2], k[3]);
+        } else {
+          for (uint32_t i = i0; i < i1; ++i) {
+            step(i);
+            ikey[i] = (K)(tile + (i - start - off));
+            ival[i] = rec;
+          }
         }
-        k -= xb - xa;
       }
-      ikey[i] = (K)(s_tb[lo] + tile);
-      ival[i] = d0 + (uint32_t)lo;
     }
+    if (r1 < nrec) __syncthreads();  // the rows are read before the next records' replace them
   }
 }
 
@@ -1250,8 +1271,13 @@ void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, cons
     if (ranges_init) launch_ranges_init(ranges_init, tiles, s);
     return;
   }
-  hipLaunchKernelGGL(k_emit<K>, dim3(grid_for(n_max, kEmitRecs)), dim3(kThreads), 0, s, n_dev, n_max, toff, boff, total,
-                     cap, rec_sorted, ids, (uint32_t)n_prims, views, exact, ikey, ival, ranges_init, tiles);
+  // many records: twice as many per block, for half the blocks' fixed steps (4M
+  // 232 -> 192 us, 5.7M 462 -> 412; equal at 0.7M, and for one view's 88k, whose
+  // nearest and largest footprints share a block, 13.4 -> 18.1)
+  const bool many = n_max >= (1u << 20);
+  const auto kernel = many ? k_emit<K, 128> : k_emit<K, 64>;
+  hipLaunchKernelGGL(kernel, dim3(grid_for(n_max, many ? 128 : 64)), dim3(kThreads), 0, s, n_dev, n_max, toff, boff,
+                     total, cap, rec_sorted, ids, (uint32_t)n_prims, views, exact, ikey, ival, ranges_init, tiles);
 }
 
 void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,

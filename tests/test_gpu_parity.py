@@ -1572,3 +1572,26 @@ def test_counts_beyond_the_guess():
         d = dl[:got[0].numel()]
         _close_grads(r.backward(d), f.backward(d))
 
+
+@pytest.mark.parametrize("every", [9, 40])
+def test_emission_of_many_records(every):
+    """From 2^20 records on the emission takes 128 of them a block, and a block's
+    tile rows 1024 at a time: tall images (126 rows of tiles) with every 9th or
+    40th primitive across the whole height, so that most blocks or few have
+    more. Views of the one call equal their own renders (64 records a block)
+    bit for bit, and the tile lists are in order."""
+    sc = _big_splat_scene(83, 74000, grow=-2.5, sh=1, to=1, mu_log_t=1.0)
+    sc.log_scales4[::every, :3] += np.float32(3.0)
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.ring_camera(0.1 * v, 40, 2010) for v in range(16)]
+    times = [0.5] * 16
+    rgb = r.render(cams, times, depth=False, alpha=False)[0]
+    assert r.stats()["active_total"] >= 1 << 20 and r.stats()["rounds"] == 1
+    vals, ranges = r.debug("tile_vals").astype(np.int64), r.debug("ranges").astype(np.int64)
+    step = np.diff(vals) > 0
+    step[ranges[ranges[:, 0] < ranges[:, 1], 1][:-1] - 1] = True
+    assert step.all() and (ranges[:, 1] - ranges[:, 0]).sum() == len(vals)
+    k = 3 * 40 * 2010
+    for v in (0, 7, 15):
+        assert torch.equal(rgb[k * v:k * (v + 1)], r.render([cams[v]], [0.5], depth=False, alpha=False)[0]), v
+
