@@ -291,29 +291,37 @@ __global__ void __launch_bounds__(256) k_list_active(const uint8_t* __restrict__
   }
 }
 
-constexpr int kColourViews = 8;  // views whose activity flags k_colour loads together
+constexpr int kColourViews = 8;  // views that k_colour takes together
 
 // 4D spherindrical-harmonic colour (Sec. 3.2) of the primitives active in
-// some view (the list the preprocess built): a quad of lanes per listed
-// primitive, lane `sub` owning the basis functions lm = 4 sub + i and reading
+// some view (the list of them): a wave takes 16 listed primitives, a quad of
+// lanes each, lane `sub` owning the basis functions lm = 4 sub + i and reading
 // their coefficients straight from memory (the quad reads the primitive's
-// 192-byte Fourier terms together). Each quad walks only its own active
-// views, the k-th in round k (a wave takes as many rounds as its busiest
-// primitive has active views), with the next view's direction loaded while
-// the current one is evaluated. The colour goes into the pair's record in
-// (view, primitive) order, before the depth sort moves it (the pass runs
-// beside the scans and the depth sort). Per view every lane evaluates the basis,
-// weights its four functions by the Fourier terms, and a quad sum gives
-// c = max(0, 0.5 + sum). A primitive with a non-finite coefficient gets a
-// NaN colour, which the rasterisers read as fully transparent (and the pair
-// is counted as culled).
-__global__ void __launch_bounds__(256) k_colour(RenderParams p, PairBits pb,
+// coefficients once for all views, and in whole 16-byte pieces where they are
+// aligned). The pairs of the 16 primitives in eight views at a time, up to 128:
+//   1. a lane per view and primitive: its pair's place, listed in LDS;
+//   2. a lane per listed pair: the basis and the Fourier terms, to LDS;
+//   3. a quad per primitive, its pairs one after the other: the products with the
+//      coefficients, summed over the quad.
+// Vector instructions bounded it while each quad formed the bases of its own
+// pairs (four times the same, and idle while another quad of the wave had
+// more: 655 instructions a pair and lane, 270 of 355 us alone for 4M pairs). 355
+// -> 255 us, beside the compaction and the depth sort 452 -> 329; 5.7M pairs 715
+// -> 650; 0.7M 86 -> 66.
+struct ColourPair {  // (a fifth 16 bytes also spreads the pairs over the banks)
+  float4 basis[4];
+  float2 cs;  // cs[1], cs[2]
+  uint32_t place, pad;
+};
+__global__ void __launch_bounds__(256, 4) k_colour(RenderParams p, PairBits pb,
                                                 const float4* __restrict__ cdir, Record* __restrict__ rec) {
+  __shared__ ColourPair s_pairs[4][16 * kColourViews];  // 40 KB: four workgroups per CU
+  ColourPair* pairs = s_pairs[threadIdx.x >> 6];
   const int nb = (p.sh_degree + 1) * (p.sh_degree + 1);
   const int nt = p.t_order + 1;
   const int K3 = nt * nb * 3;
   const uint32_t count = *p.plist_n;
-  const int sub = threadIdx.x & 3;
+  const int sub = threadIdx.x & 3, lane = threadIdx.x & 63;
   const uint32_t stride = (gridDim.x * blockDim.x) >> 2;
   for (uint32_t e0 = ((blockIdx.x * blockDim.x) >> 2); e0 < count; e0 += stride) {
     const uint32_t e = e0 + (threadIdx.x >> 2);
@@ -321,82 +329,80 @@ __global__ void __launch_bounds__(256) k_colour(RenderParams p, PairBits pb,
     const int gidx = live ? (int)p.plist[e] : 0;
     float k[3][kBasisPerLane][3];
     if (live) load_own_coeffs(p.coeffs + (size_t)gidx * K3, sub, nb, nt, k);
-    bool finite = true;
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-#pragma unroll
-      for (int i = 0; i < kBasisPerLane; ++i)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          if (!live) k[n][i][c] = 0.f;
-          finite = finite && isfinite(k[n][i][c]);
-        }
-    const bool bad = quad_any(!finite);
     for (int v0 = 0; v0 < p.n_views; v0 += kColourViews) {
-      int ds[kColourViews];
-      uint32_t m = 0u;
+      // 1. lane `sub`: views v0 + sub and v0 + sub + 4
+      uint32_t at[2], m = 0u;
 #pragma unroll
-      for (int w = 0; w < kColourViews; ++w) {
-        ds[w] = -1;
-        if (live && v0 + w < p.n_views) {
-          const int at = (int)pair_place(pb, v0 + w, gidx);
-          ds[w] = pair_active(pb, v0 + w, gidx) ? at : -1;
-        }
-        m |= (ds[w] >= 0 ? 1u : 0u) << w;
+      for (int t = 0; t < 2; ++t) {
+        const int v = v0 + sub + 4 * t;
+        const bool there = live && v < p.n_views;
+        at[t] = there ? pair_place(pb, v, gidx) : 0u;
+        m |= (there && pair_active(pb, v, gidx) ? 1u : 0u) << (sub + 4 * t);
       }
-      uint32_t rounds = (uint32_t)__popc(m);
+      m |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xF, 0xF, true);  // over the quad
+      m |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xF, 0xF, true);
+      const uint32_t mine = (uint32_t)__popc(m);
+      uint32_t upto = mine;  // inclusive scan over the quads
 #pragma unroll
-      for (int off = 4; off < 64; off <<= 1) rounds = max(rounds, (uint32_t)__shfl_xor((int)rounds, off, 64));
-      // the quad's next active view, its pair's place and direction (in flight)
-      int w, d;
-      const auto next = [&] {
-        w = m ? __ffs(m) - 1 : -1;
-        m = m ? m & (m - 1u) : 0u;
-        d = -1;
+      for (int off = 4; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(upto, off, 64);
+        if (lane >= off) upto += y;
+      }
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63), first = upto - mine;
+      __builtin_amdgcn_wave_barrier();  // (the wave's LDS accesses are in order)
 #pragma unroll
-        for (int ww = 0; ww < kColourViews; ++ww) d = (ww == w) ? ds[ww] : d;
-      };
-      next();
-      float4 cd = w >= 0 ? cdir[d] : make_float4(0.f, 0.f, 1.f, 0.f);
-      for (uint32_t r = 0; r < rounds; ++r) {
-        const int wc = w, dc = d;
-        const float4 cdc = cd;
-        next();
-        if (w >= 0) cd = cdir[d];
-        if (wc < 0) continue;  // uniform per quad
-        float* o = reinterpret_cast<float*>(&rec[dc].c);
-        if (bad) {
-          if (sub == 0) {
-            const float nan = __int_as_float(0x7FC00000);
-            o[0] = nan;
-            o[1] = nan;
-            o[2] = nan;
-            if (p.nonfinite) atomicAdd(p.nonfinite + v0 + wc, 1u);
-          }
-          continue;
-        }
+      for (int t = 0; t < 2; ++t) {
+        const int w = sub + 4 * t;
+        if ((m >> w) & 1u) pairs[first + __popc(m & ((1u << w) - 1u))].place = at[t];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // 2.
+      for (uint32_t i = lane; i < total; i += 64) {
+        const float4 cd = cdir[pairs[i].place];
         float Y[16], cs[3] = {0.f, 0.f, 0.f};
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) Y[jj] = 0.f;
-        sh_eval(p.sh_degree, cdc.x, cdc.y, cdc.z, Y);
-        fourier_terms(p.t_order, cdc.w, p.t_period, cs);
-        float y[kBasisPerLane];
-        own_basis(Y, sub, y);
+        sh_eval(p.sh_degree, cd.x, cd.y, cd.z, Y);
+        fourier_terms(p.t_order, cd.w, p.t_period, cs);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pairs[i].basis[q] = make_float4(Y[4 * q], Y[4 * q + 1], Y[4 * q + 2], Y[4 * q + 3]);
+        pairs[i].cs = make_float2(cs[1], cs[2]);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // 3.
+      bool finite = true;
+#pragma unroll
+      for (int n = 0; n < 3; ++n)
+#pragma unroll
+        for (int i = 0; i < kBasisPerLane; ++i)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            if (!live) k[n][i][c] = 0.f;
+            finite = finite && isfinite(k[n][i][c]);
+          }
+      const bool bad = quad_any(!finite);
+      for (uint32_t i = first; i < upto; ++i) {  // uniform per quad
+        const float4 y4 = pairs[i].basis[sub];
+        const float2 f = pairs[i].cs;
+        const float y[kBasisPerLane] = {y4.x, y4.y, y4.z, y4.w};
         float col[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           float acc = 0.f;
 #pragma unroll
-          for (int i = 0; i < kBasisPerLane; ++i)
-            acc = fmaf(y[i], fmaf(cs[0], k[0][i][c], fmaf(cs[1], k[1][i][c], cs[2] * k[2][i][c])), acc);
-          col[c] = quad_sum(acc);
+          for (int j = 0; j < kBasisPerLane; ++j)
+            acc = fmaf(y[j], fmaf(1.f, k[0][j][c], fmaf(f.x, k[1][j][c], f.y * k[2][j][c])), acc);
+          col[c] = fmaxf(quad_sum(acc) + kColorOffset, 0.f);
         }
-        if (sub == 0) {
-          o[0] = fmaxf(col[0] + kColorOffset, 0.f);
-          o[1] = fmaxf(col[1] + kColorOffset, 0.f);
-          o[2] = fmaxf(col[2] + kColorOffset, 0.f);
-        }
+        // (a primitive with a non-finite coefficient is rendered transparent)
+        const float o = bad ? __int_as_float(0x7FC00000) : sub == 0 ? col[0] : sub == 1 ? col[1] : col[2];
+        if (sub < 3) reinterpret_cast<float*>(&rec[pairs[i].place].c)[sub] = o;
       }
+      if (bad && sub == 0 && p.nonfinite)
+        for (int w = 0; w < kColourViews; ++w)
+          if ((m >> w) & 1u) atomicAdd(p.nonfinite + v0 + w, 1u);
     }
   }
 }
