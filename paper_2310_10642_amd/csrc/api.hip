@@ -465,7 +465,7 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   else
     radix_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2), cnt + kCntA,
                (uint32_t)vn, 0, 32, radix_grid((uint32_t)est, c->sort_blocks), P<uint32_t>(c->radix_scratch), s);
-  // 4. depth-ordered records, slot map, tiles per record; 5. instance offsets
+  // 4. depth-ordered records; 5. instance offsets and totals
   if ((st = join_side(c))) return st;
   static_assert(kCntA == 0 && kCntI == 1 && kCntInst64 == 2, "HostCounts::counts");
   const HostCounts host{to_host ? c->counters_h : nullptr, c->counters_h + kCntViews, cnt + kCntViews, nv};
@@ -475,7 +475,8 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   stage_end(c, G4D_STAGE_BINNING);
   HIPCHK(c, hipGetLastError());
   if (to_host) {
-    if (!vn) HIPCHK(c, hipMemcpyAsync(c->counters_h, cnt, sizeof(uint32_t) * (kCntViews + nv), hipMemcpyDeviceToHost, s));
+    if (!vn)
+      HIPCHK(c, hipMemcpyAsync(c->counters_h, cnt, sizeof(uint32_t) * (kCntViews + nv), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipEventRecord(c->ev_counts, s));
   }
   return G4D_OK;
@@ -620,10 +621,10 @@ g4d_status resolve_round(g4d_ctx* c, g4d_ctx::Round& r) {
 
 // The render's scratch buffers in the carving order of na_sizes.
 void render_bufs(g4d_ctx* c, DevBuf** b) {
-  DevBuf* l[kNABufs] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey, &c->ckey,         &c->cval,
-                        &c->ckey2,   &c->cval2, &c->toff, &c->rec,    &c->rec_sorted,   &c->cdir,
-                        &c->pany,    &c->plist, &c->scan_scratch, &c->radix_scratch, &c->ikey, &c->ival, &c->ikey2, &c->ival2, &c->ranges,
-                        &c->okey,    &c->oval,  &c->okey2, &c->oval2, &c->pix_t,  &c->pix_last,     &c->counters};
+  DevBuf* l[kNABufs] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey, &c->ckey, &c->cval,
+                        &c->ckey2, &c->cval2, &c->toff, &c->rec, &c->rec_sorted, &c->cdir, &c->pany, &c->plist,
+                        &c->scan_scratch, &c->radix_scratch, &c->ikey, &c->ival, &c->ikey2, &c->ival2, &c->ranges,
+                        &c->okey, &c->oval, &c->okey2, &c->oval2, &c->pix_t, &c->pix_last, &c->counters};
   for (int i = 0; i < kNABufs; ++i) b[i] = l[i];
 }
 
@@ -744,11 +745,11 @@ g4d_status g4d_destroy(g4d_ctx* c) {
   if (!c) return G4D_EINVAL;
   (void)hipStreamSynchronize(c->stream);
   (void)hipStreamSynchronize(c->side);
-  DevBuf* bufs[] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey, &c->rec, &c->slot, &c->ckey, &c->cval, &c->ckey2,
-                    &c->cval2, &c->rec_sorted, &c->toff, &c->ikey, &c->ival, &c->ikey2, &c->ival2,
-                    &c->ranges, &c->pix_t, &c->pix_last, &c->grad2d, &c->scan_scratch, &c->radix_scratch,
-                    &c->counters, &c->bwd_scratch, &c->okey, &c->oval, &c->okey2, &c->oval2, &c->cdir,
-                    &c->pany, &c->plist, &c->loss_part};
+  DevBuf* bufs[] = {&c->views_d, &c->pactive, &c->plisted, &c->pfirst, &c->gcount, &c->dkey, &c->rec, &c->slot,
+                    &c->ckey, &c->cval, &c->ckey2, &c->cval2, &c->rec_sorted, &c->toff, &c->ikey, &c->ival, &c->ikey2,
+                    &c->ival2, &c->ranges, &c->pix_t, &c->pix_last, &c->grad2d, &c->scan_scratch, &c->radix_scratch,
+                    &c->counters, &c->bwd_scratch, &c->okey, &c->oval, &c->okey2, &c->oval2, &c->cdir, &c->pany,
+                    &c->plist, &c->loss_part};
   for (DevBuf* b : bufs)
     if (b->ptr) (void)hipFree(b->ptr);
   if (c->counters_h) (void)hipHostFree(c->counters_h);
@@ -1128,8 +1129,8 @@ g4d_status backward_impl(g4d_ctx* c, const LossSpec& ls, const float* rgb_in, co
     }
     RenderParams p = make_params(c, nv);
     stage_begin(c);
-    launch_preprocess_backward(p, pair_bits(c), P<int32_t>(c->slot), P<double>(c->grad2d), cnt + kCntA, a_max, P<uint32_t>(c->cval),
-                               P<Record>(c->rec_sorted), P<float>(c->bwd_scratch), g_means4, g_log_scales4, g_q_left,
+    launch_preprocess_backward(p, pair_bits(c), P<int32_t>(c->slot), P<double>(c->grad2d), cnt + kCntA, a_max,
+                               P<uint32_t>(c->cval), P<Record>(c->rec_sorted), P<float>(c->bwd_scratch), g_means4, g_log_scales4, g_q_left,
                                g_q_right, g_opacity_logit, g_coeffs, accumulate, c->densify, s);
     stage_end(c, G4D_STAGE_PREPROCESS_BWD);
     HIPCHK(c, hipGetLastError());

@@ -9,8 +9,8 @@
 // rounding alone and the cull, near-plane and rectangle decisions are those of
 // the exact arithmetic.
 // k_colour: the 4D spherindrical-harmonic colour (Sec. 3.2) of the active
-// pairs, written into their depth-ordered records once the gather has placed
-// them; it reads the coefficients of the primitives active in some view only.
+// pairs, written into their records before the gather orders them by depth; it
+// reads the coefficients of the primitives active in some view only.
 // The backward is in preprocess_bwd.hip.
 #include <cmath>
 

@@ -139,16 +139,6 @@ __device__ __forceinline__ uint4 load_group(const uint32_t* __restrict__ p, size
   return make_uint4(e < n ? p[e] : 0u, e + 1 < n ? p[e + 1] : 0u, e + 2 < n ? p[e + 2] : 0u, e + 3 < n ? p[e + 3] : 0u);
 }
 
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
-  return x;
-}
-
 __global__ void __launch_bounds__(kThreads) k_scan_reduce(const uint32_t* __restrict__ in, const uint32_t* n_dev,
                                                            uint32_t n_max, uint32_t* __restrict__ bsum) {
   __shared__ uint32_t s_wave[4];
@@ -649,9 +639,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_rs_small(const K* keys_in, co
 // the three launches of the passes above were latency: 17.7 us a pass -> 8.8
 // for 88k pairs, 18.0 -> 9.5 for 400k slots with 200k active, 25 -> 22.5 for 525k;
 // equal (24.5, 24) for 670k. Tiles of 8192, or 512 threads, took 10.6 and 9.1 for
-// 88k; windows of 16 and 32 tiles 9.1 and 9.4. Workgroups take tiles by ticket, and a tile's place behind the earlier ones comes from
-// what those have published per digit: their own count, then the sum up to and
-// with them, a flag in the same word. A tile publishes its count before it
+// 88k; windows of 16 and 32 tiles 9.1 and 9.4.
+// Workgroups take tiles by ticket, and a tile's place behind the earlier ones
+// comes from what those have published per digit: their own count, then the sum
+// up to and with them, a flag in the same word. A tile publishes its count before it
 // waits, and waits only for tiles with smaller tickets, which running
 // workgroups hold: every wait ends, whatever else occupies the device.
 constexpr int kChainThreads = 1024, kChainItems = 4;  // tiles of 4096 pairs
@@ -1265,8 +1256,9 @@ void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, c
 
 template <typename K>
 void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
-               const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact, K* ikey,
-               uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
+               const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims,
+               const ViewDev* views, bool exact, K* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles,
+               hipStream_t s) {
   if (n_max == 0) {
     if (ranges_init) launch_ranges_init(ranges_init, tiles, s);
     return;
@@ -1281,17 +1273,19 @@ void emit_keys(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, cons
 }
 
 void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
-                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims,
+                 const ViewDev* views, bool exact,
                  uint32_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
-  emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
-            s);
+  emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init,
+            tiles, s);
 }
 
 void launch_emit(const uint32_t* n_dev, uint32_t n_max, const uint32_t* toff, const uint32_t* boff,
-                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims, const ViewDev* views, bool exact,
+                 const uint32_t* total, uint32_t cap, const Record* rec_sorted, const uint32_t* ids, int n_prims,
+                 const ViewDev* views, bool exact,
                  uint16_t* ikey, uint32_t* ival, uint2* ranges_init, uint32_t tiles, hipStream_t s) {
-  emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init, tiles,
-            s);
+  emit_keys(n_dev, n_max, toff, boff, total, cap, rec_sorted, ids, n_prims, views, exact, ikey, ival, ranges_init,
+            tiles, s);
 }
 
 void launch_ranges_init(uint2* ranges, uint32_t tiles, hipStream_t s) {
