@@ -208,18 +208,11 @@ __device__ __forceinline__ bool next_item(const uint32_t* __restrict__ order, ui
   return true;
 }
 
-// Index of the lowest set bit (unspecified, but a lane, when there is none).
-__device__ __forceinline__ int lowest(uint64_t m) {
-  int j;
-  asm("s_ff1_i32_b64 %0, %1" : "=s"(j) : "s"(m));
-  return j;
-}
-
 // The front-to-back blend of one pixel per lane. A pixel that is done (or
 // outside the image) has an infinite floor, so no fragment counts any more.
 struct Blend {
   float T, C0, C1, C2, D, floor;
-  uint32_t last;  // 1 + list position of the last contributor
+  uint32_t last;  // list position of the last contributor (~0: none)
 };
 
 // A staged list entry.
@@ -235,7 +228,7 @@ __device__ __forceinline__ Entry staged_entry(const Record& s) {
   return Entry{a.x, a.y, a.z, a.w, b.x, b.y, DEPTH ? s.b.z : 0.f, c.x, c.y, c.z, __float_as_uint(c.w)};
 }
 
-// One entry over one quadrant: p2 = log2 alpha, pos its list position + 1. done
+// One entry over one quadrant: p2 = log2 alpha, pos its list position. done
 // is called when the quadrant's last pixel stops.
 template <bool DEPTH, typename Done>
 __device__ __forceinline__ void blend(Blend& s, float p2, const Entry& e, uint32_t pos, const Done& done) {
@@ -287,9 +280,9 @@ __device__ __forceinline__ void blend(Blend& s, float p2, const Entry& e, uint32
 // DEPTH: whether the depth plane is written (otherwise its sum is compiled
 // out). NQ: quadrants per wave: 4 (one wave per tile, four pixels per lane), 2
 // (two waves, one over the tile's upper and one over its lower half) or 1.
-// A wave stages 64 list entries at a time in LDS of its own, a lane each, and
-// tests them against its quadrants; then it walks those that can touch any,
-// reading each one's values once for all its quadrants.
+// A wave takes 64 list entries at a time, a lane each, tests them against its
+// quadrants and stages those that can touch any in LDS of its own, without gaps;
+// then it walks them, reading each one's values once for all its quadrants.
 template <bool DEPTH, int NQ>
 __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __restrict__ order, uint32_t n_items,
                                                               uint32_t* queue, int n_views,
@@ -304,7 +297,8 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
                                                               float* __restrict__ pix_t,
                                                               uint32_t* __restrict__ pix_last) {
   constexpr int kWaves = 4 / NQ;
-  // staged: (u, v, A, B) (C, log2 opacity, z, -) (r, g, b, list position + 1);
+  // staged: (u, v, A, B) (C, log2 opacity, z, -) (r, g, b, list position; with
+  // several quadrants, the position's last six bits and the quadrants);
   // the walk reads up to four entries past the last
   __shared__ Record s_rec[kWaves][68];
   __shared__ uint32_t s_item;
@@ -328,22 +322,28 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const bool inside = px + 8 * (q & 1) < vw.width && py + 8 * (q >> 1) < vw.height;
-    s[q] = Blend{1.f, 0.f, 0.f, 0.f, 0.f, inside ? kLog2AlphaMin : __builtin_inff(), 0u};
+    s[q] = Blend{1.f, 0.f, 0.f, 0.f, 0.f, inside ? kLog2AlphaMin : __builtin_inff(), ~0u};
   }
   uint32_t d = (uint32_t)lane < count ? list[lane] : 0u;
   for (uint32_t b0 = 0; b0 < count; b0 += 64) {
+    uint32_t live = 0u;  // the quadrants with a pixel still going
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) live |= __any(s[q].floor < 0.f) ? 1u << q : 0u;
+    if (!live) break;
     uint32_t hits = 0u;  // per lane: the quadrants its entry can touch
+    __builtin_amdgcn_wave_barrier();  // (compiler only: the wave's LDS accesses are in order)
     if (b0 + lane < count) {
       float4 sa, sb, sc;
       stage_record(recs[d], sa, sb, sc);
 #pragma unroll
       for (int q = 0; q < NQ; ++q) hits |= !cull || quadrant_hit(sa, sb, tile_x0, tile_y0, q0 + q) ? 1u << q : 0u;
-      // one quadrant: the entries that touch it, without gaps
+      // the entries that touch a live one, without gaps
+      hits &= live;
       const uint64_t in = __ballot(hits != 0u);
-      const uint32_t slot =
-          NQ == 1 ? __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u)) : lane;
-      if (NQ > 1 || hits) {
-        sc.w = __uint_as_float(b0 + lane + 1);
+      if (hits) {
+        const uint32_t slot =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+        sc.w = __uint_as_float(NQ > 1 ? hits << 6 | lane : b0 + lane);
         Record& r = s_rec[wave][slot];
         r.a = sa;
         r.b = sb;
@@ -351,15 +351,11 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
       }
     }
     d = b0 + 64 + lane < count ? list[b0 + 64 + lane] : 0u;  // the next entries' records
-    uint32_t live = 0u;  // the quadrants with a pixel still going
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) live |= __any(s[q].floor < 0.f) ? 1u << q : 0u;
-    if (!live) break;
-    uint64_t any = __ballot(hits & live);
-    int left = __popcll(any);  // (one quadrant) entries to walk
-    __builtin_amdgcn_wave_barrier();  // (compiler only: the wave's LDS accesses are in order)
-    const auto walk = [&](const Entry& e, int j) {
-      const uint32_t touch = NQ == 1 ? 1u : __builtin_amdgcn_readlane(hits, j) & live;
+    int left = __popcll(__ballot(hits != 0u));  // entries to walk
+    __builtin_amdgcn_wave_barrier();
+    const auto walk = [&](const Entry& e) {
+      const uint32_t touch = NQ == 1 ? 1u : (uint32_t)__builtin_amdgcn_readfirstlane(e.pos) >> 6 & live;
+      const uint32_t pos = NQ == 1 ? e.pos : (e.pos & 63u) | b0;
       const float dx[2] = {fx[0] - e.u, fx[1] - e.u};
       float row1[2], row2[2];
 #pragma unroll
@@ -373,49 +369,45 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
         if (NQ > 1 && !__builtin_expect((touch >> q) & 1u, 1)) continue;
         const float dq = dx[q & 1];
         const float p2 = fmaf(dq, fmaf(e.A, dq, row1[q >> 1]), row2[q >> 1]);
-        blend<DEPTH>(s[q], p2, e, e.pos, [&] {
+        blend<DEPTH>(s[q], p2, e, pos, [&] {
           live &= ~(1u << q);
-          if (NQ == 1) left = 0;
-          else any &= __ballot(hits & live);
+          if (NQ == 1 || !live) left = 0;
         });
       }
     };
     const Record* stage = s_rec[wave];
+    int off = 0;
+    asm("" : "+v"(off));  // a vector register: the LDS address
+    const auto at = [&](int k) {
+      return staged_entry<DEPTH>(reinterpret_cast<const Record*>(reinterpret_cast<const char*>(stage) + off)[k]);
+    };
     if constexpr (NQ == 1) {
       // few waves, so the longest list's instructions one after the other are
-      // the launch's time: the entries lie without gaps (no bit scan: one view of
-      // 300k primitives 97 -> 84 us), and the next one's LDS reads are in flight
-      // while one is blended
-      int off = 0;
-      asm("" : "+v"(off));  // a vector register: the LDS address
-      const auto at = [&](int k) {
-        return staged_entry<DEPTH>(reinterpret_cast<const Record*>(reinterpret_cast<const char*>(stage) + off)[k]);
-      };
+      // the launch's time: no bit scan over gaps (one view of 300k primitives 97
+      // -> 84 us), and the next entry's LDS reads are in flight while one is
+      // blended (with more quadrants that costs registers: 630 -> 655 us for 16
+      // mixed views of 1M)
       if (left) {
         Entry e0 = at(0), e1;
         for (;;) {
           e1 = at(1);
-          walk(e0, 0);
+          walk(e0);
           if (left < 2) break;
           e0 = at(2);
-          walk(e1, 0);
+          walk(e1);
           if (left < 3) break;
           e1 = at(3);
-          walk(e0, 0);
+          walk(e0);
           if (left < 4) break;
           e0 = at(4);
-          walk(e1, 0);
+          walk(e1);
           if (left < 5) break;
           off += 4 * (int)sizeof(Record);
           left -= 4;
         }
       }
     } else {
-      while (any) {
-        const int j = lowest(any);
-        any &= ~(1ull << j);
-        walk(staged_entry<DEPTH>(stage[j]), j);
-      }
+      for (; left > 0; --left, off += (int)sizeof(Record)) walk(at(0));
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -433,7 +425,7 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
     if (DEPTH) out_depth[pix] = s[q].D;
     if (out_alpha) out_alpha[pix] = 1.f - s[q].T;
     pix_t[pix] = s[q].T;
-    pix_last[pix] = s[q].last;
+    pix_last[pix] = s[q].last + 1u;
   }
   }  // items
 }
@@ -1241,7 +1233,9 @@ void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* que
   // wave; 300k primitives at 1352x1014): 5.4k tiles 84 / 114 / 173, 10.9k 133 /
   // 147 / 196, 16.3k 190 / 187, 21.8k 260 / 229 / 256, 32.6k 420 / 325 / 338 (with
   // depth), 43.5k 446 / 376 / 351; without depth 10.9k 118 / 144, 16.3k 162 / 172,
-  // 21.8k 212 / 211, 32.6k 320 / 293.
+  // 21.8k 212 / 211, 32.6k 320 / 293. (All before the entries lay without gaps for
+  // two and four quadrants too: 43.5k then 419 -> 404 with depth, 358 -> 347
+  // without, 16 mixed views of 1M 654 -> 635.)
 #define G4D_FWD(D, NQ)                                                                                            \
   launch_fwd<D, NQ>(total_tiles, order, queue, blocks, n_views, views, ranges, ival, rec_sorted, bg, channels, cull, \
                     out_rgb, out_depth, out_alpha, pix_t, pix_last, s)
