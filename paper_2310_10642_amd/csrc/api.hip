@@ -458,20 +458,31 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   launch_compact(pair_bits(c), P<uint32_t>(c->gcount), nv, P<uint32_t>(c->dkey), P<uint32_t>(c->ckey),
                  P<uint32_t>(c->cval), chained ? P<uint32_t>(c->radix_scratch) : nullptr, cnt + kCntA,
                  cnt + kCntViews + (c->totals_on_device ? v0 : 0), P<uint32_t>(c->scan_scratch), s);
-  // 3. stable sort by depth (any grid gives the same order)
-  if (chained)
-    chain_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2), cnt + kCntA,
-               (uint32_t)vn, (uint32_t)est, P<uint32_t>(c->radix_scratch), s);
-  else
-    radix_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2), cnt + kCntA,
-               (uint32_t)vn, 0, 32, radix_grid((uint32_t)est, c->sort_blocks), P<uint32_t>(c->radix_scratch), s);
-  // 4. depth-ordered records; 5. instance offsets and totals
-  if ((st = join_side(c))) return st;
   static_assert(kCntA == 0 && kCntI == 1 && kCntInst64 == 2, "HostCounts::counts");
   const HostCounts host{to_host ? c->counters_h : nullptr, c->counters_h + kCntViews, cnt + kCntViews, nv};
-  launch_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->cval), pair_bits(c), P<Record>(c->rec),
-                P<Record>(c->rec_sorted), P<uint32_t>(c->toff), c->ellipse_cull,
-                P<uint32_t>(c->scan_scratch), cnt + kCntI, cnt + kCntInst64, host, s);
+  int tile_rows = 0;
+  for (const ViewDev& d : vr) tile_rows = std::max(tile_rows, (int)d.tiles_y);
+  if (vn && sort_gather_fits(vn, tile_rows)) {
+    // 3. to 5. in one launch
+    if ((st = join_side(c))) return st;
+    launch_sort_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->ckey), P<uint32_t>(c->cval), pair_bits(c),
+                       P<Record>(c->rec), P<Record>(c->rec_sorted), P<uint32_t>(c->toff), c->ellipse_cull,
+                       P<uint32_t>(c->scan_scratch), cnt + kCntI, cnt + kCntInst64, host, s);
+  } else {
+    // 3. stable sort by depth (any grid gives the same order)
+    if (chained)
+      chain_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2),
+                 cnt + kCntA, (uint32_t)vn, (uint32_t)est, P<uint32_t>(c->radix_scratch), s);
+    else
+      radix_sort(P<uint32_t>(c->ckey), P<uint32_t>(c->cval), P<uint32_t>(c->ckey2), P<uint32_t>(c->cval2),
+                 cnt + kCntA, (uint32_t)vn, 0, 32, radix_grid((uint32_t)est, c->sort_blocks),
+                 P<uint32_t>(c->radix_scratch), s);
+    // 4. depth-ordered records; 5. instance offsets and totals
+    if ((st = join_side(c))) return st;
+    launch_gather(cnt + kCntA, (uint32_t)vn, P<uint32_t>(c->cval), pair_bits(c), P<Record>(c->rec),
+                  P<Record>(c->rec_sorted), P<uint32_t>(c->toff), c->ellipse_cull, P<uint32_t>(c->scan_scratch),
+                  cnt + kCntI, cnt + kCntInst64, host, s);
+  }
   stage_end(c, G4D_STAGE_BINNING);
   HIPCHK(c, hipGetLastError());
   if (to_host) {

@@ -191,6 +191,12 @@ struct HostCounts {
 void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
                    const Record* rec, Record* rec_sorted, uint32_t* toff, bool exact, uint32_t* boff,
                    uint32_t* total, uint32_t* total64, const HostCounts& host, hipStream_t s);
+// For few pairs and images of few tile rows: the sort of the (key, id) pairs by
+// the whole key and the gather of the result, in one launch.
+bool sort_gather_fits(uint64_t pairs, int tile_rows);
+void launch_sort_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* keys, uint32_t* ids,
+                        const PairBits& pb, const Record* rec, Record* rec_sorted, uint32_t* toff, bool exact,
+                        uint32_t* boff, uint32_t* total, uint32_t* total64, const HostCounts& host, hipStream_t s);
 // Instances beyond min(*total, cap) are not written; exact as for launch_gather.
 // Keys are 16-bit when the round's tile ids are below 2^16, else 32-bit. With
 // ranges_init, the launch also sets ranges_init[0..tiles) to (~0u, 0), the

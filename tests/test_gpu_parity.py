@@ -1513,10 +1513,11 @@ def test_large_tile_sort(n):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("n,views", [(1, 1), (1024, 1), (1025, 1), (4097, 1), (8192, 1), (8193, 1), (2731, 3), (9000, 5),
+@pytest.mark.parametrize("n,views", [(1, 1), (1024, 1), (1025, 1), (2048, 1), (2049, 1), (4097, 1), (8192, 1), (8193, 1), (2731, 3), (9000, 5),
                                      (40960, 8), (130000, 8)])
 def test_small_sorts(n, views):
-    """The sorts of few pairs: one workgroup of 1, 4 or 8 pairs a thread up to 8192,
+    """The sorts of few pairs: with the gather up to 2048, one workgroup of 4 or 8
+    pairs a thread up to 8192,
     chained one-launch passes beyond, the three-launch passes past 3 * 2^18. Pairs
     at the depth of others (copies of primitives) keep their order: the records
     are in order of (depth, view, primitive), every tile's list in order of the
