@@ -1100,6 +1100,28 @@ def test_image_loss_kernel():
         assert np.allclose(_np(grad), 0.5 * ref_g, rtol=1e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("n,off", [(1, 0), (2047, 0), (2052, 1), (524288, 0), (524293, 0), (2000003, 3)])
+def test_image_loss_blocks(n, off):
+    """The image loss around its 512-thread workgroups, one to 256 of them, on
+    aligned and unaligned images. Every term is >= 0, so the sum is off by at most
+    2^-24 of itself per addition of the longest chain: a thread's own, 6 in the
+    wave, 8 over the waves, 256 workgroups, and 4 roundings of a term and its
+    scale."""
+    from paper_2310_10642_amd import g4d
+    r = g4d.Renderer(1, 1)
+    gen = torch.Generator().manual_seed(n)
+    img, tgt = torch.rand(n + off, generator=gen)[off:], torch.rand(n + off, generator=gen)[off:]
+    I, Tg = (torch.cat([torch.zeros(off), x]).cuda()[off:] for x in (img, tgt))
+    d = img.double() - tgt.double()
+    for kind, ref, rg in [(g4d.G4D_LOSS_L1, d.abs().sum(), d.sign()), (g4d.G4D_LOSS_L2, (d * d).sum(), 2 * d)]:
+        loss = torch.zeros(1, device="cuda")
+        grad = torch.empty(n + off, device="cuda")[off:]
+        r.image_loss(kind, I, Tg, 0.5, loss, grad)
+        bound = (-(-n // (512 * 256)) + 4 + 6 + 8 + 256 + 4) * 2.0**-24
+        assert abs(float(loss) - 0.5 * float(ref)) <= bound * 0.5 * float(ref)
+        assert torch.allclose(grad.cpu().double(), 0.5 * rg, rtol=2.0**-22, atol=0)
+
+
 def test_backward_loss_equals_loss_then_backward():
     """The image loss folded into the backward (g4d_render_backward_loss) gives
     what g4d_image_loss followed by g4d_render_backward gives: gradients up to
@@ -1513,15 +1535,15 @@ def test_large_tile_sort(n):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("n,views", [(1, 1), (1024, 1), (1025, 1), (2048, 1), (2049, 1), (4097, 1), (8192, 1), (8193, 1), (2731, 3), (9000, 5),
-                                     (40960, 8), (130000, 8)])
+@pytest.mark.parametrize("n,views", [(1, 1), (1024, 1), (1025, 1), (2048, 1), (2049, 1), (4097, 1), (8192, 1),
+                                     (8193, 1), (2731, 3), (9000, 5), (40960, 8), (130000, 8)])
 def test_small_sorts(n, views):
     """The sorts of few pairs: with the gather up to 2048, one workgroup of 4 or 8
-    pairs a thread up to 8192,
-    chained one-launch passes beyond, the three-launch passes past 3 * 2^18. Pairs
-    at the depth of others (copies of primitives) keep their order: the records
-    are in order of (depth, view, primitive), every tile's list in order of the
-    records, on the first render and on the next (whose grid is another)."""
+    pairs a thread up to 8192, chained one-launch passes beyond, the three-launch
+    passes past 3 * 2^18. Pairs at the depth of others (copies of primitives) keep
+    their order: the records are in order of (depth, view, primitive), every tile's
+    list in order of the records, on the first render and on the next (whose grid
+    is another)."""
     sc = _big_splat_scene(73, n, grow=0.3 if n < 10000 else -1.5, sh=1, to=1, mu_log_t=1.0)
     sc.means4[n // 2:2 * (n // 2)] = sc.means4[:n // 2]
     r, _ = PT.gpu_setup(sc)
