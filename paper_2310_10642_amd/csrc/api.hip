@@ -393,7 +393,10 @@ int round_tiles(const g4d_ctx* c, int v0, int v1) {
 // records in that order and scan their tile counts. Counts stay on the device.
 // count: the pairs culled for a non-finite parameter are counted per view
 // (a render; not the binning again of a backward).
-g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = false) {
+// to_host: the counts are on their way to the host (take_counts); with guess,
+// what the stages enqueued next can hold: beyond that they see no instance.
+g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = false,
+                         const g4d_ctx::Round* guess = nullptr) {
   g4d_status st = join_side(c);  // the last colour pass writes buffers reused below
   if (st) return st;
   c->bound = -1;
@@ -459,7 +462,11 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
                  P<uint32_t>(c->cval), chained ? P<uint32_t>(c->radix_scratch) : nullptr, cnt + kCntA,
                  cnt + kCntViews + (c->totals_on_device ? v0 : 0), P<uint32_t>(c->scan_scratch), s);
   static_assert(kCntA == 0 && kCntI == 1 && kCntInst64 == 2, "HostCounts::counts");
-  const HostCounts host{to_host ? c->counters_h : nullptr, c->counters_h + kCntViews, cnt + kCntViews, nv};
+  HostCounts host{to_host ? c->counters_h : nullptr, c->counters_h + kCntViews, cnt + kCntViews, nv};
+  if (guess) {
+    host.max_records = guess->A;
+    host.max_instances = guess->I;
+  }
   int tile_rows = 0;
   for (const ViewDev& d : vr) tile_rows = std::max(tile_rows, (int)d.tiles_y);
   if (vn && sort_gather_fits(vn, tile_rows)) {
@@ -1014,13 +1021,13 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
     int k = cap_round_tiles(c, v0, k0);
     uint32_t A = 0;
     uint64_t inst = 0;
-    bool ahead;
+    bool ahead, guessed;
     for (;;) {
       // With counts from earlier renders to go by, the binning and the
       // rasteriser are enqueued behind the pairs for a guess at the counts (a
       // quarter above, within the arena), and the host waits for the true ones
-      // while the device works on; if they exceed the guess (the emission
-      // stops at its end) both stages run again for them. Waiting first left
+      // while the device works on; if they exceed the guess, these stages get
+      // no instance, and both run again for the true counts. Waiting first left
       // the device idle in the middle of every render: 120 -> 108 us for 1000
       // primitives at 64x64, 296 -> 286 for one view of 300k
       const int tiles_k = round_tiles(c, v0, v0 + k);
@@ -1029,10 +1036,11 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
       const uint64_t i_cap = std::min(std::min<uint64_t>(arena_instances(c), inst_cap),
                                       (uint64_t)(c->inst_hint * 1.25 * tiles_k) + 4096);
       ahead = c->active_hint > 0 && c->inst_hint > 0.0 && i_cap > 0 && !capturing(c);
-      if ((st = enqueue_pairs(c, v0, v0 + k, true, /*to_host=*/true))) return st;
+      const g4d_ctx::Round guess{v0, v0 + k, tiles_k, a_cap, (uint32_t)i_cap};
+      if ((st = enqueue_pairs(c, v0, v0 + k, true, /*to_host=*/true, ahead ? &guess : nullptr))) return st;
+      guessed = ahead;
       if (ahead) {
         if ((st = bin_tiles(c, tiles_k, a_cap, (uint32_t)i_cap))) return st;
-        const g4d_ctx::Round guess{v0, v0 + k, tiles_k, a_cap, (uint32_t)i_cap};
         if ((st = rasterise_round(c, guess, out_rgb, out_depth, out_alpha))) return st;
       }
       if ((st = take_counts(c, v0, k, A, inst))) return st;
@@ -1045,7 +1053,10 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
       k = std::max(1, std::min(k - 1, (int)(0.9 * (double)k * (double)inst_cap / (double)inst)));
     }
     g4d_ctx::Round r{v0, v0 + k, round_tiles(c, v0, v0 + k), A, (uint32_t)inst};
-    if (!ahead && (st = bin_tiles(c, r.tiles, r.A, r.I))) return st;
+    if (!ahead) {
+      if (guessed) launch_fill_u32(cnt + kCntI, 1, r.I, s);  // (zero, being beyond the guess)
+      if ((st = bin_tiles(c, r.tiles, r.A, r.I))) return st;
+    }
     c->rounds.push_back(r);
     c->bound = (int)c->rounds.size() - 1;
     if (!ahead && (st = rasterise_round(c, r, out_rgb, out_depth, out_alpha))) return st;

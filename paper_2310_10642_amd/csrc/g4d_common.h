@@ -183,10 +183,16 @@ struct HostCounts {
   uint32_t* views;   // [n_views]
   const uint32_t* view_end;
   int n_views;
+  // The records and instances that the stages enqueued behind the counts can
+  // hold (they may be guesses): beyond either, *total is zero, so that those
+  // stages see no instance.
+  uint32_t max_records = 0xFFFFFFFFu;
+  uint64_t max_instances = 0xFFFFFFFFull;
 };
 // Depth-ordered records and the place of each record's first instance: toff[d] from its 256-record
-// block's start boff[d / 256]. The instance total in *total, and as 64 bits (to
-// detect 32-bit overflow) in total64[0..1]. boff: scan scratch words.
+// block's start boff[d / 256]. The instance total in *total (zero beyond host's
+// limits), and as 64 bits (to detect 32-bit overflow) in total64[0..1]. boff:
+// scan scratch words.
 // exact: count only the rectangle's tiles the record's alpha-floor ellipse reaches.
 void launch_gather(const uint32_t* n_dev, uint32_t n_max, const uint32_t* ids, const PairBits& pb,
                    const Record* rec, Record* rec_sorted, uint32_t* toff, bool exact, uint32_t* boff,

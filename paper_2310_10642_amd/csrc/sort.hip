@@ -773,11 +773,13 @@ __global__ void __launch_bounds__(kThreads) k_gather(const uint32_t* n_dev, uint
 }
 
 // The instance total of n records to the device and, if asked for, the counts to
-// the host, by a workgroup of 1024.
+// the host, by a workgroup of 1024. The emission writes the instances of the
+// records that it was launched for, and of those the ones below its capacity;
+// the sort and the rasteriser would take as many as the total says.
 __device__ __forceinline__ void write_totals(uint64_t sum, uint32_t n, uint32_t* total, unsigned long long* total64,
                                              const HostCounts& host) {
   if (threadIdx.x == 0) {
-    *total = (uint32_t)sum;
+    *total = n <= host.max_records && sum <= host.max_instances ? (uint32_t)sum : 0u;
     *total64 = sum;
   }
   if (host.counts) {

@@ -1618,3 +1618,46 @@ def test_emission_of_many_records(every):
     for v in (0, 7, 15):
         assert torch.equal(rgb[k * v:k * (v + 1)], r.render([cams[v]], [0.5], depth=False, alpha=False)[0]), v
 
+
+
+def _near_and_far_scene(seed, n_big, n_small):
+    """n_big large primitives alive around t = 0.1 only, n_small tiny ones around 0.9."""
+    sc = scenegen.random_scene(seed, n_big + n_small, sh_degree=1, t_order=1)
+    sc.q_left[:], sc.q_right[:] = np.float32([1, 0, 0, 0]), np.float32([1, 0, 0, 0])
+    sc.log_scales4[:, 3] = np.float32(-4.0)
+    sc.log_scales4[:n_big, :3], sc.log_scales4[n_big:, :3] = np.float32(0.0), np.float32(-6.0)
+    sc.opacity_logit[:] = np.float32(1.0)
+    sc.means4[:, :3] *= np.float32(0.5)
+    sc.means4[:n_big, 3], sc.means4[n_big:, 3] = np.float32(0.1), np.float32(0.9)
+    return sc
+
+
+@pytest.mark.parametrize("w,h,views,n_big", [(160, 120, 1, 1000), (160, 120, 3, 1000), (160, 120, 1, 200), (16, 16, 1, 1000)])
+def test_records_beyond_the_guess(w, h, views, n_big):
+    """A render whose records (and in two cases its instances) exceed the guess
+    from earlier renders: few active primitives that cover the image, then
+    20,000 active ones of a few tiles at most, and back. The stages enqueued
+    for the guess may see no instance (they would read slots that nothing
+    wrote): images, statistics (the longest list among them), tile lists and
+    gradients are those of a new context. A 16x16 image has one tile, whose list takes no
+    sort."""
+    sc = _near_and_far_scene(91, n_big, 20000)
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.look_at_camera((0.2 * v, 0.1, 4.0), w, h) for v in range(views)]
+    dl = torch.from_numpy(np.random.default_rng(92).uniform(-1, 1, 3 * w * h * views).astype(np.float32)).cuda()
+    if w == 16:  # (an arena of more slots than the first single tile fills)
+        r.render([scenegen.look_at_camera((0.0, 0.1, 4.0), 160, 120)], [0.1])
+    most = 0  # active in one view so far
+    for t in (0.1, 0.1, 0.9, 0.1, 0.9):
+        f, _ = PT.gpu_setup(sc)
+        got, want = r.render(cams, [t] * views), f.render(cams, [t] * views)
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), t
+        sg = r.stats()
+        assert sg == f.stats(), t
+        assert sg["max_tile_list"] == int(np.diff(r.debug("ranges").astype(np.int64), axis=1).max())
+        if t == 0.9 and most <= n_big:
+            assert sg["active_total"] > most * views * 5 // 4 + 4096  # beyond the guess at the records
+        most = max(most, max(sg["active_per_view"]))
+        assert np.array_equal(r.debug("tile_vals"), f.debug("tile_vals"))
+        _close_grads(r.backward(dl), f.backward(dl))
