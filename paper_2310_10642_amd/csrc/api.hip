@@ -113,6 +113,7 @@ constexpr int kCntNF = kCntTot + 4;
 // then the length of the round's list of primitives active in some view
 constexpr int kCntPList = kCntNF + kMaxViews;
 constexpr int kCntQueue = kCntPList + 1;  // the rasterisers' tile queue head
+constexpr int kCntBeyond = kCntPList + 2;  // whether a round is beyond the guess at its counts
 constexpr int kCntWords = kCntPList + 4;
 constexpr uint32_t kOnDevice = 0xFFFFFFFFu;  // a round count known only on the device
 // Tiles per round (unless one view alone has more): tile ids then fit 16
@@ -466,6 +467,7 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   if (guess) {
     host.max_records = guess->A;
     host.max_instances = guess->I;
+    host.beyond = cnt + kCntBeyond;
   }
   int tile_rows = 0;
   for (const ViewDev& d : vr) tile_rows = std::max(tile_rows, (int)d.tiles_y);
@@ -606,7 +608,9 @@ g4d_status bin_tiles(g4d_ctx* c, int tiles, uint32_t a_max, uint32_t cap) {
   return G4D_OK;
 }
 
-g4d_status rasterise_round(g4d_ctx* c, const g4d_ctx::Round& r, float* out_rgb, float* out_depth, float* out_alpha) {
+// guess: the round's counts are guesses, and nothing is written if they are too small
+g4d_status rasterise_round(g4d_ctx* c, const g4d_ctx::Round& r, float* out_rgb, float* out_depth, float* out_alpha,
+                           bool guess = false) {
   hipStream_t s = c->stream;
   g4d_status st = join_side(c);  // the records' colours
   if (st) return st;
@@ -617,8 +621,8 @@ g4d_status rasterise_round(g4d_ctx* c, const g4d_ctx::Round& r, float* out_rgb, 
                         c->persistent_blocks ? P<uint32_t>(c->counters) + kCntQueue : nullptr, c->persistent_blocks,
                         r.v1 - r.v0,
                         P<ViewDev>(c->views_d), P<uint2>(c->ranges), P<uint32_t>(c->ival), P<Record>(c->rec_sorted),
-                        c->flow_mode ? kZero3 : c->opts.bg, c->flow_mode ? 2 : 3, c->ellipse_cull, out_rgb,
-                        out_depth, out_alpha,
+                        c->flow_mode ? kZero3 : c->opts.bg, c->flow_mode ? 2 : 3, c->ellipse_cull,
+                        guess ? P<uint32_t>(c->counters) + kCntBeyond : nullptr, out_rgb, out_depth, out_alpha,
                         P<float>(c->pix_t), P<uint32_t>(c->pix_last), s);
   stage_end(c, G4D_STAGE_RASTER_FWD);
   HIPCHK(c, hipGetLastError());
@@ -1027,9 +1031,10 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
       // rasteriser are enqueued behind the pairs for a guess at the counts (a
       // quarter above, within the arena), and the host waits for the true ones
       // while the device works on; if they exceed the guess, these stages get
-      // no instance, and both run again for the true counts. Waiting first left
-      // the device idle in the middle of every render: 120 -> 108 us for 1000
-      // primitives at 64x64, 296 -> 286 for one view of 300k
+      // no instance and write no pixel (the true counts may be over the cap), and
+      // both run again for the true counts. Waiting first left the device idle in
+      // the middle of every render: 120 -> 108 us for 1000 primitives at 64x64,
+      // 296 -> 286 for one view of 300k
       const int tiles_k = round_tiles(c, v0, v0 + k);
       const uint64_t vn = (uint64_t)c->n * k;
       const uint32_t a_cap = (uint32_t)std::min<uint64_t>(vn, (uint64_t)c->active_hint * k * 5 / 4 + 4096);
@@ -1041,7 +1046,7 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
       guessed = ahead;
       if (ahead) {
         if ((st = bin_tiles(c, tiles_k, a_cap, (uint32_t)i_cap))) return st;
-        if ((st = rasterise_round(c, guess, out_rgb, out_depth, out_alpha))) return st;
+        if ((st = rasterise_round(c, guess, out_rgb, out_depth, out_alpha, /*guess=*/true))) return st;
       }
       if ((st = take_counts(c, v0, k, A, inst))) return st;
       c->inst_hint = std::max((double)inst / std::max(tiles_k, 1), c->inst_hint * (15.0 / 16.0));

@@ -779,8 +779,10 @@ __global__ void __launch_bounds__(kThreads) k_gather(const uint32_t* n_dev, uint
 __device__ __forceinline__ void write_totals(uint64_t sum, uint32_t n, uint32_t* total, unsigned long long* total64,
                                              const HostCounts& host) {
   if (threadIdx.x == 0) {
-    *total = n <= host.max_records && sum <= host.max_instances ? (uint32_t)sum : 0u;
+    const bool fits = n <= host.max_records && sum <= host.max_instances;
+    *total = fits ? (uint32_t)sum : 0u;
     *total64 = sum;
+    if (host.beyond) *host.beyond = fits ? 0u : 1u;
   }
   if (host.counts) {
     if (threadIdx.x == 0) {

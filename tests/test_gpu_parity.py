@@ -1661,3 +1661,32 @@ def test_records_beyond_the_guess(w, h, views, n_big):
         most = max(most, max(sg["active_per_view"]))
         assert np.array_equal(r.debug("tile_vals"), f.debug("tile_vals"))
         _close_grads(r.backward(dl), f.backward(dl))
+
+
+def test_a_refused_render_writes_no_output():
+    """A view over the instance cap is a capacity error that leaves its outputs as
+    they were, also when earlier renders let the stages be enqueued before the
+    counts are known: with and without the tile queue, for images, flow and the
+    no-allocation render."""
+    from paper_2310_10642_amd import g4d
+    sc = _big_splat_scene(93, 3000, grow=0.5, sh=1, to=1, mu_log_t=1.0)
+    r, _ = PT.gpu_setup(sc)
+    cam = scenegen.look_at_camera((0.3, 0.1, 3.5), 150, 110)
+    calls = (lambda out: r.render([cam], [0.5], out=out), lambda out: r.render_flow([cam], [0.5], 0.1, out=out[0][:2 * 150 * 110]),
+             lambda out: r.render_noalloc([cam], [0.5], out))
+    ref = [x.clone() for x in r.render([cam], [0.5])]
+    need = r.stats()["instances"]
+    for queue in (0, -1):
+        r.set_tuning(g4d.G4D_TUNE_PERSISTENT_BLOCKS, queue)
+        for call in calls:
+            for cap in (1, need // 2, need - 1):
+                out = [torch.full_like(x, 7.0) for x in ref]
+                r.set_tuning(g4d.G4D_TUNE_ROUND_INSTANCES, cap)
+                with pytest.raises(g4d.G4DError) as ei:
+                    call(out)
+                torch.cuda.synchronize()
+                assert ei.value.status == g4d.G4D_ECAPACITY
+                assert all(bool((x == 7.0).all()) for x in out), (queue, cap)
+        r.set_tuning(g4d.G4D_TUNE_ROUND_INSTANCES, need)
+        for a, b in zip(r.render([cam], [0.5]), ref):
+            assert torch.equal(a, b)
