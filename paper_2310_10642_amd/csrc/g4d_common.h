@@ -19,7 +19,10 @@ constexpr float kColorOffset = 0.5f;
 // log2(1/255): fragments with log2(opacity * exp(power)) below this are skipped
 constexpr float kLog2AlphaMin = -7.994353436858858f;
 // log2(0.99) less a margin over the rounding of log2 and exp2: a fragment of a
-// record whose log2 opacity is below this never reaches the alpha clamp
+// record whose log2 opacity is below this never reaches the alpha clamp, as its
+// power is not positive. For elongated footprints (ill_conditioned) FP32 rounding
+// can make it so by far more than the margin; for others the quadratic form is
+// at least 1/200 of the sum of its terms' magnitudes, whose rounding is 1e-6 of it.
 constexpr float kLog2AlphaMax = -0.0146f;
 constexpr float kLog2e = 1.4426950408889634f;
 

@@ -1013,7 +1013,7 @@ __global__ void __launch_bounds__(64, 4) k_raster_backward_wave(
       hits = (p < most0 && (!cull || quadrant_hit(sa, sb, tile_x0, tile_y0, sq)) ? 1u : 0u) |
              (p < most1 && (!cull || quadrant_hit(sa, sb, tile_x0, tile_y0, sq + 1)) ? 2u : 0u);
       ill = ill_conditioned(r);
-      clamp = sb.y >= kLog2AlphaMax;
+      clamp = ill || sb.y >= kLog2AlphaMax;
     }
     if (b0 >= 32) d = list[b0 - 32 + se];  // the next entries' records
     const uint64_t touched = __ballot(hits != 0u);

@@ -1690,3 +1690,40 @@ def test_a_refused_render_writes_no_output():
         r.set_tuning(g4d.G4D_TUNE_ROUND_INSTANCES, need)
         for a, b in zip(r.render([cam], [0.5]), ref):
             assert torch.equal(a, b)
+
+
+def test_backward_clamps_the_alpha_of_very_long_needles():
+    """Footprints thousands of pixels long and under one wide: in FP32 the quadratic
+    form of such a record comes out positive for some pixels, so that an opacity
+    of 0.985 gives alphas above the clamp at 0.99, and above 1. Three
+    1920x1080 views in one launch (24480 tiles: one wave per tile) give the
+    gradient lines of three launches of one view (8160 tiles: four waves per tile),
+    whose products are the same value for value. The lines' position sums are
+    then formed in FP64, and the colour sums are float32 sums of 256 terms a tile,
+    as in test_backward_one_wave_per_tile. (The lines, not the primitives'
+    gradients: those multiply the float32 rounding of a pair's dL/dSigma by the
+    square of the long axis.)"""
+    n = 200
+    sc = scenegen.random_scene(95, n, sh_degree=1, t_order=1)
+    sc.log_scales4[:] = np.float32([2.5, -8.0, -8.0, 3.0])
+    th = 0.5 * np.random.default_rng(95).uniform(0, np.pi, n)
+    q = np.stack([np.cos(th), np.sin(th), 0 * th, 0 * th], 1).astype(np.float32)
+    sc.q_left[:], sc.q_right[:] = q, q          # a turn by 2 th in the image plane
+    sc.means4[:, :3] *= np.float32(0.5)
+    sc.opacity_logit[:] = np.float32(math.log(0.985 / 0.015))
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.look_at_camera((0.01 * v, 0.0, 4.0), 1920, 1080) for v in range(3)]
+    times, k = [0.4, 0.5, 0.6], 3 * 1920 * 1080
+    dl = torch.from_numpy(np.random.default_rng(96).uniform(-1, 1, 3 * k).astype(np.float32)).cuda()
+
+    def lines(v0, v1):
+        r.render(cams[v0:v1], times[v0:v1])
+        r.backward(dl[k * v0:k * v1])
+        out = np.zeros(((v1 - v0) * n, 16))
+        out[r.debug("ids")] = r.debug("grad2d")
+        return out
+
+    got, want = lines(0, 3), np.concatenate([lines(v, v + 1) for v in range(3)])
+    assert np.isfinite(got).all()
+    for col in range(9):
+        assert np.linalg.norm(got[:, col] - want[:, col]) <= 3e-5 * np.linalg.norm(want[:, col]), col
