@@ -1023,7 +1023,8 @@ __global__ void __launch_bounds__(kThreads) k_emit(const uint32_t* n_dev, uint32
     // come from the same spans
     const uint32_t start = offs[r0], iend = min(min(offs[r1], lim), start + carry);
     const uint32_t g_end = (iend + 3) / 4;
-    for (uint32_t c0 = start / 4; c0 * 4 < iend; c0 += kEmitGroups) {
+    // (no instance of these records to write: the map would name no row)
+    for (uint32_t c0 = start / 4; start < iend && c0 * 4 < iend; c0 += kEmitGroups) {
       if (c0 != start / 4) __syncthreads();  // the previous chunk's reads of the map are done
       const uint32_t c1 = min(c0 + (uint32_t)kEmitGroups, g_end);
       for (uint32_t j = threadIdx.x; j < rows_here; j += kThreads) {

@@ -1727,3 +1727,35 @@ def test_backward_clamps_the_alpha_of_very_long_needles():
     assert np.isfinite(got).all()
     for col in range(9):
         assert np.linalg.norm(got[:, col] - want[:, col]) <= 3e-5 * np.linalg.norm(want[:, col]), col
+
+
+@pytest.mark.parametrize("front", [1, 2, 3, 4])
+def test_emission_of_records_without_a_tile(front):
+    """Active records whose alpha-floor ellipse lies between the pixel centres of
+    two tiles have no instance: blocks of 64 such records behind `front` instances, so that
+    their place in the output is and is not a multiple of four. Image and lists
+    are those of the scene without them."""
+    cam = scenegen.look_at_camera((0.0, 0.0, 4.0), 64, 48)
+    rng = np.random.default_rng(97)
+    n, m = 200, front + 5
+    z = np.concatenate([np.linspace(1.0, 1.2, front), np.linspace(2.0, 3.0, n), np.linspace(4.0, 4.5, 5)])
+    u = np.concatenate([rng.uniform(4, 12, front), 16.0 + rng.uniform(-0.3, 0.3, n), rng.uniform(20, 28, 5)])
+    v = np.concatenate([rng.uniform(4, 12, front), rng.uniform(2, 46, n), rng.uniform(20, 28, 5)])
+    sc = scenegen.random_scene(98, n + m, sh_degree=1, t_order=1)
+    sc.q_left[:], sc.q_right[:] = np.float32([1, 0, 0, 0]), np.float32([1, 0, 0, 0])
+    sc.log_scales4[:] = np.float32([-9.0, -9.0, -9.0, 3.0])
+    sc.means4[:] = np.stack([(u - 32) * z / cam.fx, (24 - v) * z / cam.fy, 4 - z, 0 * z + 0.5], 1)
+    o = 1.0001 / 255
+    sc.opacity_logit[:] = np.float32(2.0)
+    sc.opacity_logit[front:front + n] = np.float32(math.log(o / (1 - o)))
+    r, _ = PT.gpu_setup(sc)
+    got = r.render([cam], [0.5])
+    st = r.stats()
+    assert st["active_total"] == n + m and st["instances"] == m
+    keep = np.r_[:front, front + n:front + n + 5]
+    for a in ("means4", "log_scales4", "q_left", "q_right", "opacity_logit", "coeffs"):
+        setattr(sc, a, getattr(sc, a)[keep])
+    f, _ = PT.gpu_setup(sc)
+    for a, b in zip(got, f.render([cam], [0.5])):
+        assert torch.equal(a, b)
+    assert f.stats()["instances"] == m and np.array_equal(r.debug("ranges"), f.debug("ranges"))
