@@ -152,7 +152,8 @@ g4d_status g4d_render(g4d_ctx* ctx, int32_t n_views, const g4d_camera* cams, con
  * render_backward (and invalidates a previous render's), and g4d_get_stats
  * does not describe it. Every call on one GPU, from any context, shares that
  * GPU's array: calls whose work overlaps on one GPU (other streams, other
- * threads) race; serialise them. Stage timing is off during the call. */
+ * threads) race and give wrong images, possibly after waiting seconds for one
+ * another; serialise them. Stage timing is off during the call. */
 g4d_status g4d_render_noalloc(g4d_ctx* ctx, int32_t n_views, const g4d_camera* cams, const float* times,
                               float* out_rgb, float* out_depth, float* out_alpha);
 

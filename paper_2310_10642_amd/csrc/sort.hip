@@ -13,6 +13,7 @@
 // Every pass is stable, so the result equals a stable sort by (tile, depth)
 // of the instances emitted in (view, index) order.
 #include <utility>
+#include "chain.h"
 #include "g4d_common.h"
 
 namespace g4d {
@@ -652,10 +653,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_rs_small(const K* keys_in, co
 // comes from what those have published per digit: their own count, then the sum
 // up to and with them, a flag in the same word. A tile publishes its count before it
 // waits, and waits only for tiles with smaller tickets, which running
-// workgroups hold: every wait ends, whatever else occupies the device.
+// workgroups hold: every wait ends, whatever else occupies the device. The
+// wait is bounded besides (chain_sum_before), for calls that share their
+// scratch and overlap although they must not.
 constexpr int kChainThreads = 1024, kChainItems = 4;  // tiles of 4096 pairs
-constexpr int kChainWindow = 8;                       // earlier tiles read at once
-constexpr uint32_t kChainCount = 1u << 30, kChainSum = 2u << 30, kChainMask = kChainCount - 1u;
 
 struct ChainedOffsets {
   uint32_t base;     // thread d < 256: pairs of smaller digits
@@ -670,28 +671,9 @@ struct ChainedOffsets {
   }
   __device__ __forceinline__ void ready(uint32_t ctot) {
     if (threadIdx.x >= 256) return;
-    uint32_t sum = 0;
-    int j = (int)tile - 1;
-    while (j >= 0) {
-      uint32_t w[kChainWindow];
-#pragma unroll
-      for (int i = 0; i < kChainWindow; ++i)
-        w[i] = j - i >= 0 ? __hip_atomic_load(&status[(size_t)(j - i) * 256 + threadIdx.x], __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT)
-                          : kChainSum;
-      int step = 0;
-      bool open = true;
-#pragma unroll
-      for (int i = 0; i < kChainWindow; ++i) {
-        open = open && w[i] != 0u;
-        if (open) {
-          sum += w[i] & kChainMask;
-          step = (w[i] & kChainSum) ? j + 1 : i + 1;
-          open = !(w[i] & kChainSum);
-        }
-      }
-      j -= step;
-    }
+    const uint32_t sum = chain_sum_before((int)tile, kChainPolls, [&](int t) {
+      return __hip_atomic_load(&status[(size_t)t * 256 + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
     if (tile) publish(kChainSum | (sum + ctot));
     run[threadIdx.x] = base + sum;
   }

@@ -105,6 +105,58 @@ def test_validation_before_any_hip_call():
     assert lib.g4d_destroy(None) == g4d.G4D_EINVAL
 
 
+def test_chained_sort_waits_end():
+    """The look-back of the chained sort (csrc/chain.h) on the host: the sum of the
+    tiles before it, whatever of them is published at first and however late the rest is,
+    and an end of the wait when a tile never publishes."""
+    import shutil
+    import subprocess
+    import tempfile
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    src = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "chain.h"
+using namespace g4d;
+int main() {
+  std::srand(1);
+  for (int run = 0; run < 20000; ++run) {
+    const int tile = std::rand() % 200, late = 1 + std::rand() % 50;
+    std::vector<uint32_t> count(tile), word(tile);
+    uint32_t want = 0;
+    for (int t = 0; t < tile; ++t) want += count[t] = std::rand() % 4097;
+    const int sums = tile ? std::rand() % tile : 0;  // the last tile with its sum published
+    uint32_t up = 0;
+    for (int t = 0; t < tile; ++t) {
+      up += count[t];
+      word[t] = t == 0 || t == sums || (t < sums && std::rand() % 2) ? kChainSum | up : kChainCount | count[t];
+    }
+    std::vector<int> after(tile);  // readings until the word is there
+    for (int& a : after) a = std::rand() % 3 ? 0 : std::rand() % late;
+    const auto load = [&](int t) { return after[t]-- > 0 ? 0u : word[t]; };
+    if (chain_sum_before(tile, 1000, load) != want) return std::printf("run %d\n", run), 1;
+  }
+  long reads = 0;  // tile 2 never publishes
+  const auto never = [&](int t) { ++reads; return t == 2 ? 0u : kChainCount | 5u; };
+  const uint32_t got = chain_sum_before(6, 1000, never);
+  if (got != 15 || reads > 1010 * kChainWindow) return std::printf("%u %ld\n", got, reads), 1;
+  static_assert(kChainPolls >= 1u << 16 && kChainPolls <= 1u << 20, "seconds at most");
+  return 0;
+}
+"""
+    with tempfile.TemporaryDirectory() as d:
+        path, exe = os.path.join(d, "chain.cpp"), os.path.join(d, "chain")
+        with open(path, "w") as f:
+            f.write(src)
+        subprocess.run([cxx, "-std=c++17", "-O1", "-Wno-unknown-pragmas",
+                        "-I", os.path.join(ROOT, "paper_2310_10642_amd", "csrc"), path, "-o", exe], check=True)
+        p = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout + p.stderr
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU: --gpus above 1 exits with a message before
     touching any device."""
