@@ -113,7 +113,6 @@ constexpr int kCntNF = kCntTot + 4;
 // then the length of the round's list of primitives active in some view
 constexpr int kCntPList = kCntNF + kMaxViews;
 constexpr int kCntQueue = kCntPList + 1;  // the rasterisers' tile queue head
-constexpr int kCntBeyond = kCntPList + 2;  // whether a round is beyond the guess at its counts
 constexpr int kCntWords = kCntPList + 4;
 constexpr uint32_t kOnDevice = 0xFFFFFFFFu;  // a round count known only on the device
 // Tiles per round (unless one view alone has more): tile ids then fit 16
@@ -389,6 +388,17 @@ int round_tiles(const g4d_ctx* c, int v0, int v1) {
   return (int)t;
 }
 
+// The views of a round, with their first tiles in it.
+std::vector<ViewDev> round_views(const g4d_ctx* c, int v0, int v1) {
+  std::vector<ViewDev> vr(c->views_h.begin() + v0, c->views_h.begin() + v1);
+  int tile_base = 0;
+  for (ViewDev& d : vr) {
+    d.tile_base = tile_base;
+    tile_base += d.tiles_x * d.tiles_y;
+  }
+  return vr;
+}
+
 // Per-pair stage of one round, views [v0, v1): preprocess every (view,
 // primitive) pair, compact the active ones, sort them by depth, gather the
 // records in that order and scan their tile counts. Counts stay on the device.
@@ -403,12 +413,7 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   c->bound = -1;
   hipStream_t s = c->stream;
   const int nv = v1 - v0;
-  std::vector<ViewDev> vr(c->views_h.begin() + v0, c->views_h.begin() + v1);
-  int tile_base = 0;
-  for (ViewDev& d : vr) {
-    d.tile_base = tile_base;
-    tile_base += d.tiles_x * d.tiles_y;
-  }
+  const std::vector<ViewDev> vr = round_views(c, v0, v1);
   const uint64_t vn = (uint64_t)c->n * nv;
   if ((st = ensure(c, c->views_d, sizeof(ViewDev) * nv))) return st;
   const size_t vgroups = pair_groups((int)c->n), groups = vgroups * nv;
@@ -467,7 +472,7 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   if (guess) {
     host.max_records = guess->A;
     host.max_instances = guess->I;
-    host.beyond = cnt + kCntBeyond;
+    host.guess_views = P<ViewDev>(c->views_d);
   }
   int tile_rows = 0;
   for (const ViewDev& d : vr) tile_rows = std::max(tile_rows, (int)d.tiles_y);
@@ -608,9 +613,7 @@ g4d_status bin_tiles(g4d_ctx* c, int tiles, uint32_t a_max, uint32_t cap) {
   return G4D_OK;
 }
 
-// guess: the round's counts are guesses, and nothing is written if they are too small
-g4d_status rasterise_round(g4d_ctx* c, const g4d_ctx::Round& r, float* out_rgb, float* out_depth, float* out_alpha,
-                           bool guess = false) {
+g4d_status rasterise_round(g4d_ctx* c, const g4d_ctx::Round& r, float* out_rgb, float* out_depth, float* out_alpha) {
   hipStream_t s = c->stream;
   g4d_status st = join_side(c);  // the records' colours
   if (st) return st;
@@ -622,8 +625,7 @@ g4d_status rasterise_round(g4d_ctx* c, const g4d_ctx::Round& r, float* out_rgb, 
                         r.v1 - r.v0,
                         P<ViewDev>(c->views_d), P<uint2>(c->ranges), P<uint32_t>(c->ival), P<Record>(c->rec_sorted),
                         c->flow_mode ? kZero3 : c->opts.bg, c->flow_mode ? 2 : 3, c->ellipse_cull,
-                        guess ? P<uint32_t>(c->counters) + kCntBeyond : nullptr, out_rgb, out_depth, out_alpha,
-                        P<float>(c->pix_t), P<uint32_t>(c->pix_last), s);
+                        out_rgb, out_depth, out_alpha, P<float>(c->pix_t), P<uint32_t>(c->pix_last), s);
   stage_end(c, G4D_STAGE_RASTER_FWD);
   HIPCHK(c, hipGetLastError());
   return G4D_OK;
@@ -1046,7 +1048,7 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
       guessed = ahead;
       if (ahead) {
         if ((st = bin_tiles(c, tiles_k, a_cap, (uint32_t)i_cap))) return st;
-        if ((st = rasterise_round(c, guess, out_rgb, out_depth, out_alpha, /*guess=*/true))) return st;
+        if ((st = rasterise_round(c, guess, out_rgb, out_depth, out_alpha))) return st;
       }
       if ((st = take_counts(c, v0, k, A, inst))) return st;
       c->inst_hint = std::max((double)inst / std::max(tiles_k, 1), c->inst_hint * (15.0 / 16.0));
@@ -1059,7 +1061,11 @@ static g4d_status render_impl(g4d_ctx* c, int32_t n_views, const g4d_camera* cam
     }
     g4d_ctx::Round r{v0, v0 + k, round_tiles(c, v0, v0 + k), A, (uint32_t)inst};
     if (!ahead) {
-      if (guessed) launch_fill_u32(cnt + kCntI, 1, r.I, s);  // (zero, being beyond the guess)
+      if (guessed) {  // beyond the guess: the total is zero, and the views' widths
+        launch_fill_u32(cnt + kCntI, 1, r.I, s);
+        const std::vector<ViewDev> vr = round_views(c, r.v0, r.v1);
+        launch_set_views(vr.data(), r.v1 - r.v0, P<ViewDev>(c->views_d), ZeroWords{}, s);
+      }
       if ((st = bin_tiles(c, r.tiles, r.A, r.I))) return st;
     }
     c->rounds.push_back(r);

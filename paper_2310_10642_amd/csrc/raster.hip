@@ -291,7 +291,6 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
                                                               const uint32_t* __restrict__ ival,
                                                               const Record* __restrict__ recs, float bg0, float bg1,
                                                               float bg2, int channels, bool cull,
-                                                              const uint32_t* __restrict__ skip,
                                                               float* __restrict__ out_rgb,
                                                               float* __restrict__ out_depth,
                                                               float* __restrict__ out_alpha,
@@ -303,7 +302,6 @@ __global__ void __launch_bounds__(256 / NQ) k_raster_forward(const uint32_t* __r
   // the walk reads up to four entries past the last
   __shared__ Record s_rec[kWaves][68];
   __shared__ uint32_t s_item;
-  if (skip && *skip) return;
   int tile;
   for (bool first = true; next_item(order, n_items, queue, &s_item, first, tile); first = false) {
   const int vi = find_view(views, n_views, tile);
@@ -1214,21 +1212,20 @@ unsigned item_grid(K kernel, int threads, int total_tiles, uint32_t* queue, int 
 template <bool DEPTH, int NQ>
 void launch_fwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blocks, int n_views,
                 const ViewDev* views, const uint2* ranges, const uint32_t* ival, const Record* rec_sorted,
-                const float* bg, int channels, bool cull, const uint32_t* skip, float* out_rgb, float* out_depth,
-                float* out_alpha, float* pix_t, uint32_t* pix_last, hipStream_t s) {
+                const float* bg, int channels, bool cull, float* out_rgb, float* out_depth, float* out_alpha,
+                float* pix_t, uint32_t* pix_last, hipStream_t s) {
   const unsigned grid = item_grid(k_raster_forward<DEPTH, NQ>, 256 / NQ, total_tiles, queue, blocks, s);
   hipLaunchKernelGGL((k_raster_forward<DEPTH, NQ>), dim3(grid), dim3(256 / NQ), 0, s, order, (uint32_t)total_tiles,
-                     queue, n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], channels, cull, skip,
-                     out_rgb, out_depth, out_alpha, pix_t, pix_last);
+                     queue, n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], channels, cull, out_rgb,
+                     out_depth, out_alpha, pix_t, pix_last);
 }
 
 }  // namespace
 
 void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* queue, int blocks, int n_views,
                            const ViewDev* views, const uint2* ranges, const uint32_t* ival,
-                           const Record* rec_sorted, const float* bg, int channels, bool cull, const uint32_t* skip,
-                           float* out_rgb, float* out_depth, float* out_alpha, float* pix_t, uint32_t* pix_last,
-                           hipStream_t s) {
+                           const Record* rec_sorted, const float* bg, int channels, bool cull, float* out_rgb,
+                           float* out_depth, float* out_alpha, float* pix_t, uint32_t* pix_last, hipStream_t s) {
   if (total_tiles == 0) return;
   // Quadrants per wave, by the waves that the launch would have (8192 stay
   // resident): wider waves share more work per entry, but leave a small launch
@@ -1241,7 +1238,7 @@ void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* que
   // without, 16 mixed views of 1M 654 -> 635.)
 #define G4D_FWD(D, NQ)                                                                                            \
   launch_fwd<D, NQ>(total_tiles, order, queue, blocks, n_views, views, ranges, ival, rec_sorted, bg, channels, cull, \
-                    skip, out_rgb, out_depth, out_alpha, pix_t, pix_last, s)
+                    out_rgb, out_depth, out_alpha, pix_t, pix_last, s)
   const bool d = out_depth != nullptr;
   if (total_tiles < 2 * 8192) {
     if (d) G4D_FWD(true, 1); else G4D_FWD(false, 1);

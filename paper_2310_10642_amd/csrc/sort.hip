@@ -760,12 +760,13 @@ __global__ void __launch_bounds__(kThreads) k_gather(const uint32_t* n_dev, uint
 // the sort and the rasteriser would take as many as the total says.
 __device__ __forceinline__ void write_totals(uint64_t sum, uint32_t n, uint32_t* total, unsigned long long* total64,
                                              const HostCounts& host) {
+  const bool fits = n <= host.max_records && sum <= host.max_instances;
   if (threadIdx.x == 0) {
-    const bool fits = n <= host.max_records && sum <= host.max_instances;
     *total = fits ? (uint32_t)sum : 0u;
     *total64 = sum;
-    if (host.beyond) *host.beyond = fits ? 0u : 1u;
   }
+  if (!fits && host.guess_views)
+    for (int v = threadIdx.x; v < host.n_views; v += 1024) host.guess_views[v].width = 0;
   if (host.counts) {
     if (threadIdx.x == 0) {
       host.counts[0] = n;
