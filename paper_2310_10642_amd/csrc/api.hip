@@ -439,9 +439,13 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   // up to 192 tiles of 4096 the one-launch passes (a workgroup waits for the
   // counts of all earlier tiles: see k_rs_chain for both sides), for up to
   // 8192 pairs the one-workgroup sort
-  const bool chained = vn > 8192 && est <= (3u << 18) && vn <= (size_t(1) << 24);
+  const bool may_chain = vn > 8192 && vn <= (size_t(1) << 24), chained = may_chain && est <= (3u << 18);
   const size_t chain_words = chained ? chain_scratch_words(vn) : 0;
-  if ((st = ensure(c, c->radix_scratch, 4 * std::max(radix_scratch_words(c->sort_blocks), chain_words)))) return st;
+  // (for either choice: the next call of the same shape, with other counts to
+  // go by, may be captured)
+  if ((st = ensure(c, c->radix_scratch,
+                   4 * std::max(radix_scratch_words(c->sort_blocks), may_chain ? chain_scratch_words(vn) : 0))))
+    return st;
   RenderParams p = make_params(c, nv);
   uint32_t* cnt = P<uint32_t>(c->counters);
   if (count) p.nonfinite = cnt + kCntNF + v0;

@@ -1759,3 +1759,33 @@ def test_emission_of_records_without_a_tile(front):
     for a, b in zip(got, f.render([cam], [0.5])):
         assert torch.equal(a, b)
     assert f.stats()["instances"] == m and np.array_equal(r.debug("ranges"), f.debug("ranges"))
+
+
+def test_capture_after_a_synchronous_render():
+    """The scratch of a call depends on its shape, not on the counts that earlier
+    calls saw: a sync-free render is captured right after a synchronous one of the
+    same shape, whose counts let the depth sort take the chained passes for the
+    first time (2.1M pairs, few of them active), and its replays give its image."""
+    from paper_2310_10642_amd import g4d
+    sc = scenegen.random_scene(101, 262145, sh_degree=0, t_order=0, mu_log_t=-4.0)
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.ring_camera(0.5 * v, 96, 64) for v in range(8)]
+    times = [0.1 * v for v in range(8)]
+    ref = r.render(cams, times)
+    assert 0 < r.stats()["active_total"] * 5 // 4 + 4096 < 3 << 18
+    out = [torch.empty_like(x) for x in ref]
+    r.set_tuning(g4d.G4D_TUNE_SYNC_FREE, 1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        r.render(cams, times, out=out)
+    for _ in range(3):
+        for t in out:
+            t.fill_(float("nan"))
+        x = torch.randn(512, 512, device="cuda")
+        _ = float((x @ x).sum())               # eager work and a synchronisation
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, ref):
+            assert torch.equal(a, b)
+    del graph
