@@ -33,6 +33,7 @@
 // tile in step at barriers: four, batches of 12 primitives (small launches), or
 // eight in two roles, batches of 16 (the smallest).
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "shade.h"
@@ -1179,17 +1180,19 @@ __global__ void __launch_bounds__(64, 4) k_raster_backward_wave(
   }  // items
 }
 
-// Workgroups of `kernel` that stay resident on the current device (looked
-// up once per kernel and device).
-template <typename K>
-unsigned resident_grid(K kernel, int threads) {
+// Workgroups of Kernel that stay resident on the current device (looked up
+// once per kernel, which has one workgroup size, and device: kernels of one
+// signature hold from 16 waves a CU to 32, in workgroups of one wave to eight).
+template <auto Kernel>
+unsigned resident_grid(int threads) {
   constexpr int kDevs = 64;
-  static unsigned cached[kDevs] = {};
+  static std::atomic<unsigned> cached[kDevs] = {};
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 1024;
-  if (dev >= 0 && dev < kDevs && cached[dev]) return cached[dev];
+  if (dev >= 0 && dev < kDevs)
+    if (const unsigned g = cached[dev]) return g;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1 || cus < 1)
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, Kernel, threads, 0) != hipSuccess || per_cu < 1 || cus < 1)
     return 1024;
   const unsigned g = (unsigned)(per_cu * cus);
   if (dev >= 0 && dev < kDevs) cached[dev] = g;
@@ -1198,11 +1201,11 @@ unsigned resident_grid(K kernel, int threads) {
 
 // Grid of a launch over total_tiles items: one workgroup per item, or with
 // a queue, `blocks` workgroups (-1: as many as stay resident).
-template <typename K>
-unsigned item_grid(K kernel, int threads, int total_tiles, uint32_t* queue, int blocks, hipStream_t s) {
+template <auto Kernel>
+unsigned item_grid(int threads, int total_tiles, uint32_t* queue, int blocks, hipStream_t s) {
   unsigned grid = (unsigned)total_tiles;
   if (queue) {
-    const unsigned want = blocks > 0 ? (unsigned)blocks : resident_grid(kernel, threads);
+    const unsigned want = blocks > 0 ? (unsigned)blocks : resident_grid<Kernel>(threads);
     grid = std::min(grid, want);
     launch_fill_u32(queue, 1, 0u, s);
   }
@@ -1214,7 +1217,7 @@ void launch_fwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blo
                 const ViewDev* views, const uint2* ranges, const uint32_t* ival, const Record* rec_sorted,
                 const float* bg, int channels, bool cull, float* out_rgb, float* out_depth, float* out_alpha,
                 float* pix_t, uint32_t* pix_last, hipStream_t s) {
-  const unsigned grid = item_grid(k_raster_forward<DEPTH, NQ>, 256 / NQ, total_tiles, queue, blocks, s);
+  const unsigned grid = item_grid<k_raster_forward<DEPTH, NQ>>(256 / NQ, total_tiles, queue, blocks, s);
   hipLaunchKernelGGL((k_raster_forward<DEPTH, NQ>), dim3(grid), dim3(256 / NQ), 0, s, order, (uint32_t)total_tiles,
                      queue, n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], channels, cull, out_rgb,
                      out_depth, out_alpha, pix_t, pix_last);
@@ -1266,7 +1269,7 @@ void launch_bwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blo
   // tiles 368 / 259, 690 174 / 122, 1200 199 / 143, 1900 138 / 134, 2961 162 / 165,
   // 5.4k 205 / 229; the 5k-primitive step's 520 tiles 45.6 / 32.
   if (total_tiles >= 5 * 4096) {
-    const unsigned grid = item_grid(k_raster_backward_wave<HD, HA>, 64, total_tiles, queue, blocks, s);
+    const unsigned grid = item_grid<k_raster_backward_wave<HD, HA>>(64, total_tiles, queue, blocks, s);
     hipLaunchKernelGGL((k_raster_backward_wave<HD, HA>), dim3(grid), dim3(64), 0, s, order, (uint32_t)total_tiles,
                        queue, n_views, views, ranges, ival, rec_sorted, bg[0], bg[1], bg[2], dl_rgb, dl_depth, dl_alpha,
                        pix_t, pix_last, grad2d, mark_blended, cull, loss);
@@ -1275,7 +1278,8 @@ void launch_bwd(int total_tiles, const uint32_t* order, uint32_t* queue, int blo
   const bool pipe = total_tiles < 2048;
   const auto kernel = pipe ? k_raster_backward<HD, HA, true> : k_raster_backward<HD, HA, false>;
   const unsigned threads = pipe ? 512 : 256;
-  const unsigned grid = item_grid(kernel, threads, total_tiles, queue, blocks, s);
+  const unsigned grid = pipe ? item_grid<k_raster_backward<HD, HA, true>>(512, total_tiles, queue, blocks, s)
+                             : item_grid<k_raster_backward<HD, HA, false>>(256, total_tiles, queue, blocks, s);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, order, (uint32_t)total_tiles, queue, n_views, views,
                      ranges, ival, rec_sorted, bg[0], bg[1], bg[2], dl_rgb, dl_depth, dl_alpha, pix_t, pix_last,
                      grad2d, mark_blended, cull, loss);

@@ -1789,3 +1789,35 @@ def test_capture_after_a_synchronous_render():
         for a, b in zip(out, ref):
             assert torch.equal(a, b)
     del graph
+
+
+def test_resident_workgroups_of_each_kernel():
+    """G4D_TUNE_PERSISTENT_BLOCKS = -1 sizes each rasteriser's grid by that
+    kernel's own residency, whatever was launched before: after one view (5440
+    tiles: workgroups of 256 threads, 5 to a CU in the backward) eight views (one wave per
+    tile, 16 to a CU) hold the whole device. Results are the same; the eight views'
+    backward takes 1.3 times the time of one workgroup per tile (2.4 on the
+    first kernel's grid)."""
+    from paper_2310_10642_amd import g4d
+    wl = scenegen.bench_workload(8)
+    r, _ = PT.gpu_setup(wl.scene)
+    times = [float(x) for x in wl.times]
+    dl = torch.from_numpy(np.random.default_rng(58).uniform(-1, 1, 8 * 3 * 1352 * 1014).astype(np.float32)).cuda()
+    ms, out = {}, {}
+    for queue in (0, -1):
+        r.set_tuning(g4d.G4D_TUNE_PERSISTENT_BLOCKS, queue)
+        for views in (1, 8):
+            best = float("inf")
+            for _ in range(6):
+                img = r.render(wl.cameras[:views], times[:views])
+                r.stage_timing(True)
+                grads = r.backward(dl[:img[0].numel()])
+                best = min(best, r.stage_times()["raster_bwd"][0])
+                r.stage_timing(False)
+            out[queue, views], ms[queue, views] = (img, grads), best
+    for views in (1, 8):
+        for a, b in zip(out[0, views][0], out[-1, views][0]):
+            assert torch.equal(a, b)
+        _close_grads(out[-1, views][1], out[0, views][1])
+    _say(f"  {ms}")
+    assert ms[-1, 8] <= 1.8 * ms[0, 8]
