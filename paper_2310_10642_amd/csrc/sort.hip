@@ -1304,10 +1304,12 @@ void radix_sort16(uint16_t* keys, uint32_t* vals, uint16_t* keys_alt, uint32_t* 
   // digit runs of 32 instances write half as many partial cache lines, and
   // fewer lines are open at once, than with five 256-thread ones (per pass:
   // 109 -> 101 us for 26M instances, 186 -> 174 for 44M, 368 -> 325 for 80M,
-  // 1139 -> 980 for 236M; equal at 14M, and at 3.4M 18.4 -> 21.4)
+  // 1139 -> 980 for 236M; equal at 14M, and at 3.4M 18.4 -> 21.4). Fewer if fewer
+  // are asked for, and beyond the default of 1280 more in proportion (80M: 204
+  // workgroups 455 us a pass, 409 366, 512 333, 819 364)
   if (n_max >= 1u << 24)
-    radix_passes_run<uint16_t, 512>(keys, vals, keys_alt, vals_alt, n_dev, n_max, bit0, bit1, std::min(grid, 512),
-                                    scratch, s, last_ranges, n_ranges);
+    radix_passes_run<uint16_t, 512>(keys, vals, keys_alt, vals_alt, n_dev, n_max, bit0, bit1,
+                                    std::max(std::min(grid, 512), grid / 5 * 2), scratch, s, last_ranges, n_ranges);
   else
     radix_passes_run(keys, vals, keys_alt, vals_alt, n_dev, n_max, bit0, bit1, grid, scratch, s, last_ranges,
                      n_ranges);

@@ -1821,3 +1821,21 @@ def test_resident_workgroups_of_each_kernel():
         _close_grads(out[-1, views][1], out[0, views][1])
     _say(f"  {ms}")
     assert ms[-1, 8] <= 1.8 * ms[0, 8]
+
+
+@pytest.mark.parametrize("blocks", [1, 4, 512, 2048])
+def test_large_tile_sort_on_any_grid(blocks):
+    """G4D_TUNE_SORT_BLOCKS sizes the wide workgroups' grid of the tile sort from
+    2^24 instances on too (1, 4, 512 and 818 workgroups here); the image and the
+    tile lists are those of the default."""
+    from paper_2310_10642_amd import g4d
+    r, _ = PT.gpu_setup(_big_splat_scene(71, 3300, grow=3.0, sh=1, to=1, mu_log_t=1.0))
+    cams = [scenegen.ring_camera(0.3 * v, 512, 512) for v in range(6)]
+    times = [0.1 * v for v in range(6)]
+    one = r.render(cams, times)
+    vals = r.debug("tile_vals")
+    assert r.stats()["rounds"] == 1 and len(vals) >= 1 << 24
+    r.set_tuning(g4d.G4D_TUNE_SORT_BLOCKS, blocks)
+    for a, b in zip(one, r.render(cams, times)):
+        assert torch.equal(a, b)
+    assert np.array_equal(vals, r.debug("tile_vals"))
