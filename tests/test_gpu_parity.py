@@ -1839,3 +1839,18 @@ def test_large_tile_sort_on_any_grid(blocks):
     for a, b in zip(one, r.render(cams, times)):
         assert torch.equal(a, b)
     assert np.array_equal(vals, r.debug("tile_vals"))
+
+
+def test_counts_that_come_back():
+    """The guess at the counts forgets a crowded render: after 40 sparse ones the
+    next crowded one is beyond it again, and the images, statistics and lists are
+    those of a new context."""
+    sc = _near_and_far_scene(103, 300, 20000)
+    r, _ = PT.gpu_setup(sc)
+    cams = [scenegen.look_at_camera((0.2, 0.1, 4.0), 160, 120)]
+    for t in [0.9] + [0.1] * 40 + [0.9, 0.1, 0.9]:
+        got = r.render(cams, [t])
+        f, _ = PT.gpu_setup(sc)
+        for a, b in zip(got, f.render(cams, [t])):
+            assert torch.equal(a, b), t
+        assert r.stats() == f.stats() and np.array_equal(r.debug("tile_vals"), f.debug("tile_vals"))
