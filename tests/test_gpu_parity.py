@@ -1854,3 +1854,50 @@ def test_counts_that_come_back():
         for a, b in zip(got, f.render(cams, [t])):
             assert torch.equal(a, b), t
         assert r.stats() == f.stats() and np.array_equal(r.debug("tile_vals"), f.debug("tile_vals"))
+
+
+@pytest.mark.parametrize("t_cull", [0.0, 1e-30, 0.05, 0.999, 1.0])
+@pytest.mark.parametrize("t", [0.0, 1000.5, -3e7])
+def test_temporal_filter_against_the_oracle(t, t_cull, monkeypatch):
+    """The pairs that pass p(t) >= t_cull are the FP64 definition's: primitives from
+    1e-4 of the boundary to ten times it away, temporal scales from e^-80 to e^40
+    (squares that underflow and overflow single precision), at times near and far
+    from zero, half of them with quaternions of any orientation and of norms from 2^-60
+    to 2^60. Left out: pairs within 1e-6 of the boundary, or whose rectangle
+    FP64 rounding decides."""
+    from paper_2310_10642_amd import g4d
+    n, rng = 6000, np.random.default_rng(107)
+    sc = scenegen.random_scene(107, n, sh_degree=0, t_order=0)
+    half = n // 2
+    sc.q_left[:half], sc.q_right[:half] = np.float32([1, 0, 0, 0]), np.float32([1, 0, 0, 0])
+    sc.log_scales4[:half, 3] = rng.uniform(-80, 40, half).astype(np.float32)
+    sc.log_scales4[half:, 3] = rng.uniform(-6, 2, n - half).astype(np.float32)
+    sc.q_left[half:] *= (2.0 ** rng.integers(-60, 61, (n - half, 1))).astype(np.float32)
+    sc.q_right[half:] *= (2.0 ** rng.integers(-60, 61, (n - half, 1))).astype(np.float32)
+    sc.means4[:, :3] *= np.float32(0.3)
+    p = O.params_from_scene(sc)
+    s44 = O.covariance_4d(p["log_scales4"], p["q_left"], p["q_right"])[:, 3, 3].numpy()
+    edge = np.sqrt(-2.0 * np.log(min(max(t_cull, 1e-300), 0.999)) * s44)
+    off = rng.choice([0.0, 0.9, 0.999, 0.9999, 1.0001, 1.001, 1.1, 10.0], n) * rng.choice([-1.0, 1.0], n)
+    with np.errstate(over="ignore"):
+        sc.means4[:, 3] = np.clip(t + off * edge, -3e38, 3e38).astype(np.float32)
+    monkeypatch.setitem(O.CONVENTIONS, "t_cull", PT.f32(t_cull))
+    cam = scenegen.look_at_camera((0.3, 0.2, 3.5), 96, 80)
+    pre = O.preprocess(O.params_from_scene(sc), O.to_ocamera(cam), PT.f32(t), 0, 0)
+    pt, rects = pre["pt"].numpy(), (pre["rect_sure"].numpy(), pre["rect_maybe"].numpy(), pre["rect"].numpy())
+    full = [(r[:, 2] > r[:, 0]) & (r[:, 3] > r[:, 1]) for r in rects]
+    kept = pt >= PT.f32(t_cull)
+    sure = (np.abs(pt - PT.f32(t_cull)) > 1e-6 * PT.f32(t_cull)) | (sc.means4[:, 3] == np.float32(t)) | (t_cull == 0)
+    sure &= np.isfinite(pt) & (~kept | (full[0] == full[1]) | (t_cull in (0.0, 1.0)))  # (there the oracle is never sure)
+    want = kept & full[2] & (pre["z"].numpy() > O.CONVENTIONS["near"])
+    r = g4d.Renderer(0, 0, t_cull=t_cull)
+    params = [torch.from_numpy(np.ascontiguousarray(a)).cuda()
+              for a in (sc.means4, sc.log_scales4, sc.q_left, sc.q_right, sc.opacity_logit, sc.coeffs)]
+    r.set_primitives(*params)
+    r.set_tuning(g4d.G4D_TUNE_ELLIPSE_CULL, 0)
+    r.render([cam], [t])
+    got = np.zeros(n, bool)
+    got[r.debug("ids")] = True
+    _say(f"  t {t} t_cull {t_cull}: {int(got.sum())} active, {int((want & sure).sum())} surely, {int((~sure).sum())} left out")
+    assert sure.sum() > 0.7 * n and (want & sure).sum() > 100
+    assert np.array_equal(got[sure], want[sure]), np.flatnonzero(sure & (got != want))[:10]
