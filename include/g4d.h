@@ -133,7 +133,8 @@ g4d_status g4d_set_primitives(g4d_ctx* ctx, int64_t n, const float* means4, cons
  * a round over the instance cap is shrunk and binned again. Each view's
  * result does not depend on the grouping. Synchronises the stream once per binning attempt, to size the
  * tile-instance arena (see G4D_TUNE_SYNC_FREE for the mode that does not).
- * G4D_ECAPACITY if one view alone exceeds the cap. Views reach the device as
+ * G4D_ECAPACITY if one view alone exceeds the cap; the outputs of it and of
+ * the views after it are left as they were. Views reach the device as
  * kernel arguments: cams and times may be reused as soon as this returns. */
 g4d_status g4d_render(g4d_ctx* ctx, int32_t n_views, const g4d_camera* cams, const float* times,
                       float* out_rgb, float* out_depth, float* out_alpha);
@@ -319,14 +320,16 @@ g4d_status g4d_get_stats(g4d_ctx* ctx, g4d_stats* out, int64_t* active_per_view)
  *
  * The rasteriser knobs of a (lds_batch, split_threshold, persistent_blocks)
  * tuning call map to these keys: lds_batch -> G4D_TUNE_LDS_BATCH (without
- * effect: the forward stages 64 entries per wave, the backward 12 entries at a
- * time, fixed by its LDS budget of five workgroups per CU and its 12-primitive
- * x 16-column second phase); persistent_blocks -> G4D_TUNE_PERSISTENT_BLOCKS;
- * split_threshold has no key: heavy tiles are not split. A wave owns an 8x8
- * quarter of its tile, so a split would not shorten its longest walk, and
- * with the tiles taken heaviest first the launch does not end on one heavy
- * tile (the heaviest carries at most an eighth of a resident workgroup's
- * share of the work on the workloads measured).                          */
+ * effect: the forward stages 64 entries per wave; the backward 32 with one wave
+ * per tile, 12 with four waves and 16 with eight, fixed by the LDS of the
+ * workgroups that share a CU and the shape of its second phase);
+ * persistent_blocks -> G4D_TUNE_PERSISTENT_BLOCKS; split_threshold has no key:
+ * heavy tiles are not split. By the launch's tiles a wave of the forward owns
+ * one, two or four 8x8 quarters of a tile, and a tile of the backward has eight
+ * waves, four or one: few tiles are spread over more waves, and a launch whose
+ * waves own whole tiles (40960 or more in the forward, 20480 in the backward)
+ * has some five times as many tiles as such waves stay resident. With the tiles taken
+ * heaviest first it does not end on one heavy tile.                        */
 enum {
   G4D_TUNE_SORT_BLOCKS = 1, G4D_TUNE_STAGE_TIMING = 2, G4D_TUNE_ROUND_PAIRS = 3, G4D_TUNE_ROUND_INSTANCES = 4,
   G4D_TUNE_SYNC_FREE = 5, G4D_TUNE_ARENA_INSTANCES = 6, G4D_TUNE_TILE_ORDER = 7, G4D_TUNE_AUTOTUNE = 8,
@@ -343,14 +346,15 @@ enum {
   G4D_STAGE_PREPROCESS = 0,   /* slice, project, cull (geometry) */
   G4D_STAGE_BINNING = 1,      /* compaction, depth sort, emission, tile sort, ranges; the
                                * 4DSH colour of the active records runs on a second stream
-                               * alongside, and the forward rasteriser waits for it */
+                               * alongside, up to the gather (for up to 2^17 pairs before it,
+                               * on the same stream) */
   G4D_STAGE_RASTER_FWD = 2,   /* the forward rasteriser alone */
   G4D_STAGE_RASTER_BWD = 3,   /* the backward rasteriser alone */
   G4D_STAGE_PREPROCESS_BWD = 4, /* zeroing the gradient lines, then the per-record and
                                  * per-primitive backward (two timed windows per round) */
   G4D_STAGE_LOSS = 5,          /* g4d_image_loss; in g4d_render_backward_loss the per-tile
                                  * loss sums (the per-pixel terms run in the backward rasteriser) */
-  G4D_STAGE_COLOUR = 6,       /* the 4DSH colour pass, timed on its own (second) stream */
+  G4D_STAGE_COLOUR = 6,       /* the 4DSH colour pass, timed on the stream it runs on */
   G4D_NUM_STAGES = 7
 };
 g4d_status g4d_stage_times(g4d_ctx* ctx, double* ms_out, int64_t* launches_out);

@@ -26,8 +26,8 @@ struct DevBuf {
 struct g4d_ctx {
   g4d_options opts{};
   hipStream_t stream = nullptr;
-  // The colour pass runs on a second stream, overlapping the instance
-  // emission and tile sort; the rasterisers wait for it.
+  // The colour pass of many pairs runs on a second stream, overlapping the
+  // compaction and the depth sort; the gather waits for it.
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_counts = nullptr;
   bool side_pending = false;
@@ -455,14 +455,13 @@ g4d_status enqueue_pairs(g4d_ctx* c, int v0, int v1, bool count, bool to_host = 
   launch_set_views(vr.data(), nv, P<ViewDev>(c->views_d),
                    ZeroWords{{cnt + kCntPList, cnt + kCntNF + v0, cnt + kCntMaxList},
                              {1u, count ? (uint32_t)nv : 0u, count && v0 == 0 ? 1u : 0u}}, s);
-  // 1. per (view, primitive): cull, slice, project (the colour follows the
-  //    gather, on the second stream)
+  // 1. per (view, primitive): cull, slice, project
   stage_begin(c);
   launch_preprocess(p, pair_bits(c), P<uint32_t>(c->gcount), P<uint32_t>(c->dkey),
                     P<Record>(c->rec), P<float4>(c->cdir), P<uint32_t>(c->radix_scratch), (uint32_t)chain_words, s);
   stage_end(c, G4D_STAGE_PREPROCESS);
-  // the records' colours on the second stream, beside the scans and the
-  // depth sort (joined before the gather copies the records)
+  // the records' colours, of many pairs on the second stream beside the
+  // compaction and the depth sort (joined before the gather copies the records)
   if ((st = fork_colour(c, p))) return st;
   // 2. compaction of active records
   stage_begin(c);

@@ -1233,12 +1233,10 @@ void launch_raster_forward(int total_tiles, const uint32_t* order, uint32_t* que
   // Quadrants per wave, by the waves that the launch would have (8192 stay
   // resident): wider waves share more work per entry, but leave a small launch
   // too few waves and a long tail. Measured (us, one / two / four quadrants per
-  // wave; 300k primitives at 1352x1014): 5.4k tiles 84 / 114 / 173, 10.9k 133 /
-  // 147 / 196, 16.3k 190 / 187, 21.8k 260 / 229 / 256, 32.6k 420 / 325 / 338 (with
-  // depth), 43.5k 446 / 376 / 351; without depth 10.9k 118 / 144, 16.3k 162 / 172,
-  // 21.8k 212 / 211, 32.6k 320 / 293. (All before the entries lay without gaps for
-  // two and four quadrants too: 43.5k then 419 -> 404 with depth, 358 -> 347
-  // without, 16 mixed views of 1M 654 -> 635.)
+  // wave; 300k primitives, views of 1352x1014), with the depth plane: 5.4k tiles 89 /
+  // 119 / 179, 10.9k 128 / 147 / 193, 16.3k 159 / 170 / 207, 21.8k 212 / 197 / 252,
+  // 32.6k 314 / 276 / 297, 43.5k 415 / 364 / 350; without: 80 / 112 / 170, 117 / 146 /
+  // 189, 146 / 166 / 203, 186 / 189 / 230, 278 / 259 / 286, 364 / 340 / 331.
 #define G4D_FWD(D, NQ)                                                                                            \
   launch_fwd<D, NQ>(total_tiles, order, queue, blocks, n_views, views, ranges, ival, rec_sorted, bg, channels, cull, \
                     out_rgb, out_depth, out_alpha, pix_t, pix_last, s)
