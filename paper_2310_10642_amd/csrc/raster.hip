@@ -81,6 +81,11 @@ __device__ __forceinline__ void stage_record(const Record& r, float4& sa, float4
   sc = hide ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(r.c.x, r.c.y, r.c.z, 0.f);
 }
 
+// For the backward, which divides by the opacity: that of a record with none (p(t)
+// underflows; only with the ellipse cull off and t_cull near 0 is it binned) is
+// held at the same place, so that its gradient is 0 instead of 0 / 0.
+__device__ __forceinline__ float nonzero_log2_opacity(float l2o) { return fmaxf(l2o, kHiddenLog2); }
+
 // Whether the record's alpha-floor ellipse (where opacity * exp(power) reaches
 // 1/255) meets the 8x8 quadrant q of the tile, whose pixel centres span
 // x0 + 8 (q & 1) + [0.5, 7.5], y0 + 8 (q >> 1) + [0.5, 7.5]. In the staged
@@ -628,7 +633,7 @@ __global__ void __launch_bounds__(PIPE ? 512 : 256, PIPE ? 4 : 5) k_raster_backw
   // staging lane by a shuffle) and a ballot gathers the four bits.
   auto stage = [&](int e0, int bb) {
     const int t = lane;
-    const float l2o = staged_log2_opacity(nxt);
+    const float l2o = nonzero_log2_opacity(staged_log2_opacity(nxt));
     if (t < kBatch && e0 + t < count) {
       stage_split(nxt, l2o, &s_a2[bb][t], &s_b2[bb][t], &s_c2[bb][t]);
       s_d2[bb][t] = nxt_d;
@@ -1005,6 +1010,7 @@ __global__ void __launch_bounds__(64, 4) k_raster_backward_wave(
       const Record r = recs[d];
       float4 sa, sb, sc;
       stage_record(r, sa, sb, sc);
+      sb.y = nonzero_log2_opacity(sb.y);
       sb.w = __uint_as_float(d);
       s_rec[se].a = sa;  // (both lanes of an entry write the same)
       s_rec[se].b = sb;
