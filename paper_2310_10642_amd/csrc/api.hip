@@ -1170,8 +1170,8 @@ g4d_status backward_impl(g4d_ctx* c, const LossSpec& ls, const float* rgb_in, co
     RenderParams p = make_params(c, nv);
     stage_begin(c);
     launch_preprocess_backward(p, pair_bits(c), P<int32_t>(c->slot), P<double>(c->grad2d), cnt + kCntA, a_max,
-                               P<uint32_t>(c->cval), P<Record>(c->rec_sorted), P<float>(c->bwd_scratch), g_means4, g_log_scales4, g_q_left,
-                               g_q_right, g_opacity_logit, g_coeffs, accumulate, c->densify, s);
+                               P<uint32_t>(c->cval), P<Record>(c->rec_sorted), P<float>(c->bwd_scratch), g_means4,
+                               g_log_scales4, g_q_left, g_q_right, g_opacity_logit, g_coeffs, accumulate, c->densify, s);
     stage_end(c, G4D_STAGE_PREPROCESS_BWD);
     HIPCHK(c, hipGetLastError());
     accumulate = true;

@@ -1632,7 +1632,8 @@ def _near_and_far_scene(seed, n_big, n_small):
     return sc
 
 
-@pytest.mark.parametrize("w,h,views,n_big", [(160, 120, 1, 1000), (160, 120, 3, 1000), (160, 120, 1, 200), (16, 16, 1, 1000)])
+@pytest.mark.parametrize("w,h,views,n_big", [(160, 120, 1, 1000), (160, 120, 3, 1000), (160, 120, 1, 200),
+                                             (16, 16, 1, 1000)])
 def test_records_beyond_the_guess(w, h, views, n_big):
     """A render whose records (and in two cases its instances) exceed the guess
     from earlier renders: few active primitives that cover the image, then
@@ -1672,7 +1673,8 @@ def test_a_refused_render_writes_no_output():
     sc = _big_splat_scene(93, 3000, grow=0.5, sh=1, to=1, mu_log_t=1.0)
     r, _ = PT.gpu_setup(sc)
     cam = scenegen.look_at_camera((0.3, 0.1, 3.5), 150, 110)
-    calls = (lambda out: r.render([cam], [0.5], out=out), lambda out: r.render_flow([cam], [0.5], 0.1, out=out[0][:2 * 150 * 110]),
+    calls = (lambda out: r.render([cam], [0.5], out=out),
+             lambda out: r.render_flow([cam], [0.5], 0.1, out=out[0][:2 * 150 * 110]),
              lambda out: r.render_noalloc([cam], [0.5], out))
     ref = [x.clone() for x in r.render([cam], [0.5])]
     need = r.stats()["instances"]
@@ -1898,7 +1900,8 @@ def test_temporal_filter_against_the_oracle(t, t_cull, monkeypatch):
     r.render([cam], [t])
     got = np.zeros(n, bool)
     got[r.debug("ids")] = True
-    _say(f"  t {t} t_cull {t_cull}: {int(got.sum())} active, {int((want & sure).sum())} surely, {int((~sure).sum())} left out")
+    _say(f"  t {t} t_cull {t_cull}: {int(got.sum())} active, {int((want & sure).sum())} surely, "
+         f"{int((~sure).sum())} left out")
     assert sure.sum() > 0.7 * n and (want & sure).sum() > 100
     assert np.array_equal(got[sure], want[sure]), np.flatnonzero(sure & (got != want))[:10]
 
